@@ -235,7 +235,7 @@ struct hm_handle {
   int2 *dns = nullptr, *lr = nullptr;
   Storage sto;
 
-  void *z = nullptr, *w = nullptr, *ypart = nullptr;
+  void *z = nullptr, *xt = nullptr, *w = nullptr, *ypart = nullptr;
   int64_t ypart_bytes = 0;
   std::unique_ptr<SolveWs> sws;         // graph-replay solve workspace
   std::vector<std::array<double, 2>> tune;   // autotuner: (unit columns, ms)
@@ -278,10 +278,9 @@ struct hm_handle {
     (void)hipDeviceSynchronize();
     for (auto& q : owned) cache_put(q.first, q.second);
   }
+  MvLeaves leaves() const { return MvLeaves{leaf_lo, leaf_m, ldpre, nleaf}; }
   MvPlan plan() const {
     MvPlan P;
-    P.runs = sto.runs;
-    P.nruns = sto.nruns;
     P.units = sto.units;
     P.nunits = sto.nunits;
     P.ubeg = sto.ubeg;
@@ -293,13 +292,16 @@ struct hm_handle {
     P.nlr = nl;
     P.meta1 = sto.meta1;
     P.nu1 = sto.nu1;
+    P.metax = sto.metax;
+    P.nux = sto.nux;
     P.ucol = sto.ucol;
     P.tbeg = sto.tbeg;
     P.titems = sto.titems;
-    P.L = MvLeaves{leaf_lo, leaf_m, ldpre, nleaf};
+    P.L = leaves();
     P.perm = perm;
     P.n = n;
     P.z = z;
+    P.xt = xt;
     P.w = w;
     P.su = sto.su;
     P.max_nr_t = max_nr_t;
@@ -378,7 +380,7 @@ void autotune_units(hm_handle* h, hipStream_t s) {
   int best = h->sto.unit_cols;
   float best_ms = 0.f;
   for (int ucols : kTuneCols) {
-    make_units(h->sto, h->ldpre, h->nleaf, ucols, [h](size_t b) { return h->alloc(b); }, s);
+    make_units(h->sto, h->leaves(), ucols, [h](size_t b) { return h->alloc(b); }, s);
     const MvPlan P = h->plan();
     matvec_dispatch(P, h->form, xt, yt, 1, 0, false, s);
     HM_HIP(hipEventRecord(e0, s));
@@ -394,7 +396,7 @@ void autotune_units(hm_handle* h, hipStream_t s) {
       best = ucols;
     }
   }
-  make_units(h->sto, h->ldpre, h->nleaf, best, [h](size_t b) { return h->alloc(b); }, s);
+  make_units(h->sto, h->leaves(), best, [h](size_t b) { return h->alloc(b); }, s);
   h->profiling = prof;
   dfree(xt, s);
   dfree(yt, s);
@@ -540,11 +542,13 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
   // ---- product workspace: z = [x ; t] with 16 columns, w for the
   // transposed product sized to at most 2 GB (fewer columns per pass)
   h->z = h->alloc((size_t)(n + h->sto.toff_total + 1) * kMaxNr * sizeof(double));
+  // x per leaf with the rows padded to ld (at most three more per leaf)
+  h->xt = h->alloc((size_t)(n + 3 * h->nleaf) * kMaxNr * sizeof(double));
   {
     // partial rows for the most units any unit size of the tuner produces
     int64_t nu = h->sto.nunits;
     if (p.flags & HM_AUTOTUNE)
-      nu = std::max(nu, count_units(h->sto, h->nleaf, kTuneCols[0], s));
+      nu = std::max(nu, count_units(h->sto, h->leaves(), kTuneCols[0], s));
     h->ypart_bytes = (nu + 1) * (int64_t)h->sto.ldmax * kMaxNr * (int64_t)sizeof(double);
     h->ypart = h->alloc((size_t)h->ypart_bytes);
   }

@@ -157,17 +157,26 @@ struct MvProfile {
   double ms[8];
   double launches[8];
 };
-// Unit of the per-row-leaf product kernels: columns [a, a + w) of run `run`
-// of row leaf `leaf` (at most kUnitCols columns), so that a leaf with a wide
-// panel is shared by several workgroups.  Units of a leaf are consecutive.
+// Unit of the per-row-leaf product kernels: w columns (at most the unit width)
+// of one run of a row leaf, so that a leaf with a wide panel is shared by
+// several workgroups.  Everything a workgroup needs to start its loads is in
+// the record: the address of the first column, the first column's index
+// (colmap, w), the leaf's first position, size and ld, and whether the panel
+// is dense (else U slices).  Units of a leaf are consecutive.
 struct Unit {
-  int32_t leaf, run, a, w;
+  uint64_t data;
+  int64_t col;
+  int32_t w, lo;
+  uint16_t ld, m, dense, pad;
 };
 constexpr int kUnitCols = 1024;
+// Columns of a phase-1 unit on the matrix cores: four tiles of 16 terms share
+// one read of x.  (In the narrower units of the one-column kernel -- 12
+// columns of FP64 slices at ld = 40 -- the x of a leaf is as many bytes as
+// the V it multiplies.)
+constexpr int kXUnitCols = 64;
 
 struct MvPlan {
-  const Run* runs;          // [nruns][nleaf]
-  int nruns;
   const Unit* units;        // nunits, grouped by leaf
   int64_t nunits;
   const int32_t* ubeg;      // leaf -> first unit (nleaf + 1)
@@ -179,6 +188,8 @@ struct MvPlan {
   int64_t nlr;
   const LrMeta* meta1;      // work units of the forward phase 1 (panel column chunks)
   int64_t nu1;
+  const LrMeta* metax;      // the same panels in units of 64 columns, for the matrix-core phase 1
+  int64_t nux;
   const int64_t* ucol;
   const int32_t* tbeg;      // column leaf -> first transposed item (nleaf + 1)
   const TItem* titems;
@@ -186,6 +197,7 @@ struct MvPlan {
   const int32_t* perm;
   int64_t n;
   void* z;                  // workspace: [x in Morton order ; t], 16 columns
+  void* xt;                 // workspace: x per leaf, NR columns of ld values each
   void* w;                  // workspace: panel-column partial dots
   const float* su;          // per-term scales of FP16 U factors (null: none)
   int max_nr_t;             // right-hand sides per transposed pass (w size)
@@ -237,6 +249,8 @@ struct Storage {
   LrMeta* meta = nullptr;
   LrMeta* meta1 = nullptr;   // forward phase-1 units
   int64_t nu1 = 0;
+  LrMeta* metax = nullptr;   // phase-1 units of kXUnitCols columns
+  int64_t nux = 0;
   int64_t* ucol = nullptr;
   uint64_t* uptr = nullptr;
   int64_t lr_elems = 0, toff_total = 0, nchunks = 0, u_items = 0, aca_reruns = 0;
@@ -245,6 +259,7 @@ struct Storage {
   Unit* units = nullptr;
   int64_t nunits = 0;
   int unit_cols = 0;
+  int esize = 0, lsize = 0;  // bytes of a dense and of a factor value
   int32_t* ubeg = nullptr;
   int ldmax = 0;
   float* su = nullptr;       // per-term scales when the factors are FP16
@@ -265,9 +280,8 @@ using Alloc = std::function<void*(size_t)>;
 template <typename T, typename TL>
 void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Alloc& alloc,
                    hipStream_t s);
-void make_units(Storage& out, const int64_t* ldpre, int64_t nleaf, int ucols, const Alloc& alloc,
-                hipStream_t s);
-int64_t count_units(const Storage& out, int64_t nleaf, int ucols, hipStream_t s);
+void make_units(Storage& out, const MvLeaves& L, int ucols, const Alloc& alloc, hipStream_t s);
+int64_t count_units(const Storage& out, const MvLeaves& L, int ucols, hipStream_t s);
 template <typename TL, typename TO>
 void launch_unpack(const int2* lr, int64_t b, const Cluster* cl, const int32_t* leaf_lo,
                    const int32_t* leaf_m, const int64_t* ldpre, const int2* cl_leaves,

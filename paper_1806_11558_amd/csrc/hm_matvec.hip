@@ -117,14 +117,15 @@ __device__ inline int64_t xcd_item(int64_t li, int64_t per) {
 
 // ------------------------------------------------------------------ gather
 template <typename VT, typename A>
-__global__ void k_gather(const VT* __restrict__ x, int nrhs, int k0, int nr,
+__global__ void k_gather(const VT* __restrict__ x, int nrhs, int k0, int nr, int nv,
                          const int32_t* __restrict__ perm, int64_t n, A* __restrict__ z) {
+  // columns nv .. nr - 1 (a pass wider than what is left) are zero
   const int64_t tot = n * nr;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < tot;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t p = e / nr;
     const int k = (int)(e % nr);
-    z[e] = (A)x[(int64_t)perm[p] * nrhs + k0 + k];
+    z[e] = k < nv ? (A)x[(int64_t)perm[p] * nrhs + k0 + min(k, nv - 1)] : (A)0;
   }
 }
 
@@ -211,7 +212,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   constexpr int G = Gran<T>::G;
   // loads per lane of the one-pass form; the phase-1 units of FP16 slices
   // are sized for eight, of FP32 and FP64 ones for four
-  constexpr int PMAX = (NR == 1 && sizeof(T) == 2) ? 8 : (NR <= 2 ? 4 : (NR <= 4 ? 2 : 1));
+  static_assert(NR <= 2, "more right-hand sides go to the matrix cores");
+  constexpr int PMAX = (NR == 1 && sizeof(T) == 2) ? 8 : 4;
   const int lane = threadIdx.x & 63;
   // wave-uniform block index: descriptors and leaf data come in by scalar loads
   const int64_t wid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -315,77 +317,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   }
 }
 
-// Several right-hand sides (NR >= 4): lane = (term j, right-hand-side group
-// kg) with JG terms per pass and KPL = NR JG / 64 right-hand sides per lane,
-// so every lane owns complete sums and no cross-lane reduction is needed.
-// All lanes walk the same rows; a lane reads its term's granule (shared by the
-// lanes of other groups) and its KPL values of each x row.
-template <typename T, typename A, int NR, int JG>
-__device__ inline void fwd1m_block(const LrMeta& M, const MvLeaves& L, A* __restrict__ z,
-                                   int64_t n, const float* __restrict__ su, int lane) {
-  constexpr int G = Gran<T>::G;
-  constexpr int KPL = NR * JG / 64;
-  static_assert(KPL >= 1 && KPL * (64 / JG) == NR, "lane layout must cover NR");
-  const int r = M.r;
-  const int jl = lane % JG, k0 = (lane / JG) * KPL;
-  const A sc0 = (A)1;
-  for (int jp = 0; jp < r; jp += JG) {
-    const int j = jp + jl;
-    const bool ok = j < r;
-    const int jc = ok ? j : r - 1;
-    A acc[KPL];
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) acc[k] = 0;
-    const T* S = reinterpret_cast<const T*>((uintptr_t)M.vptr);
-    for (int lf = M.sf; lf <= M.sl; ++lf) {
-      const int ld = (int)(L.ldpre[lf + 1] - L.ldpre[lf]);
-      const int m = L.m[lf], lo = L.lo[lf];
-      const T* col = S + (int64_t)jc * ld;
-      const A* zr = z + (int64_t)lo * NR + k0;
-      for (int i0 = 0; i0 < m; i0 += G) {
-        typename Gran<T>::E sv[G];
-        Gran<T>::load(col + i0, sv);
-#pragma unroll
-        for (int e = 0; e < G; ++e) {
-          if (i0 + e < m) {                              // uniform over the wavefront
-            A xv[KPL];
-            load_row<A, KPL>(zr + (int64_t)(i0 + e) * NR, xv);
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) acc[k] += (A)sv[e] * xv[k];
-          }
-        }
-      }
-      S += (int64_t)ld * M.vw;
-    }
-    if (ok) {
-      const A sc = su ? (A)su[M.toff + j] : sc0;
-#pragma unroll
-      for (int k = 0; k < KPL; ++k) z[(n + M.toff + j) * NR + k0 + k] = acc[k] * sc;
-    }
-  }
-}
-
-template <typename T, typename A, int NR>
-__global__ __launch_bounds__(256) void k_fwd1m(const LrMeta* __restrict__ meta, int64_t nl,
-                                               MvLeaves L, A* __restrict__ z, int64_t n,
-                                               const float* __restrict__ su) {
-  const int lane = threadIdx.x & 63;
-  // wave-uniform block index: descriptors and leaf data come in by scalar loads
-  const int64_t wid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t nw = (int64_t)gridDim.x * 4;
-  for (int64_t b = wid; b < nl; b += nw) {
-    const LrMeta M = meta[b];
-    if (M.r == 0) continue;
-    if constexpr (NR >= 8) {
-      if (M.r <= 8) {
-        fwd1m_block<T, A, NR, 8>(M, L, z, n, su, lane);
-        continue;
-      }
-    }
-    fwd1m_block<T, A, NR, 16>(M, L, z, n, su, lane);
-  }
-}
-
 // ------------------------------------------------------------------ forward, phase 2
 // Per row leaf: y_c = sum over its panels of P z[colmap], then scattered to
 // application order.  Panel 0 of a leaf holds dense slices (type TD), the
@@ -404,14 +335,15 @@ template <typename A, int NR>
 constexpr int z_tile() { return kZTileBytes / (int)(NR * sizeof(A)); }
 
 template <typename T, typename A, int NR, int G>
-__device__ inline void fwd2_run_lds(const Run& rn, int a, int uw, int ld, int C, int cg, int g,
+__device__ inline void fwd2_run_lds(const Unit& U, int ld, int C, int cg, int g,
                                     bool act, int wave, const int32_t* __restrict__ colmap,
                                     const A* __restrict__ z, A* __restrict__ zt,
                                     A (&acc)[G][NR]) {
   constexpr int UNR = 4;
   static_assert(Gran<T>::G == G, "panel granules must cover the same rows");
-  const T* S = reinterpret_cast<const T*>((uintptr_t)rn.data) + (int64_t)a * ld + g * G;
-  const int32_t* map = colmap + rn.col0 + a;
+  const int uw = U.w;
+  const T* S = reinterpret_cast<const T*>((uintptr_t)U.data) + g * G;
+  const int32_t* map = colmap + U.col;
   constexpr int kTile = z_tile<A, NR>();
   for (int t0 = 0; t0 < uw; t0 += kTile) {
     const int tw = min(kTile, uw - t0);
@@ -451,8 +383,7 @@ __device__ inline void fwd2_run_lds(const Run& rn, int a, int uw, int ld, int C,
 }
 
 template <typename TD, typename TL, typename A, int NR>
-__global__ __launch_bounds__(256) void k_fwd2(const Run* __restrict__ runs, MvLeaves L,
-                                              const Unit* __restrict__ units, int64_t nunits,
+__global__ __launch_bounds__(256) void k_fwd2(const Unit* __restrict__ units, int64_t nunits,
                                               const int32_t* __restrict__ colmap,
                                               const A* __restrict__ z, A* __restrict__ ypart,
                                               int ldmax) {
@@ -465,22 +396,19 @@ __global__ __launch_bounds__(256) void k_fwd2(const Run* __restrict__ runs, MvLe
     const int64_t u = xcd_item(li, per);
     if (u >= nunits) continue;                          // uniform over the workgroup
     const Unit U = units[u];
-    const int64_t c = U.leaf;
-    const int ld = (int)(L.ldpre[c + 1] - L.ldpre[c]);
+    const int ld = U.ld, m = U.m;
     const int R = ld / G, C = 64 / R;
     const int cg = lane / R, g = lane % R;
     const bool act = cg < C;
-    const int m = L.m[c];
     A acc[G][NR];
 #pragma unroll
     for (int e = 0; e < G; ++e)
 #pragma unroll
       for (int k = 0; k < NR; ++k) acc[e][k] = 0;
-    const Run rn = runs[(int64_t)U.run * L.nleaf + c];
-    if (std::is_same<TD, TL>::value || U.run == 0)
-      fwd2_run_lds<TD, A, NR, G>(rn, U.a, U.w, ld, C, cg, g, act, wave, colmap, z, zt, acc);
+    if (std::is_same<TD, TL>::value || U.dense)
+      fwd2_run_lds<TD, A, NR, G>(U, ld, C, cg, g, act, wave, colmap, z, zt, acc);
     else
-      fwd2_run_lds<TL, A, NR, G>(rn, U.a, U.w, ld, C, cg, g, act, wave, colmap, z, zt, acc);
+      fwd2_run_lds<TL, A, NR, G>(U, ld, C, cg, g, act, wave, colmap, z, zt, acc);
     // combine the column groups (tree over cg, stride R), then the waves
 #pragma unroll
     for (int e = 0; e < G; ++e)
@@ -513,29 +441,34 @@ __global__ __launch_bounds__(256) void k_fwd2(const Run* __restrict__ runs, MvLe
 }
 
 // y rows of every leaf = sum of its units' partial rows (in unit order),
-// scattered to application order.  One wavefront per leaf (a leaf has at
-// most 64 rows).
+// scattered to application order.  One wavefront per leaf for one or two
+// right-hand sides (a leaf has at most 64 rows), a workgroup for more: a
+// leaf of 40 rows has 640 sums of 16 columns, ten dependent rounds for one
+// wavefront (2,048 leaves of FP64 sums, 16 columns: 93 -> 35 us).
+template <int NR>
+constexpr int sum_leaves() { return NR <= 2 ? 4 : 1; }   // leaves per 256-thread workgroup
 template <typename A, typename VT, int NR>
 __global__ __launch_bounds__(256) void k_fwd2_sum(MvLeaves L, const int32_t* __restrict__ ubeg,
                                                   const A* __restrict__ ypart, int ldmax,
                                                   const int32_t* __restrict__ perm,
-                                                  VT* __restrict__ y, int nrhs, int k0) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t c = blockIdx.x * 4 + (threadIdx.x >> 6); c < L.nleaf; c += (int64_t)gridDim.x * 4) {
+                                                  VT* __restrict__ y, int nrhs, int k0, int nv) {
+  constexpr int LW = sum_leaves<NR>(), TL = 256 / LW;
+  for (int64_t c = blockIdx.x * LW + threadIdx.x / TL; c < L.nleaf; c += (int64_t)gridDim.x * LW) {
     const int m = L.m[c], lo = L.lo[c];
     const int u0 = ubeg[c], u1 = ubeg[c + 1];
-    for (int e = lane; e < m * NR; e += 64) {
+    for (int e = threadIdx.x % TL; e < m * NR; e += TL) {
       const int row = e / NR, k = e % NR;
       A v = 0;
       for (int u = u0; u < u1; ++u) v += ypart[(int64_t)u * ldmax * NR + e];
-      y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
+      if (k < nv) y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
     }
   }
 }
 
 // ------------------------------------------------------------------ many right-hand sides on MFMA
-// With 8 or 16 right-hand sides, both forward phases are small dense
-// products with a long inner dimension: phase 1 is T_b = V_b^T X (terms x
+// With many right-hand sides, both forward phases are small dense
+// products with a long inner dimension (phase 1 from 4 columns on, phase 2
+// from 8): phase 1 is T_b = V_b^T X (terms x
 // right-hand sides, inner dimension = rows of sigma), phase 2 is
 // Y_c += P Z (rows of the leaf x right-hand sides, inner dimension = panel
 // columns).  Both run on 16 x 16 x 4 matrix instructions, C[16][16] +=
@@ -566,154 +499,138 @@ struct Mfma<float> {
   __device__ static inline int row(int j, int q) { return 4 * q + j; }
 };
 
-template <typename A, typename T>
-__device__ inline A widen(T v) { return (A)v; }
-
-// Four consecutive stored values (a 16-byte FP32 granule, two FP64
-// granules, an 8-byte FP16 granule), widened to A; streamed once per
-// product, so the loads are non-temporal.
-template <typename A, typename T>
-__device__ inline void load4(const T* p, A (&o)[4]) {
-  if constexpr (std::is_same<T, double>::value) {
-    const f64x2 u = __builtin_nontemporal_load(reinterpret_cast<const f64x2*>(p));
-    const f64x2 v = __builtin_nontemporal_load(reinterpret_cast<const f64x2*>(p + 2));
-    o[0] = (A)u.x; o[1] = (A)u.y; o[2] = (A)v.x; o[3] = (A)v.y;
-  } else if constexpr (std::is_same<T, float>::value) {
-    const f32x4 u = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
-    o[0] = (A)u.x; o[1] = (A)u.y; o[2] = (A)u.z; o[3] = (A)u.w;
+// N consecutive stored values (4, 2 or 1; the address is a multiple of their
+// size, 16 bytes for four doubles).  Panel addresses come from descriptors,
+// so the compiler would read them by flat instructions, which count as LDS
+// accesses too: every wait for an LDS result would then wait for all panel
+// loads in flight.  The cast to the global address space keeps the two apart.
+// NT: non-temporal.
+template <typename T, int N, bool NT>
+__device__ inline void load_n(const T* p, T* o) {
+  if constexpr (N * sizeof(T) > 16) {
+    load_n<T, N / 2, NT>(p, o);
+    load_n<T, N / 2, NT>(p + N / 2, o + N / 2);
+  } else if constexpr (N == 1) {
+    const __attribute__((address_space(1))) T* q = (const __attribute__((address_space(1))) T*)p;
+    o[0] = NT ? __builtin_nontemporal_load(q) : *q;
   } else {
-    const f16x4 u = __builtin_nontemporal_load(reinterpret_cast<const f16x4*>(p));
-    o[0] = (A)u.x; o[1] = (A)u.y; o[2] = (A)u.z; o[3] = (A)u.w;
+    typedef T TV __attribute__((ext_vector_type(N)));
+    const __attribute__((address_space(1))) TV* q = (const __attribute__((address_space(1))) TV*)p;
+    const TV u = NT ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+    for (int e = 0; e < N; ++e) o[e] = u[e];
   }
 }
+// The element i past a wavefront-uniform base, i of 32 bits: base in scalar
+// registers, one vector offset.
+template <typename T>
+__device__ inline const T* at32(const T* base, uint32_t i) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) +
+                                    (size_t)(i * (uint32_t)sizeof(T)));
+}
 
-// Phase 1 for FP64 and FP16 stored factors: term tiles of 16 (up to four
-// per pass), rows in quads (lane group lq takes row 4 i + lq of quad i), two
-// quads at a time, every load unconditional (clamped to the slice, the value
-// zeroed outside it) and every product issued, so no branch surrounds an
-// MFMA; a quad past the slice contributes exact zeros; rows go in in order.
-// (For these two the granule form below was slower: 29 against 19 ms (FP64)
-// and 10.6 against 10.0 ms (FP16) for the 16-column phase at N = 1,310,720.)
-template <typename T, typename A, int NR, int NTL>
-__device__ inline void fwd1x_pass_rows(const LrMeta& M, const MvLeaves& L,
-                                       const A* __restrict__ zx, int tg, int r, int lr, int lq,
-                                       typename Mfma<A>::V (&acc)[4]) {
-  constexpr int IU = 2;
-  const T* S = reinterpret_cast<const T*>((uintptr_t)M.vptr);
-  int lo = L.lo[M.sf];                    // the leaves of sigma are consecutive
-  for (int lf = M.sf; lf <= M.sl; ++lf) {
-    const int m = L.m[lf];
-    const int ld = (int)(L.ldpre[lf + 1] - L.ldpre[lf]);
-    for (int i00 = 0; i00 < m; i00 += 4 * IU) {
-      A bv[IU], av[IU][NTL];
-#pragma unroll
-      for (int u = 0; u < IU; ++u) {
-        const int i = i00 + 4 * u + lq;
-        const bool ok = i < m;
-        const int ic = ok ? i : m - 1;
-        bv[u] = (ok && lr < NR) ? zx[(int64_t)(lo + ic) * NR + lr] : (A)0;
-#pragma unroll
-        for (int t = 0; t < NTL; ++t) {
-          const int term = tg + t * 16 + lr;
-          const T v = S[(int64_t)min(term, r - 1) * ld + ic];
-          av[u][t] = (ok && term < r) ? widen<A>(v) : (A)0;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < IU; ++u)
-#pragma unroll
-        for (int t = 0; t < NTL; ++t) acc[t] = mfma16(av[u][t], bv[u], acc[t]);
+// ------------------------------------------------------------------ gather, 4 to 16 right-hand sides
+// One workgroup per leaf writes its x twice: row by row into z (the form the
+// panel columns of phase 2 pick single rows from) and, transposed, into xt:
+// leaf c holds NR columns of ld_c values at xt + ldpre[c] NR, rows in [m, ld)
+// zero, so that phase 1 reads four rows of one right-hand side with one load
+// and needs no row masks.  Columns nv .. NR - 1 (a pass wider than what is
+// left) are zero.
+template <typename VT, typename A, int NR>
+__global__ __launch_bounds__(256) void k_gather_x(const VT* __restrict__ x, int nrhs, int k0,
+                                                  int nv, const int32_t* __restrict__ perm,
+                                                  MvLeaves L, A* __restrict__ z,
+                                                  A* __restrict__ xt) {
+  for (int64_t c = blockIdx.x; c < L.nleaf; c += gridDim.x) {
+    const int m = L.m[c], lo = L.lo[c];
+    const int ld = (int)(L.ldpre[c + 1] - L.ldpre[c]);
+    A* xc = xt + L.ldpre[c] * NR;
+    for (int e = threadIdx.x; e < ld * NR; e += blockDim.x) {
+      const int i = e / NR, k = e % NR;
+      const A v = (i < m && k < nv) ? (A)x[(int64_t)perm[lo + min(i, m - 1)] * nrhs + k0 + min(k, nv - 1)] : (A)0;
+      if (i < m) z[(int64_t)(lo + i) * NR + k] = v;
+      xc[k * ld + i] = v;
     }
-    S += (int64_t)ld * M.vw;
-    lo += m;
   }
 }
 
-// Phase 1 for FP32 stored factors: one wavefront per admissible block, term
-// tiles of 16 (up to four per pass), rows in tiles of 16.  The inner dimension may be summed in any
-// order, so lane (term lr, quad lq) reads the four consecutive rows
-// 4 lq .. 4 lq + 3 of a tile as one granule and feeds them to four
-// instructions: step e takes row 4 lq + e of the tile from lane group lq,
-// and the x values follow the same rows.  Up to four tiles are in flight,
-// every load unconditional (clamped to the slice, the value zeroed outside
-// it) and every product issued, so no branch surrounds an MFMA.  Rows in
-// [m, ld) of a slice are zero padding; granules that start at or past m
-// are zeroed.  A leaf's rows go in groups of four tiles and a last group of
-// as many tiles as remain (three for the 40-row leaves of a sphere, where
-// a fixed group of four spent a quarter of its loads and products on
-// padding).
-template <typename T, typename A, int NR, int NTL, int IU>
-__device__ inline void fwd1x_tiles_gran(const T* __restrict__ S, int ld, int m, int i00,
-                                        const A* __restrict__ zx, int lo, const int (&tc)[NTL],
-                                        const bool (&tok)[NTL], bool rhs, int lr, int lq,
-                                        typename Mfma<A>::V (&acc)[4]) {
-  A av[IU][NTL][4], bv[IU][4];
+// ------------------------------------------------------------------ phase 1 on MFMA
+// One wavefront per unit of up to 64 terms (four tiles of 16).  The inner
+// dimension (rows) may be summed in any order: lane (term lr, quad lq) reads
+// the ST consecutive rows i0 + ST lq .. of its term with one load and feeds
+// them to ST instructions, and the x values of its right-hand side come from
+// the transposed copy in the same form.  The rows of a leaf are its ld:
+// tiles of 16 (ST = 4), then one of 8 (ST = 2) and one of 4 (ST = 1) for the
+// rest of ld (a multiple of 4), so nothing is spent on padding beyond ld, and
+// no load or product has a mask: rows in [m, ld) are zero on both sides, and
+// terms past r - 1 repeat term r - 1 into rows of the result that are not
+// stored.  The loads are temporal: a term's rows are 16 to 128 bytes per tile,
+// pieces of a cache line whose rest the next tile needs (non-temporal, FP64
+// fetched 3.3 GB for 1.8 GB of factors).  Bound by HBM: 16 columns at N =
+// 81,920, FP64 581 -> 448 us (1.8 GB: 4.0 TB/s), FP32 281 -> 227 us; FP16 at N =
+// 162,000 551 -> 272 us; four columns, FP32, 1,458 -> 212 us (on the vector
+// units before).
+template <typename T, typename A, int NTL, int ST, int IU>
+__device__ inline void fwd1x_rows(const T* __restrict__ S, const A* __restrict__ xb, int ld,
+                                  int i0, const int (&tc)[NTL], int xo, int lq,
+                                  typename Mfma<A>::V (&acc)[4]) {
+  T av[IU][NTL][ST];
+  A bv[IU][ST];
 #pragma unroll
   for (int u = 0; u < IU; ++u) {
-    const int i0 = i00 + 16 * u + 4 * lq;       // first row of the lane's granule
-    const bool okg = i0 < m;
-    const int ig = okg ? i0 : 0;
+    const int i = i0 + 16 * u + ST * lq;
 #pragma unroll
-    for (int t = 0; t < NTL; ++t) {
-      A v[4];
-      load4<A, T>(S + (int64_t)tc[t] * ld + ig, v);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) av[u][t][e] = (okg && tok[t]) ? v[e] : (A)0;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool okr = rhs && i0 + e < m;
-      const A x = zx[(int64_t)(lo + (okr ? i0 + e : 0)) * NR + (rhs ? lr : 0)];
-      bv[u][e] = okr ? x : (A)0;
-    }
+    for (int t = 0; t < NTL; ++t) load_n<T, ST, false>(S + (tc[t] * ld + i), av[u][t]);
+    load_n<A, ST, false>(xb + (xo * ld + i), bv[u]);
   }
 #pragma unroll
   for (int u = 0; u < IU; ++u)
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int e = 0; e < ST; ++e)
 #pragma unroll
-      for (int t = 0; t < NTL; ++t) acc[t] = mfma16(av[u][t][e], bv[u][e], acc[t]);
+      for (int t = 0; t < NTL; ++t) acc[t] = mfma16((A)av[u][t][e], bv[u][e], acc[t]);
 }
 
 template <typename T, typename A, int NR, int NTL>
-__device__ inline void fwd1x_pass_gran(const LrMeta& M, const MvLeaves& L,
-                                       const A* __restrict__ zx, int tg, int r, int lr, int lq,
-                                       typename Mfma<A>::V (&acc)[4]) {
+__device__ inline void fwd1x_pass(const LrMeta& M, const MvLeaves& L, const A* __restrict__ xt,
+                                  int tg, int r, int lr, int lq,
+                                  typename Mfma<A>::V (&acc)[4]) {
   const T* S = reinterpret_cast<const T*>((uintptr_t)M.vptr);
-  int lo = L.lo[M.sf];                    // the leaves of sigma are consecutive
   int tc[NTL];                            // clamped term of each tile
-  bool tok[NTL];
 #pragma unroll
-  for (int t = 0; t < NTL; ++t) {
-    const int term = tg + t * 16 + lr;
-    tok[t] = term < r;
-    tc[t] = tok[t] ? term : r - 1;
-  }
-  const bool rhs = lr < NR;
+  for (int t = 0; t < NTL; ++t) tc[t] = min(tg + t * 16 + lr, r - 1);
+  const int xo = lr & (NR - 1);           // NR = 8: columns 8 .. 15 repeat, not stored
+  int64_t lp = L.ldpre[M.sf];
   for (int lf = M.sf; lf <= M.sl; ++lf) {
-    const int m = L.m[lf];
-    const int ld = (int)(L.ldpre[lf + 1] - L.ldpre[lf]);
-    int i00 = 0;
-    for (; i00 + 64 <= m; i00 += 64)
-      fwd1x_tiles_gran<T, A, NR, NTL, 4>(S, ld, m, i00, zx, lo, tc, tok, rhs, lr, lq, acc);
-    switch ((m - i00 + 15) / 16) {        // uniform over the wavefront
-      case 1: fwd1x_tiles_gran<T, A, NR, NTL, 1>(S, ld, m, i00, zx, lo, tc, tok, rhs, lr, lq, acc); break;
-      case 2: fwd1x_tiles_gran<T, A, NR, NTL, 2>(S, ld, m, i00, zx, lo, tc, tok, rhs, lr, lq, acc); break;
-      case 3: fwd1x_tiles_gran<T, A, NR, NTL, 3>(S, ld, m, i00, zx, lo, tc, tok, rhs, lr, lq, acc); break;
-      default: break;
+    const int64_t lpn = L.ldpre[lf + 1];
+    const int ld = (int)(lpn - lp);
+    const A* xb = xt + lp * NR;
+    // tiles of 16 rows, two at a time where their registers fit
+    constexpr int IU = sizeof(T) == 8 ? 1 : 2;
+    int i0 = 0;
+    for (; i0 + 16 * IU <= ld; i0 += 16 * IU)
+      fwd1x_rows<T, A, NTL, 4, IU>(S, xb, ld, i0, tc, xo, lq, acc);
+    if (IU == 2 && i0 + 16 <= ld) {
+      fwd1x_rows<T, A, NTL, 4, 1>(S, xb, ld, i0, tc, xo, lq, acc);
+      i0 += 16;
     }
+    if (ld & 8) {
+      fwd1x_rows<T, A, NTL, 2, 1>(S, xb, ld, i0, tc, xo, lq, acc);
+      i0 += 8;
+    }
+    if (ld & 4) fwd1x_rows<T, A, NTL, 1, 1>(S, xb, ld, i0, tc, xo, lq, acc);
     S += (int64_t)ld * M.vw;
-    lo += m;
+    lp = lpn;
   }
 }
 
 template <typename T, typename A, int NR>
 __global__ __launch_bounds__(256) void k_fwd1x(const LrMeta* __restrict__ meta, int64_t nl,
-                                               MvLeaves L, const A* __restrict__ zx,
+                                               MvLeaves L, const A* __restrict__ xt,
                                                A* __restrict__ zt, int64_t n,
                                                const float* __restrict__ su) {
   using V = typename Mfma<A>::V;
-  static_assert(NR == 8 || NR == 16, "MFMA phase 1 takes 8 or 16 right-hand sides");
+  static_assert(NR == 4 || NR == 8 || NR == 16, "MFMA phase 1 takes 4, 8 or 16 right-hand sides");
   const int lane = threadIdx.x & 63;
   const int lr = lane & 15, lq = lane >> 4;     // a: term lr, row lq; b: row lq, rhs lr
   const int64_t wid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -727,20 +644,11 @@ __global__ __launch_bounds__(256) void k_fwd1x(const LrMeta* __restrict__ meta, 
       V acc[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) acc[t] = V{0, 0, 0, 0};
-      if constexpr (!std::is_same<T, float>::value) {
-        switch (ntile) {                      // uniform over the wavefront
-          case 1: fwd1x_pass_rows<T, A, NR, 1>(M, L, zx, tg, r, lr, lq, acc); break;
-          case 2: fwd1x_pass_rows<T, A, NR, 2>(M, L, zx, tg, r, lr, lq, acc); break;
-          case 3: fwd1x_pass_rows<T, A, NR, 3>(M, L, zx, tg, r, lr, lq, acc); break;
-          default: fwd1x_pass_rows<T, A, NR, 4>(M, L, zx, tg, r, lr, lq, acc); break;
-        }
-      } else {
-        switch (ntile) {
-          case 1: fwd1x_pass_gran<T, A, NR, 1>(M, L, zx, tg, r, lr, lq, acc); break;
-          case 2: fwd1x_pass_gran<T, A, NR, 2>(M, L, zx, tg, r, lr, lq, acc); break;
-          case 3: fwd1x_pass_gran<T, A, NR, 3>(M, L, zx, tg, r, lr, lq, acc); break;
-          default: fwd1x_pass_gran<T, A, NR, 4>(M, L, zx, tg, r, lr, lq, acc); break;
-        }
+      switch (ntile) {                        // uniform over the wavefront
+        case 1: fwd1x_pass<T, A, NR, 1>(M, L, xt, tg, r, lr, lq, acc); break;
+        case 2: fwd1x_pass<T, A, NR, 2>(M, L, xt, tg, r, lr, lq, acc); break;
+        case 3: fwd1x_pass<T, A, NR, 3>(M, L, xt, tg, r, lr, lq, acc); break;
+        default: fwd1x_pass<T, A, NR, 4>(M, L, xt, tg, r, lr, lq, acc); break;
       }
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -759,153 +667,160 @@ __global__ __launch_bounds__(256) void k_fwd1x(const LrMeta* __restrict__ meta, 
   }
 }
 
-// The column quads of one z tile for a leaf of NT 16-row tiles: KQ quads per
-// wavefront at a time, every load unconditional (clamped to the panel, the
-// value zeroed outside it) and every product issued, so the loop has no
-// branch around an MFMA and the accumulators stay in place.  A quad past the
-// tile contributes exact zeros; the products go in in column order.
-template <typename E, typename A, int NR, int NT, int KQ>
-__device__ inline void fwd2x_tile(const E* __restrict__ P, int64_t cbase, int ld, int tw,
-                                  const A* __restrict__ zs, int wave, int lr, int lq,
-                                  typename Mfma<A>::V (&acc)[4]) {
-  for (int q0 = wave; q0 * 4 < tw; q0 += 4 * KQ) {
-    A bv[KQ], av[KQ][NT];
+// ------------------------------------------------------------------ phase 2 on MFMA
+// A leaf of ld rows takes NT = ceil(ld / 16) row tiles.  Lane (i = lr, column
+// lq of a quad) reads its rows of a column with one or two loads that 16 lanes
+// make contiguous: one row (NT = 1), rows 2 i and 2 i + 1 of the first 32
+// (NT = 2, 3, and 4 for FP64), row 32 + i (NT = 3), rows 32 + 2 i .. (NT = 4,
+// FP64) or rows 4 i .. 4 i + 3 at once (NT = 4).  fwd2x_row names the row
+// that tile t takes from lane i.  Lanes whose rows lie past ld read the
+// column's last rows again, into rows of the result that are not stored.
+// Bound by HBM and by the z rows that every column reads from L2 (64 or 128
+// bytes against 160 or 320 of an FP32 or FP64 panel column of 40 rows):
+// without the z reads it takes 85% of its time.  16 columns at N = 81,920,
+// FP64 1,102 -> 763 us (3.3 GB: 4.3 TB/s), FP32 434 us; FP16 factors at N =
+// 162,000 911 -> 630 us (2.2 GB).  One to four batches in flight, 1,024- or
+// 4,096-column units and 1,024 to 8,192 workgroups give the same within 5%.
+template <typename E, int NT>
+__device__ inline int fwd2x_row(int t, int i) {
+  if (NT == 1) return i;
+  if (NT == 4 && sizeof(E) < 8) return 4 * i + t;
+  if (t < 2) return 2 * i + t;
+  return NT == 3 ? 32 + i : 32 + 2 * i + (t - 2);
+}
+
+// KQ quads of columns with their z rows, read straight from memory.
+template <typename E, typename A, int NR, int KQ, int NT>
+struct ColBatch {
+  E av[KQ][NT];
+  A bv[KQ];
+  // columns c0 + 4 u + lq; mc: the map entries of the batch (lane = column);
+  // r1, r2: the lane's first rows
+  __device__ inline void load(const E* __restrict__ P, const A* __restrict__ z, int mc, int c0,
+                              int w, int ld, int r1, int r2, int xo, int lq) {
 #pragma unroll
     for (int u = 0; u < KQ; ++u) {
-      const int col = (q0 + 4 * u) * 4 + lq;
-      const bool okc = col < tw;
-      const int colc = okc ? col : tw - 1;
-      bv[u] = (okc && lr < NR) ? zs[colc * NR + lr] : (A)0;
-      const E* pc = P + (cbase + colc) * ld;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int row = t * 16 + lr;
-        const E v = pc[min(row, ld - 1)];
-        av[u][t] = (okc && row < ld) ? widen<A>(v) : (A)0;
+      const int zi = __shfl(mc, 4 * u + lq, 64);
+      const uint32_t pc = (uint32_t)(min(c0 + 4 * u + lq, w - 1) * ld);   // 32 bits hold a unit
+      if constexpr (NT == 4 && sizeof(E) < 8) {
+        load_n<E, 4, true>(at32(P, pc + r1), av[u]);
+      } else {
+        load_n<E, NT == 1 ? 1 : 2, true>(at32(P, pc + r1), av[u]);
+        if constexpr (NT >= 3) load_n<E, NT - 2, true>(at32(P, pc + r2), av[u] + 2);
       }
+      bv[u] = z[(int64_t)zi * NR + xo];
     }
-#pragma unroll
-    for (int u = 0; u < KQ; ++u)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = mfma16(av[u][t], bv[u], acc[t]);
   }
-}
-
-template <typename E, typename A, int NR, int KQ>
-__device__ inline void fwd2x_tile_nt(int nrt, const E* __restrict__ P, int64_t cbase, int ld,
-                                     int tw, const A* __restrict__ zs, int wave, int lr,
-                                     int lq, typename Mfma<A>::V (&acc)[4]) {
-  switch (nrt) {                                        // uniform over the workgroup
-    case 1: fwd2x_tile<E, A, NR, 1, KQ>(P, cbase, ld, tw, zs, wave, lr, lq, acc); break;
-    case 2: fwd2x_tile<E, A, NR, 2, KQ>(P, cbase, ld, tw, zs, wave, lr, lq, acc); break;
-    case 3: fwd2x_tile<E, A, NR, 3, KQ>(P, cbase, ld, tw, zs, wave, lr, lq, acc); break;
-    default: fwd2x_tile<E, A, NR, 4, KQ>(P, cbase, ld, tw, zs, wave, lr, lq, acc); break;
-  }
-}
-
-// The same with granule loads: lane (i = lr, column lq of a quad) reads
-// rows 4 i .. 4 i + 3 of its column at once and gives row 4 i + t to the
-// accumulator of tile t, so tile t holds the rows 4 i + t (i = 0..15) and
-// every panel column is one contiguous read of 16 lanes.  Lanes with
-// 4 i >= ld contribute zeros.
-template <typename E, typename A, int NR, int KQ>
-__device__ inline void fwd2x_gran(const E* __restrict__ P, int64_t cbase, int ld, int tw,
-                                  const A* __restrict__ zs, int wave, int lr, int lq,
-                                  typename Mfma<A>::V (&acc)[4]) {
-  const bool okr = 4 * lr < ld;
-  const int rg = okr ? 4 * lr : 0;
-  for (int q0 = wave; q0 * 4 < tw; q0 += 4 * KQ) {
-    A bv[KQ], av[KQ][4];
+  // only the columns below w
+  __device__ inline void mask(int c0, int w, int lq) {
 #pragma unroll
     for (int u = 0; u < KQ; ++u) {
-      const int col = (q0 + 4 * u) * 4 + lq;
-      const bool okc = col < tw;
-      const int colc = okc ? col : tw - 1;
-      bv[u] = (okc && lr < NR) ? zs[colc * NR + lr] : (A)0;
-      A v[4];
-      load4<A, E>(P + (cbase + colc) * ld + rg, v);
+      const bool ok = c0 + 4 * u + lq < w;
+      bv[u] = ok ? bv[u] : (A)0;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) av[u][t] = (okc && okr) ? v[t] : (A)0;
+      for (int t = 0; t < NT; ++t) av[u][t] = ok ? av[u][t] : (E)0;
     }
+  }
+  __device__ inline void mul(typename Mfma<A>::V (&acc)[NT]) {
 #pragma unroll
     for (int u = 0; u < KQ; ++u)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) acc[t] = mfma16(av[u][t], bv[u], acc[t]);
+      for (int t = 0; t < NT; ++t) acc[t] = mfma16((A)av[u][t], bv[u], acc[t]);
+  }
+};
+
+// The columns of a unit for one wavefront: batches of 4 KQ columns round-robin
+// over the four wavefronts, two in turn, so that the next batch's loads are
+// in flight while the current one is multiplied.  The column map (lane =
+// column) runs two batches ahead and is read before the panel loads of its
+// iteration, so that waiting for it waits for nothing newer; loads past the
+// end are clamped, not skipped, so that no branch makes the waits
+// conservative.  The last, partial batch of the unit goes after the loop.
+template <typename E, typename A, int NR, int KQ, int NT>
+__device__ inline void fwd2x_cols(const E* __restrict__ P, const int32_t* __restrict__ map,
+                                  int w, int ld, const A* __restrict__ z, int wave, int lane,
+                                  A (*ybuf)[NR]) {
+  constexpr int CB = 4 * KQ, STEP = 4 * CB;
+  const int lr = lane & 15, lq = lane >> 4;
+  const int f1 = fwd2x_row<E, NT>(0, lr), f2 = NT >= 3 ? fwd2x_row<E, NT>(2, lr) : 0;
+  // (clamped to the column's last rows: the same cache line as its neighbours)
+  const int r1 = min(f1, ld - (NT == 1 ? 1 : (NT == 4 && sizeof(E) < 8 ? 4 : 2)));
+  const int r2 = NT >= 3 ? min(f2, ld - (NT - 2)) : 0;
+  const int xo = lr & (NR - 1);                 // NR = 8: columns 8 .. 15 repeat, not stored
+  const int ml = lane & (CB - 1);
+  typename Mfma<A>::V acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = typename Mfma<A>::V{0, 0, 0, 0};
+  auto at = [&](int c) { return map[min(c + ml, w - 1)]; };
+  ColBatch<E, A, NR, KQ, NT> b0, b1;
+  int c = wave * CB;
+  if (c + CB <= w) {
+    int ma = at(c), mb = at(c + STEP);
+    b0.load(P, z, ma, c, w, ld, r1, r2, xo, lq);
+    for (; c + STEP + CB <= w; c += 2 * STEP) {         // two batches, no branch between them
+      ma = at(c + 2 * STEP);
+      b1.load(P, z, mb, c + STEP, w, ld, r1, r2, xo, lq);
+      __builtin_amdgcn_sched_barrier(0);
+      b0.mul(acc);
+      mb = at(c + 3 * STEP);
+      b0.load(P, z, ma, c + 2 * STEP, w, ld, r1, r2, xo, lq);
+      __builtin_amdgcn_sched_barrier(0);
+      b1.mul(acc);
+    }
+    if (c + CB <= w) {
+      b0.mul(acc);
+      c += STEP;
+    }
+  }
+  if (c < w) {
+    b0.load(P, z, at(c), c, w, ld, r1, r2, xo, lq);
+    b0.mask(c, w, lq);
+    b0.mul(acc);
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (lr < NR) ybuf[fwd2x_row<E, NT>(t, Mfma<A>::row(j, lq))][lr] = acc[t][j];
+}
+
+template <typename E, typename A, int NR>
+__device__ inline void fwd2x_unit(const E* __restrict__ P, const int32_t* __restrict__ map, int w,
+                                  int ld, const A* __restrict__ z, int wave, int lane,
+                                  A (*ybuf)[NR]) {
+  constexpr int KQ = sizeof(A) == 8 ? 2 : 4;
+  switch ((ld + 15) / 16) {                             // uniform over the workgroup
+    case 1: fwd2x_cols<E, A, NR, KQ, 1>(P, map, w, ld, z, wave, lane, ybuf); break;
+    case 2: fwd2x_cols<E, A, NR, KQ, 2>(P, map, w, ld, z, wave, lane, ybuf); break;
+    case 3: fwd2x_cols<E, A, NR, KQ, 3>(P, map, w, ld, z, wave, lane, ybuf); break;
+    default: fwd2x_cols<E, A, NR, KQ, 4>(P, map, w, ld, z, wave, lane, ybuf); break;
   }
 }
 
-// Phase 2: one workgroup per work unit; the unit's z values are staged in
-// LDS per tile, each wavefront takes column quads round-robin and keeps one
-// accumulator per 16-row tile of the leaf; the four wavefronts are added in
-// LDS in a fixed order.
-template <typename TD, typename TL, typename A, int NR, bool GR>
-__global__ __launch_bounds__(256) void k_fwd2x(const Run* __restrict__ runs, MvLeaves L,
-                                               const Unit* __restrict__ units, int64_t nunits,
+// One workgroup per work unit; the four wavefronts' sums are added in LDS in
+// a fixed order.
+template <typename TD, typename TL, typename A, int NR>
+__global__ __launch_bounds__(256) void k_fwd2x(const Unit* __restrict__ units, int64_t nunits,
                                                const int32_t* __restrict__ colmap,
                                                const A* __restrict__ z,
                                                A* __restrict__ ypart, int ldmax) {
-  using V = typename Mfma<A>::V;
   static_assert(NR == 8 || NR == 16, "MFMA phase 2 takes 8 or 16 right-hand sides");
-  constexpr int kQuads = 4;
-  // the z tile and the final combination of the wavefronts share one LDS
-  // buffer (the tile is consumed before the combination starts)
-  constexpr int kTile = (4 * kMaxLeaf * NR) / NR;     // columns: 256
-  __shared__ A lbuf[4 * kMaxLeaf * NR];
-  A* zs = lbuf;
-  A (*ybuf)[kMaxLeaf][NR] = reinterpret_cast<A (*)[kMaxLeaf][NR]>(lbuf);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lr = lane & 15, lq = lane >> 4;     // a: row lr, column lq; b: column lq, rhs lr
+  __shared__ A ybuf[4][kMaxLeaf][NR];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t per = (nunits + kXcds - 1) / kXcds;
   for (int64_t li = blockIdx.x; li < per * kXcds; li += gridDim.x) {
     const int64_t u = xcd_item(li, per);
     if (u >= nunits) continue;                          // uniform over the workgroup
     const Unit U = units[u];
-    const int64_t c = U.leaf;
-    const int ld = (int)(L.ldpre[c + 1] - L.ldpre[c]);
-    const int m = L.m[c];
-    const int nrt = (ld + 15) / 16;                     // 16-row tiles, at most 4
-    const Run rn = runs[(int64_t)U.run * L.nleaf + c];
-    const bool dense = std::is_same<TD, TL>::value || U.run == 0;
-    const int32_t* map = colmap + rn.col0 + U.a;
-    V acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = V{0, 0, 0, 0};
-    for (int t0 = 0; t0 < U.w; t0 += kTile) {
-      const int tw = min(kTile, U.w - t0);
-      __syncthreads();                                  // the previous tile is consumed
-      for (int e = threadIdx.x; e < tw * NR; e += blockDim.x) {
-        const int col = e / NR, k = e % NR;
-        zs[e] = z[(int64_t)map[t0 + col] * NR + k];
-      }
-      __syncthreads();
-      const int64_t cbase = (int64_t)U.a + t0;          // first panel column of the tile
-      if constexpr (GR) {
-        if (dense)
-          fwd2x_gran<TD, A, NR, kQuads>(reinterpret_cast<const TD*>((uintptr_t)rn.data), cbase,
-                                        ld, tw, zs, wave, lr, lq, acc);
-        else
-          fwd2x_gran<TL, A, NR, kQuads>(reinterpret_cast<const TL*>((uintptr_t)rn.data), cbase,
-                                        ld, tw, zs, wave, lr, lq, acc);
-      } else {
-        if (dense)
-          fwd2x_tile_nt<TD, A, NR, kQuads>(nrt, reinterpret_cast<const TD*>((uintptr_t)rn.data),
-                                           cbase, ld, tw, zs, wave, lr, lq, acc);
-        else
-          fwd2x_tile_nt<TL, A, NR, kQuads>(nrt, reinterpret_cast<const TL*>((uintptr_t)rn.data),
-                                           cbase, ld, tw, zs, wave, lr, lq, acc);
-      }
-    }
-    __syncthreads();                                    // the last tile is consumed
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (GR || t < nrt) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int row = GR ? 4 * Mfma<A>::row(j, lq) + t : t * 16 + Mfma<A>::row(j, lq);
-          if (row < kMaxLeaf && lr < NR) ybuf[wave][row][lr] = acc[t][j];
-        }
-      }
-    }
+    const int32_t* map = colmap + U.col;
+    if (std::is_same<TD, TL>::value || U.dense)
+      fwd2x_unit<TD, A, NR>(reinterpret_cast<const TD*>((uintptr_t)U.data), map, U.w, U.ld, z,
+                            wave, lane, ybuf[wave]);
+    else
+      fwd2x_unit<TL, A, NR>(reinterpret_cast<const TL*>((uintptr_t)U.data), map, U.w, U.ld, z,
+                            wave, lane, ybuf[wave]);
+    const int m = U.m;
     __syncthreads();
     A* yp = ypart + u * ldmax * NR;
     for (int e = threadIdx.x; e < m * NR; e += blockDim.x) {
@@ -936,14 +851,15 @@ __device__ inline void wave_lds_order() {
 }
 
 template <typename T, typename A, int NR, int G>
-__device__ inline void tr1_run(const Run& rn, int a, int uw, int ld, int R, int C, int cg, int g,
+__device__ inline void tr1_run(const Unit& U, int ld, int R, int C, int cg, int g,
                                bool act, int wave, const A (&xg)[G][NR], A* __restrict__ w,
                                A* __restrict__ red) {
   static_assert(Gran<T>::G == G, "panel granules must cover the same rows");
   constexpr int UNR = tr1_unr<NR>();
   const int lane = threadIdx.x & 63;
-  const T* S = reinterpret_cast<const T*>((uintptr_t)rn.data) + (int64_t)a * ld + g * G;
-  const int64_t col0 = rn.col0 + a;
+  const int uw = U.w;
+  const T* S = reinterpret_cast<const T*>((uintptr_t)U.data) + g * G;
+  const int64_t col0 = U.col;
   const int ngrp = (uw + C - 1) / C;
   // a step covers the UNR C consecutive columns q0 C ... (q0 + UNR) C - 1;
   // reader t of a step sums column q0 C + t: group u = t / C, segment c
@@ -1013,8 +929,7 @@ __device__ inline void tr1_run(const Run& rn, int a, int uw, int ld, int R, int 
 }
 
 template <typename TD, typename TL, typename A, int NR>
-__global__ __launch_bounds__(256) void k_tr1(const Run* __restrict__ runs, MvLeaves L,
-                                             const Unit* __restrict__ units, int64_t nunits,
+__global__ __launch_bounds__(256) void k_tr1(const Unit* __restrict__ units, int64_t nunits,
                                              const A* __restrict__ z, A* __restrict__ w) {
   constexpr int G = Gran<TD>::G;
   __shared__ A red[4][tr1_unr<NR>() * 64 * NR];
@@ -1024,12 +939,10 @@ __global__ __launch_bounds__(256) void k_tr1(const Run* __restrict__ runs, MvLea
     const int64_t u = xcd_item(li, per);
     if (u >= nunits) continue;
     const Unit U = units[u];
-    const int64_t c = U.leaf;
-    const int ld = (int)(L.ldpre[c + 1] - L.ldpre[c]);
+    const int ld = U.ld, m = U.m, lo = U.lo;
     const int R = ld / G, C = 64 / R;
     const int cg = lane / R, g = lane % R;
     const bool act = cg < C;
-    const int m = L.m[c], lo = L.lo[c];
     A xg[G][NR];
 #pragma unroll
     for (int e = 0; e < G; ++e) {
@@ -1038,11 +951,10 @@ __global__ __launch_bounds__(256) void k_tr1(const Run* __restrict__ runs, MvLea
       for (int k = 0; k < NR; ++k)
         xg[e][k] = (act && row < m) ? z[(int64_t)(lo + row) * NR + k] : (A)0;
     }
-    const Run rn = runs[(int64_t)U.run * L.nleaf + c];
-    if (std::is_same<TD, TL>::value || U.run == 0)
-      tr1_run<TD, A, NR, G>(rn, U.a, U.w, ld, R, C, cg, g, act, wave, xg, w, red[wave]);
+    if (std::is_same<TD, TL>::value || U.dense)
+      tr1_run<TD, A, NR, G>(U, ld, R, C, cg, g, act, wave, xg, w, red[wave]);
     else
-      tr1_run<TL, A, NR, G>(rn, U.a, U.w, ld, R, C, cg, g, act, wave, xg, w, red[wave]);
+      tr1_run<TL, A, NR, G>(U, ld, R, C, cg, g, act, wave, xg, w, red[wave]);
   }
 }
 
@@ -1153,7 +1065,7 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
                                              const TItem* __restrict__ items, MvLeaves L,
                                              const A* __restrict__ w, const A* __restrict__ z,
                                              int64_t n, const int32_t* __restrict__ perm,
-                                             VT* __restrict__ y, int nrhs, int k0, int S,
+                                             VT* __restrict__ y, int nrhs, int k0, int nv, int S,
                                              A* __restrict__ ypart, int ldmax) {
   constexpr int G = Gran<T>::G;
   __shared__ A ybuf[4][kMaxLeaf][NR];
@@ -1268,10 +1180,10 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
     for (int e = threadIdx.x; e < m * NR; e += blockDim.x) {
       const int row = e / NR, k = e % NR;
       const A v = ((ybuf[0][row][k] + ybuf[1][row][k]) + ybuf[2][row][k]) + ybuf[3][row][k];
-      if (S == 1)
-        y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
-      else
+      if (S > 1)
         yp[e] = v;
+      else if (k < nv)
+        y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
     }
     __syncthreads();
   }
@@ -1282,42 +1194,48 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
 template <typename A, typename VT, int NR>
 __global__ __launch_bounds__(256) void k_tr2_sum(MvLeaves L, int S, const A* __restrict__ ypart,
                                                  int ldmax, const int32_t* __restrict__ perm,
-                                                 VT* __restrict__ y, int nrhs, int k0) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t c = blockIdx.x * 4 + (threadIdx.x >> 6); c < L.nleaf; c += (int64_t)gridDim.x * 4) {
+                                                 VT* __restrict__ y, int nrhs, int k0, int nv) {
+  constexpr int LW = sum_leaves<NR>(), TL = 256 / LW;
+  for (int64_t c = blockIdx.x * LW + threadIdx.x / TL; c < L.nleaf; c += (int64_t)gridDim.x * LW) {
     const int m = L.m[c], lo = L.lo[c];
     const A* yp = ypart + c * S * ldmax * NR;
-    for (int e = lane; e < m * NR; e += 64) {
+    for (int e = threadIdx.x % TL; e < m * NR; e += TL) {
       const int row = e / NR, k = e % NR;
       A v = 0;
       for (int sp = 0; sp < S; ++sp) v += yp[(int64_t)sp * ldmax * NR + e];
-      y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
+      if (k < nv) y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
     }
   }
 }
 
 // ------------------------------------------------------------------ host side
 template <typename TD, typename TL, typename A, typename VT, int NR>
-static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, bool transposed,
-                     hipStream_t s) {
+static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int nv,
+                     bool transposed, hipStream_t s) {
   A* z = static_cast<A*>(P.z);
   A* w = static_cast<A*>(P.w);
+  A* xt = static_cast<A*>(P.xt);
   MvProfile* pr = P.prof;
   if (pr) HM_HIP(hipEventRecord(pr->ev[0], s));
-  k_gather<VT, A><<<grid_for(P.n * NR, 256, 4096), 256, 0, s>>>(x, nrhs, k0, NR, P.perm, P.n, z);
+  if (NR >= 4 && !transposed) {
+    if constexpr (NR >= 4)
+      k_gather_x<VT, A, NR><<<(unsigned)std::min<int64_t>(P.L.nleaf, 1 << 20), 256, 0, s>>>(
+          x, nrhs, k0, nv, P.perm, P.L, z, xt);
+  } else {
+    k_gather<VT, A><<<grid_for(P.n * NR, 256, 4096), 256, 0, s>>>(x, nrhs, k0, NR, nv, P.perm, P.n,
+                                                                  z);
+  }
   HM_LAUNCH_CHECK();
   if (pr) HM_HIP(hipEventRecord(pr->ev[1], s));
   if (!transposed) {
     // phase 1 over its work units (column chunks of the V panels)
-    const unsigned g1 = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P.nu1, 4), 1 << 20));
-    if (P.nu1 > 0) {
-      if constexpr (NR == 8 || NR == 16) {
-        k_fwd1x<TL, A, NR><<<g1, 256, 0, s>>>(P.meta1, P.nu1, P.L, z, z, P.n, P.su);
-      } else if constexpr (NR >= 4) {
-        k_fwd1m<TL, A, NR><<<g1, 256, 0, s>>>(P.meta1, P.nu1, P.L, z, P.n, P.su);
-      } else {
+    const int64_t nu = NR >= 4 ? P.nux : P.nu1;
+    const unsigned g1 = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(nu, 4), 1 << 20));
+    if (nu > 0) {
+      if constexpr (NR >= 4)
+        k_fwd1x<TL, A, NR><<<g1, 256, 0, s>>>(P.metax, P.nux, P.L, xt, z, P.n, P.su);
+      else
         k_fwd1<TL, A, NR><<<g1, 256, 0, s>>>(P.meta1, P.nu1, P.L, z, P.n, P.su);
-      }
       HM_LAUNCH_CHECK();
     }
     if (pr) {
@@ -1326,24 +1244,22 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, bool
     }
     const unsigned gu = (unsigned)std::min<int64_t>(ceil_div(P.nunits, kXcds) * kXcds, P.grid);
     if (P.nunits > 0) {
-      // double vectors on the FP64 matrix cores; with float vectors the
-      // vector kernel streams the panels faster than the FP32 instructions
       if constexpr (NR == 8 || NR == 16)
-        k_fwd2x<TD, TL, A, NR, true><<<gu, 256, 0, s>>>(P.runs, P.L, P.units, P.nunits,
-                                                        P.colmap, z, static_cast<A*>(P.ypart),
+        k_fwd2x<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, P.colmap, z, static_cast<A*>(P.ypart),
                                                         P.ldmax);
       else
-        k_fwd2<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.runs, P.L, P.units, P.nunits, P.colmap, z,
+        k_fwd2<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, P.colmap, z,
                                                  static_cast<A*>(P.ypart), P.ldmax);
       HM_LAUNCH_CHECK();
     }
-    k_fwd2_sum<A, VT, NR><<<(unsigned)std::min<int64_t>(ceil_div(P.L.nleaf, 4), P.grid), 256, 0, s>>>(
-        P.L, P.ubeg, static_cast<const A*>(P.ypart), P.ldmax, P.perm, y, nrhs, k0);
+    k_fwd2_sum<A, VT, NR><<<(unsigned)std::min<int64_t>(ceil_div(P.L.nleaf, sum_leaves<NR>()), P.grid), 256, 0, s>>>(
+        P.L, P.ubeg, static_cast<const A*>(P.ypart), P.ldmax, P.perm, y, nrhs, k0,
+        nv);
     HM_LAUNCH_CHECK();
   } else {
     if (P.nunits > 0) {
       const unsigned gu = (unsigned)std::min<int64_t>(ceil_div(P.nunits, kXcds) * kXcds, P.grid);
-      k_tr1<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.runs, P.L, P.units, P.nunits, z, w);
+      k_tr1<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, z, w);
       HM_LAUNCH_CHECK();
     }
     if (pr) HM_HIP(hipEventRecord(pr->ev[2], s));
@@ -1363,11 +1279,12 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, bool
     // leaves carry similar work: the grid covers the XCD-ordered index range
     const unsigned gt = (unsigned)std::min<int64_t>(ceil_div(P.L.nleaf * S, kXcds) * kXcds, P.grid);
     k_tr2<TL, A, VT, NR><<<gt, 256, 0, s>>>(P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs, k0,
-                                            S, static_cast<A*>(P.ypart), P.ldmax);
+                                            nv, S, static_cast<A*>(P.ypart), P.ldmax);
     HM_LAUNCH_CHECK();
     if (S > 1) {
-      k_tr2_sum<A, VT, NR><<<(unsigned)std::min<int64_t>(ceil_div(P.L.nleaf, 4), P.grid), 256, 0, s>>>(
-          P.L, S, static_cast<const A*>(P.ypart), P.ldmax, P.perm, y, nrhs, k0);
+      k_tr2_sum<A, VT, NR><<<(unsigned)std::min<int64_t>(ceil_div(P.L.nleaf, sum_leaves<NR>()), P.grid), 256, 0, s>>>(
+          P.L, S, static_cast<const A*>(P.ypart), P.ldmax, P.perm, y, nrhs, k0,
+        nv);
       HM_LAUNCH_CHECK();
     }
   }
@@ -1384,28 +1301,30 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, bool
   }
 }
 
+// Columns of the next pass for `left` remaining ones: a pass reads the whole
+// stored operator once whatever its width, so a wider pass with zero columns
+// beats two narrow ones.
+static int pass_width(int left, int cap) {
+  int w = left >= 9 ? 16 : (left >= 5 ? 8 : (left >= 3 ? 4 : left));
+  while (w > cap) w >>= 1;
+  return w;
+}
+
 template <typename TD, typename TL, typename A, typename VT>
 void matvec_impl(const MvPlan& P, const VT* x, VT* y, int nrhs, bool transposed, hipStream_t s) {
-  const int cap = transposed ? P.max_nr_t : 16;
-  int k0 = 0;
-  while (k0 < nrhs) {
-    const int left = nrhs - k0;
-    if (left >= 16 && cap >= 16) {
-      mv_chunk<TD, TL, A, VT, 16>(P, x, y, nrhs, k0, transposed, s);
-      k0 += 16;
-    } else if (left >= 8 && cap >= 8) {
-      mv_chunk<TD, TL, A, VT, 8>(P, x, y, nrhs, k0, transposed, s);
-      k0 += 8;
-    } else if (left >= 4 && cap >= 4) {
-      mv_chunk<TD, TL, A, VT, 4>(P, x, y, nrhs, k0, transposed, s);
-      k0 += 4;
-    } else if (left >= 2 && cap >= 2) {
-      mv_chunk<TD, TL, A, VT, 2>(P, x, y, nrhs, k0, transposed, s);
-      k0 += 2;
-    } else {
-      mv_chunk<TD, TL, A, VT, 1>(P, x, y, nrhs, k0, transposed, s);
-      k0 += 1;
+  // the transposed kernels are vector code: 16 columns cost more than twice 8
+  // (N = 81,920, FP32: 549, 607, 697, 1,047 and 2,385 us for 1 to 16 columns)
+  const int cap = transposed ? std::min(P.max_nr_t, 8) : 16;
+  for (int k0 = 0; k0 < nrhs;) {
+    const int w = pass_width(nrhs - k0, cap), nv = std::min(w, nrhs - k0);
+    switch (w) {
+      case 16: mv_chunk<TD, TL, A, VT, 16>(P, x, y, nrhs, k0, nv, transposed, s); break;
+      case 8: mv_chunk<TD, TL, A, VT, 8>(P, x, y, nrhs, k0, nv, transposed, s); break;
+      case 4: mv_chunk<TD, TL, A, VT, 4>(P, x, y, nrhs, k0, nv, transposed, s); break;
+      case 2: mv_chunk<TD, TL, A, VT, 2>(P, x, y, nrhs, k0, nv, transposed, s); break;
+      default: mv_chunk<TD, TL, A, VT, 1>(P, x, y, nrhs, k0, nv, transposed, s); break;
     }
+    k0 += nv;
   }
 }
 

@@ -1510,14 +1510,16 @@ __global__ void k_group_units(const int64_t* __restrict__ gstart, int64_t ng,
                               const uint64_t* __restrict__ key, const int32_t* __restrict__ idx,
                               const int64_t* __restrict__ gw, const int2* __restrict__ blk,
                               const int2* __restrict__ cl_leaves, const int64_t* __restrict__ ldpre,
-                              int gran, int passes, int64_t* __restrict__ cnt) {
+                              int gran, int passes, int64_t* __restrict__ cnt,
+                              int64_t* __restrict__ cntx) {
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < ng;
        g += (int64_t)gridDim.x * blockDim.x) {
     const int64_t a = gstart[g];
     const int64_t w = gw[g];
     if (key[a] >= ((uint64_t)1 << 31)) {
-      cnt[g] = w > 0 ? 1 : 0;
+      cnt[g] = cntx[g] = w > 0 ? 1 : 0;
     } else {
+      cntx[g] = (w + kXUnitCols - 1) / kXUnitCols;
       const int2 ls = cl_leaves[blk[idx[a]].y];
       const int uw = unit_cols(ldpre[ls.x + 1] - ldpre[ls.x], gran, passes);
       cnt[g] = (w + uw - 1) / uw;
@@ -1525,12 +1527,13 @@ __global__ void k_group_units(const int64_t* __restrict__ gstart, int64_t ng,
   }
 }
 
+// uw0 > 0: units of uw0 columns instead of unit_cols.
 __global__ void k_emit_units(const int64_t* __restrict__ gstart, int64_t ng,
                              const uint64_t* __restrict__ key, const int32_t* __restrict__ idx,
                              const int64_t* __restrict__ gw, const int64_t* __restrict__ goff,
                              const int64_t* __restrict__ uoff, const int64_t* __restrict__ tsort,
                              int64_t toff_base, const LrMeta* __restrict__ meta, int gran, int passes,
-                             uint64_t varena, int esize, LrMeta* __restrict__ units) {
+                             int uw0, uint64_t varena, int esize, LrMeta* __restrict__ units) {
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < ng;
        g += (int64_t)gridDim.x * blockDim.x) {
     const int64_t a = gstart[g];
@@ -1542,7 +1545,7 @@ __global__ void k_emit_units(const int64_t* __restrict__ gstart, int64_t ng,
       continue;
     }
     const int64_t ld = B.vld;
-    const int uw = unit_cols(ld, gran, passes);
+    const int uw = uw0 > 0 ? uw0 : unit_cols(ld, gran, passes);
     int64_t o = uoff[g];
     for (int64_t c0 = 0; c0 < w; c0 += uw, ++o) {
       LrMeta U = B;
@@ -2194,49 +2197,77 @@ void panel_layout(const int2* blk, int64_t nb, const Cluster* cl, const int2* cl
 }
 }  // namespace
 
-// Work units of the per-row-leaf product kernels: every run of every leaf
-// cut into pieces of at most ucols columns, grouped by leaf.
-void make_units(Storage& out, const int64_t* ldpre, int64_t nleaf, int ucols, const Alloc& alloc,
-                hipStream_t s) {
-  std::vector<Run> hr((size_t)out.nruns * nleaf);
-  std::vector<int64_t> hld(nleaf + 1);
-  if (!hr.empty())
-    HM_HIP(hipMemcpyAsync(hr.data(), out.runs, hr.size() * sizeof(Run), hipMemcpyDeviceToHost, s));
-  HM_HIP(hipMemcpyAsync(hld.data(), ldpre, (nleaf + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  HM_HIP(hipStreamSynchronize(s));
-  std::vector<Unit> hu;
-  std::vector<int32_t> hb(nleaf + 1);
-  out.ldmax = 1;
-  for (int64_t c = 0; c < nleaf; ++c) {
-    hb[c] = (int32_t)hu.size();
-    out.ldmax = std::max(out.ldmax, (int)(hld[c + 1] - hld[c]));
-    for (int k = 0; k < out.nruns; ++k) {
-      const int64_t w = hr[(size_t)k * nleaf + c].w;
-      for (int64_t a = 0; a < w; a += ucols)
-        hu.push_back(Unit{(int32_t)c, k, (int32_t)a, (int32_t)std::min<int64_t>(ucols, w - a)});
+// Units of every leaf (each run cut into pieces of at most ucols columns), and
+// the largest ld in *ldmax (zero on entry).
+__global__ void k_unit_counts(const Run* __restrict__ runs, int nruns, MvLeaves L, int ucols,
+                              int64_t* __restrict__ cnt, int* __restrict__ ldmax) {
+  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < L.nleaf;
+       c += (int64_t)gridDim.x * blockDim.x) {
+    int64_t k = 0;
+    for (int r = 0; r < nruns; ++r) k += (runs[(int64_t)r * L.nleaf + c].w + ucols - 1) / ucols;
+    cnt[c] = k;
+    atomicMax(ldmax, (int)(L.ldpre[c + 1] - L.ldpre[c]));
+  }
+}
+
+__global__ void k_unit_emit(const Run* __restrict__ runs, int nruns, MvLeaves L, int ucols,
+                            const int64_t* __restrict__ off, int64_t total, int esize, int lsize,
+                            Unit* __restrict__ units, int32_t* __restrict__ ubeg) {
+  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < L.nleaf;
+       c += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t ld = L.ldpre[c + 1] - L.ldpre[c];
+    Unit* u = units + off[c];
+    ubeg[c] = (int32_t)off[c];
+    if (c == 0) ubeg[L.nleaf] = (int32_t)total;
+    for (int r = 0; r < nruns; ++r) {
+      const Run R = runs[(int64_t)r * L.nleaf + c];
+      for (int a = 0; a < R.w; a += ucols)
+        *u++ = Unit{R.data + (uint64_t)(a * ld * (r == 0 ? esize : lsize)), R.col0 + a,
+                    min(ucols, R.w - a), L.lo[c], (uint16_t)ld, (uint16_t)L.m[c],
+                    (uint16_t)(r == 0), 0};
     }
   }
-  if (hu.size() >= (size_t)INT32_MAX) throw Error{HM_ERR_STATE, "too many product units"};
-  hb[nleaf] = (int32_t)hu.size();
-  out.nunits = (int64_t)hu.size();
-  out.unit_cols = ucols;
-  out.units = static_cast<Unit*>(alloc((hu.size() + 1) * sizeof(Unit)));
-  out.ubeg = static_cast<int32_t*>(alloc(hb.size() * sizeof(int32_t)));
-  if (!hu.empty())
-    HM_HIP(hipMemcpyAsync(out.units, hu.data(), hu.size() * sizeof(Unit), hipMemcpyHostToDevice, s));
-  HM_HIP(hipMemcpyAsync(out.ubeg, hb.data(), hb.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+}
+
+// Counts the units and finds the largest ld; off receives the first unit of
+// every leaf.
+static int64_t scan_units(const Storage& out, const MvLeaves& L, int ucols, int64_t* off,
+                          int* ldmax, Temps& T, hipStream_t s) {
+  int64_t* cnt = T.get<int64_t>(L.nleaf);
+  int64_t* res = T.get<int64_t>(2);                     // total, ldmax
+  HM_HIP(hipMemsetAsync(res, 0, 2 * sizeof(int64_t), s));
+  k_unit_counts<<<grid_for(L.nleaf, 256), 256, 0, s>>>(out.runs, out.nruns, L, ucols, cnt,
+                                                       (int*)(res + 1));
+  HM_LAUNCH_CHECK();
+  scan_excl_i64(cnt, off, L.nleaf, res, s);
+  int64_t h[2];
+  HM_HIP(hipMemcpyAsync(h, res, sizeof(h), hipMemcpyDeviceToHost, s));
   HM_HIP(hipStreamSynchronize(s));
+  *ldmax = (int)(h[1] & 0x7fffffff);
+  return h[0];
+}
+
+// Work units of the per-row-leaf product kernels, grouped by leaf.
+void make_units(Storage& out, const MvLeaves& L, int ucols, const Alloc& alloc, hipStream_t s) {
+  Temps T{s, {}};
+  int64_t* off = T.get<int64_t>(L.nleaf);
+  const int64_t total = scan_units(out, L, ucols, off, &out.ldmax, T, s);
+  if (total >= INT32_MAX) throw Error{HM_ERR_STATE, "too many product units"};
+  out.nunits = total;
+  out.unit_cols = ucols;
+  out.units = static_cast<Unit*>(alloc((size_t)(total + 1) * sizeof(Unit)));
+  out.ubeg = static_cast<int32_t*>(alloc((size_t)(L.nleaf + 1) * sizeof(int32_t)));
+  k_unit_emit<<<grid_for(L.nleaf, 64), 64, 0, s>>>(out.runs, out.nruns, L, ucols, off, total,
+                                                   out.esize, out.lsize, out.units, out.ubeg);
+  HM_LAUNCH_CHECK();
 }
 
 // Number of units make_units would produce for ucols.
-int64_t count_units(const Storage& out, int64_t nleaf, int ucols, hipStream_t s) {
-  std::vector<Run> hr((size_t)out.nruns * nleaf);
-  if (!hr.empty())
-    HM_HIP(hipMemcpyAsync(hr.data(), out.runs, hr.size() * sizeof(Run), hipMemcpyDeviceToHost, s));
-  HM_HIP(hipStreamSynchronize(s));
-  int64_t cnt = 0;
-  for (const Run& r : hr) cnt += (r.w + ucols - 1) / ucols;
-  return cnt;
+int64_t count_units(const Storage& out, const MvLeaves& L, int ucols, hipStream_t s) {
+  Temps T{s, {}};
+  int64_t* off = T.get<int64_t>(L.nleaf);
+  int ldmax = 0;
+  return scan_units(out, L, ucols, off, &ldmax, T, s);
 }
 
 template <typename T, typename TL>
@@ -2266,6 +2297,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   std::vector<Run*> run_parts;
   std::vector<std::pair<int32_t*, int64_t>> colmap_parts;
   std::vector<std::pair<LrMeta*, int64_t>> unit_parts;      // forward phase-1 units per chunk
+  std::vector<std::pair<LrMeta*, int64_t>> xunit_parts;     // the same for the matrix cores
   Run* runD = keep.get<Run>(nleaf);
   k_runs<<<grid_for(nleaf, 256), 256, 0, s>>>(PD.col0, PD.W, PD.poff, nleaf, (uint64_t)(uintptr_t)D,
                                               esize, 0, runD);
@@ -2444,6 +2476,8 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
       int64_t* goff = tg.get<int64_t>(ngr + 1);
       int64_t* gcnt = tg.get<int64_t>(ngr + 1);
       int64_t* guoff = tg.get<int64_t>(ngr + 1);
+      int64_t* gcntx = tg.get<int64_t>(ngr + 1);
+      int64_t* guoffx = tg.get<int64_t>(ngr + 1);
       k_group_starts<<<grid_for(nb, 256), 256, 0, s>>>(gfirst, gpos, nb, gstart);
       HM_LAUNCH_CHECK();
       k_group_sizes<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, nb, tsort, gidx, in.lr + b0,
@@ -2472,16 +2506,27 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
         const int passes = sizeof(TL) == 2 ? 8 : 4;
         k_group_units<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, gkey, gidx, gw, in.lr + b0,
                                                          in.cl_leaves, in.ldpre, gran, passes,
-                                                         gcnt);
+                                                         gcnt, gcntx);
         HM_LAUNCH_CHECK();
-        const int64_t nu = scan_total(gcnt, guoff, ngr, tmp, s);
-        LrMeta* um = keep.get<LrMeta>(nu + 1);
+        scan_excl_i64(gcnt, guoff, ngr, tmp, s);
+        scan_excl_i64(gcntx, guoffx, ngr, tmp + 1, s);
+        int64_t nu[2];
+        HM_HIP(hipMemcpyAsync(nu, tmp, sizeof(nu), hipMemcpyDeviceToHost, s));
+        HM_HIP(hipStreamSynchronize(s));
+        LrMeta* um = keep.get<LrMeta>(nu[0] + 1);
+        LrMeta* umx = keep.get<LrMeta>(nu[1] + 1);
         k_emit_units<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, gkey, gidx, gw, goff, guoff,
                                                         tsort, toff_base, out.meta + b0, gran,
-                                                        passes, (uint64_t)(uintptr_t)varena, lsize,
-                                                        um);
+                                                        passes, 0, (uint64_t)(uintptr_t)varena,
+                                                        lsize, um);
         HM_LAUNCH_CHECK();
-        unit_parts.push_back({um, nu});
+        k_emit_units<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, gkey, gidx, gw, goff, guoffx,
+                                                        tsort, toff_base, out.meta + b0, gran,
+                                                        passes, kXUnitCols,
+                                                        (uint64_t)(uintptr_t)varena, lsize, umx);
+        HM_LAUNCH_CHECK();
+        unit_parts.push_back({um, nu[0]});
+        xunit_parts.push_back({umx, nu[1]});
       }
       HM_HIP(hipStreamSynchronize(s));
       tg.release();
@@ -2533,19 +2578,21 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   }
   out.toff_total = toff_base;
   if (toff_base >= INT32_MAX) throw Error{HM_ERR_STATE, "more than 2^31 low-rank terms"};
-  {
-    int64_t nu = 0;
-    for (auto& up : unit_parts) nu += up.second;
-    out.nu1 = nu;
-    out.meta1 = static_cast<LrMeta*>(alloc((size_t)(nu + 1) * sizeof(LrMeta)));
-    int64_t o = 0;
-    for (auto& up : unit_parts) {
+  auto join_units = [&](const std::vector<std::pair<LrMeta*, int64_t>>& parts, int64_t* cnt) {
+    int64_t nu = 0, o = 0;
+    for (auto& up : parts) nu += up.second;
+    *cnt = nu;
+    LrMeta* dst = static_cast<LrMeta*>(alloc((size_t)(nu + 1) * sizeof(LrMeta)));
+    for (auto& up : parts) {
       if (up.second)
-        HM_HIP(hipMemcpyAsync(out.meta1 + o, up.first, up.second * sizeof(LrMeta),
+        HM_HIP(hipMemcpyAsync(dst + o, up.first, up.second * sizeof(LrMeta),
                               hipMemcpyDeviceToDevice, s));
       o += up.second;
     }
-  }
+    return dst;
+  };
+  out.meta1 = join_units(unit_parts, &out.nu1);
+  out.metax = join_units(xunit_parts, &out.nux);
   out.ms_aca = ms_since(t0) - ms_pack;
 
   // ---- product plan: runs, column map, transposed items
@@ -2555,7 +2602,9 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   for (int k = 0; k < out.nruns; ++k)
     HM_HIP(hipMemcpyAsync(out.runs + (int64_t)k * nleaf, run_parts[k], nleaf * sizeof(Run),
                           hipMemcpyDeviceToDevice, s));
-  make_units(out, in.ldpre, nleaf, kUnitCols, alloc, s);
+  out.esize = esize;
+  out.lsize = lsize;
+  make_units(out, MvLeaves{in.leaf_lo, in.leaf_m, in.ldpre, nleaf}, kUnitCols, alloc, s);
   out.ncols = out.dense_cols + ucols;
   out.colmap = static_cast<int32_t*>(alloc((out.ncols + 1) * sizeof(int32_t)));
   {
