@@ -17,10 +17,8 @@ namespace hm {
 
 // ---- launchers defined in the other translation units
 void launch_centroids(const double* V, const int32_t* T, int64_t n, double* C, hipStream_t s);
-void launch_minmax(const double* C, int64_t n, int64_t off, int64_t cnt, double* out6,
-                   hipStream_t s);
-void launch_morton(const double* C, int64_t n, int64_t off, int64_t cnt, const double* a,
-                   double scale, uint64_t* keys, int32_t* idx, hipStream_t s);
+void launch_morton_order(const double* C, int64_t n, const int64_t* goff, int G, int64_t max_cnt,
+                         uint64_t* keys, int32_t* perm, hipStream_t s);
 template <typename T>
 void launch_geom_sorted(const double* V, const int32_t* Tri, const int32_t* perm, int64_t n,
                         double* c, T* o, T* aw, T* sf, hipStream_t s);
@@ -426,29 +424,16 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
   // ---- Morton codes and sort
   t0 = clk::now();
   // every geometry has its own cube box and is sorted within its own range
-  double* mm = dalloc_t<double>(6 * G, s);
-  for (int64_t g = 0; g < G; ++g) launch_minmax(Capp, n, goff[g], goff[g + 1] - goff[g], mm + 6 * g, s);
-  std::vector<double> mmh(6 * G);
-  HM_HIP(hipMemcpyAsync(mmh.data(), mm, 6 * G * sizeof(double), hipMemcpyDeviceToHost, s));
-  HM_HIP(hipStreamSynchronize(s));
   h->keys = h->alloc_t<uint64_t>(n);
   h->perm = h->alloc_t<int32_t>(n);
   h->inv = h->alloc_t<int32_t>(n);
-  uint64_t* ksort = dalloc_t<uint64_t>(n, s);
-  for (int64_t g = 0; g < G; ++g) {
-    const double* mg = mmh.data() + 6 * g;
-    double ext = 0.0;
-    for (int d = 0; d < 3; ++d) ext = std::max(ext, mg[3 + d] - mg[d]);
-    const double scale = ext > 0.0 ? 2097152.0 / ext : 0.0;
-    launch_morton(Capp, n, goff[g], goff[g + 1] - goff[g], mg, scale, h->keys, h->perm, s);
-  }
-  HM_HIP(hipMemcpyAsync(ksort, h->keys, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
-  for (int64_t g = 0; g < G; ++g)
-    radix_sort_u64_i32(ksort + goff[g], h->perm + goff[g], goff[g + 1] - goff[g],
-                       3 * kMortonBits, s);
+  int64_t* dgoff = dalloc_t<int64_t>(G + 1, s);
+  HM_HIP(hipMemcpyAsync(dgoff, goff.data(), (G + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
+  int64_t max_cnt = 0;
+  for (int64_t g = 0; g < G; ++g) max_cnt = std::max(max_cnt, goff[g + 1] - goff[g]);
+  launch_morton_order(Capp, n, dgoff, (int)G, max_cnt, h->keys, h->perm, s);
+  dfree(dgoff, s);
   launch_inverse_perm(h->perm, n, h->inv, s);
-  dfree(ksort, s);
-  dfree(mm, s);
   dfree(Capp, s);
 
   // ---- geometry in Morton order

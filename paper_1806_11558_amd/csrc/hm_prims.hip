@@ -190,6 +190,49 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_apply(const int64_t* in, 
 }
 }  // namespace
 
+// The whole scan in one workgroup of 1,024 threads, 4,096 values at a time
+// with a running total.  Up to kScanOne values: the three launches of the
+// tiled form cost 3 x 2 us on the device and as much again on the host, four
+// rounds here 6 us.
+namespace {
+constexpr int kScanOneThreads = 1024;
+constexpr int64_t kScanOne = 4 * 4 * kScanOneThreads;   // 16,384
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int64_t* in, int64_t* out,
+                                                              int n, int64_t* total) {
+  __shared__ int64_t lds_w[kScanOneThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int64_t carry = 0;
+  for (int base = 0; base < n; base += 4 * kScanOneThreads) {
+    const int i0 = base + 4 * (int)threadIdx.x;
+    int64_t loc[4], v = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      loc[k] = i0 + k < n ? in[i0 + k] : 0;
+      v += loc[k];
+    }
+    const int64_t inc = wave_incl_scan(v);
+    if (lane == 63) lds_w[wave] = inc;
+    __syncthreads();
+    int64_t pre = 0, sum = 0;
+#pragma unroll
+    for (int w = 0; w < kScanOneThreads / 64; ++w) {
+      const int64_t x = lds_w[w];
+      if (w < wave) pre += x;
+      sum += x;
+    }
+    int64_t run = carry + pre + inc - v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i0 + k < n) out[i0 + k] = run;
+      run += loc[k];
+    }
+    carry += sum;
+    __syncthreads();                                    // lds_w is read
+  }
+  if (total && threadIdx.x == 0) *total = carry;
+}
+}  // namespace
+
 void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* d_total, hipStream_t s) {
   if (n <= 0) {
     if (d_total) HM_HIP(hipMemsetAsync(d_total, 0, sizeof(int64_t), s));
@@ -198,6 +241,9 @@ void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* d_total,
   const int64_t tiles = ceil_div(n, kScanTile);
   if (tiles == 1) {
     k_tile_apply<<<1, kScanThreads, 0, s>>>(in, out, n, nullptr, d_total);
+    HM_LAUNCH_CHECK();
+  } else if (n <= kScanOne) {
+    k_scan_one<<<1, kScanOneThreads, 0, s>>>(in, out, (int)n, d_total);
     HM_LAUNCH_CHECK();
   } else {
     int64_t* sums = dalloc_t<int64_t>(tiles, s);
@@ -225,6 +271,26 @@ __device__ inline uint32_t lanes_below(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Up to kRadixDirect tiles every workgroup of the scatter adds the tile
+// histograms in front of it itself; the scan of the 256 x tiles counts (one
+// to three launches a pass) is then not needed.
+constexpr int64_t kRadixDirect = 64;
+
+// Histogram of one digit per tile, stored tile-major: hist[tile * 256 + d].
+__global__ __launch_bounds__(kRadixThreads) void k_radix_hist_t(const uint64_t* keys, int64_t n,
+                                                                int shift, int32_t* hist) {
+  __shared__ int cnt[kBins];
+  cnt[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t base = (int64_t)blockIdx.x * kRadixTile;
+  for (int k = 0; k < kRadixPer; ++k) {
+    int64_t i = base + (int64_t)k * kRadixThreads + threadIdx.x;
+    if (i < n) atomicAdd(&cnt[(int)((keys[i] >> shift) & 0xFF)], 1);
+  }
+  __syncthreads();
+  hist[(int64_t)blockIdx.x * kBins + threadIdx.x] = cnt[threadIdx.x];
+}
+
 // Histogram of one digit per tile, stored digit-major: hist[d * tiles + tile].
 __global__ __launch_bounds__(kRadixThreads) void k_radix_hist(const uint64_t* keys, int64_t n,
                                                               int shift, int64_t tiles,
@@ -242,14 +308,36 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_hist(const uint64_t* ke
 }
 
 // Stable scatter: keys of a tile are visited in index order, ranked inside
-// each wavefront by ballot matching, then across wavefronts via LDS.
+// each wavefront by ballot matching, then across wavefronts via LDS.  The
+// start of digit d in this tile comes from the scanned counts (offs), or,
+// with `hist` (tile-major counts), from the counts of the tiles in front and
+// of the smaller digits.
 __global__ __launch_bounds__(kRadixThreads) void k_radix_scatter(
     const uint64_t* kin, const int32_t* vin, uint64_t* kout, int32_t* vout, int64_t n, int shift,
-    int64_t tiles, const int64_t* offs) {
+    int64_t tiles, const int64_t* offs, const int32_t* hist) {
   __shared__ int wcnt[kRadixWaves][kBins];
   __shared__ int run[kBins];
+  __shared__ int64_t start[kBins];
+  __shared__ int64_t wtot[kRadixWaves];
   const int wave = threadIdx.x >> 6;
   run[threadIdx.x] = 0;
+  if (hist) {                                           // thread t owns digit t
+    int before = 0, all = 0;
+#pragma unroll 8
+    for (int t = 0; t < (int)tiles; ++t) {
+      const int c = hist[t * kBins + threadIdx.x];
+      before += t < (int)blockIdx.x ? c : 0;
+      all += c;
+    }
+    const int64_t inc = wave_incl_scan(all);
+    if ((threadIdx.x & 63) == 63) wtot[wave] = inc;
+    __syncthreads();
+    int64_t pre = inc - all;
+    for (int w = 0; w < wave; ++w) pre += wtot[w];
+    start[threadIdx.x] = pre + before;
+  } else {
+    start[threadIdx.x] = offs[(int64_t)threadIdx.x * tiles + blockIdx.x];
+  }
   const int64_t base = (int64_t)blockIdx.x * kRadixTile;
   for (int k = 0; k < kRadixPer; ++k) {
 #pragma unroll
@@ -285,7 +373,7 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_scatter(
     }
     __syncthreads();
     if (valid) {
-      int64_t pos = offs[(int64_t)d * tiles + blockIdx.x] + wcnt[wave][d] + rank;
+      int64_t pos = start[d] + wcnt[wave][d] + rank;
       kout[pos] = key;
       vout[pos] = val;
     }
@@ -294,23 +382,84 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_scatter(
 }
 }  // namespace
 
+// Up to kSortOne pairs: a bitonic sort of (key, position) in the LDS of one
+// workgroup, stable because the position breaks ties (keys have no bits at or
+// above `bits`, rounded up to eight, so comparing them whole is the same
+// order).  One launch where eight radix passes take sixteen or more.
+constexpr int kSortOne = 4096, kSortOneThreads = 1024;
+__global__ __launch_bounds__(kSortOneThreads) void k_sort_one(uint64_t* keys, int32_t* vals, int n,
+                                                              int np2) {
+  __shared__ uint64_t k[kSortOne];
+  __shared__ int32_t p[kSortOne];
+  for (int i = threadIdx.x; i < np2; i += kSortOneThreads) {
+    k[i] = i < n ? keys[i] : ~uint64_t(0);
+    p[i] = i;                                           // padding sorts last: its positions are the largest
+  }
+  __syncthreads();
+  for (int len = 2; len <= np2; len <<= 1)
+    for (int d = len >> 1; d > 0; d >>= 1) {
+      for (int t = threadIdx.x; t < np2 / 2; t += kSortOneThreads) {
+        const int i = 2 * t - (t & (d - 1)), j = i + d;
+        const bool up = (i & len) == 0;
+        const uint64_t ki = k[i], kj = k[j];
+        const int32_t pi = p[i], pj = p[j];
+        const bool gt = ki > kj || (ki == kj && pi > pj);
+        if (gt == up) {
+          k[i] = kj;
+          k[j] = ki;
+          p[i] = pj;
+          p[j] = pi;
+        }
+      }
+      __syncthreads();
+    }
+  int32_t v[kSortOne / kSortOneThreads];
+#pragma unroll
+  for (int q = 0; q < kSortOne / kSortOneThreads; ++q) {
+    const int i = threadIdx.x + q * kSortOneThreads;
+    v[q] = i < n ? vals[p[i]] : 0;
+  }
+  __syncthreads();                                      // every value is read
+#pragma unroll
+  for (int q = 0; q < kSortOne / kSortOneThreads; ++q) {
+    const int i = threadIdx.x + q * kSortOneThreads;
+    if (i < n) {
+      keys[i] = k[i];
+      vals[i] = v[q];
+    }
+  }
+}
+
 void radix_sort_u64_i32(uint64_t* keys, int32_t* vals, int64_t n, int bits, hipStream_t s) {
   if (n <= 1 || bits <= 0) return;
+  if (n <= kSortOne) {
+    int np2 = 2;
+    while (np2 < n) np2 <<= 1;
+    k_sort_one<<<1, kSortOneThreads, 0, s>>>(keys, vals, (int)n, np2);
+    HM_LAUNCH_CHECK();
+    return;
+  }
   const int passes = (bits + 7) / 8;
   const int64_t tiles = ceil_div(n, kRadixTile);
+  const bool direct = tiles <= kRadixDirect;
   uint64_t* k2 = dalloc_t<uint64_t>(n, s);
   int32_t* v2 = dalloc_t<int32_t>(n, s);
   int64_t* hist = dalloc_t<int64_t>(tiles * kBins, s);
-  int64_t* offs = dalloc_t<int64_t>(tiles * kBins, s);
+  int64_t* offs = direct ? nullptr : dalloc_t<int64_t>(tiles * kBins, s);
   uint64_t *ka = keys, *kb = k2;
   int32_t *va = vals, *vb = v2;
   for (int p = 0; p < passes; ++p) {
     const int shift = 8 * p;
-    k_radix_hist<<<(unsigned)tiles, kRadixThreads, 0, s>>>(ka, n, shift, tiles, hist);
+    if (direct) {
+      k_radix_hist_t<<<(unsigned)tiles, kRadixThreads, 0, s>>>(ka, n, shift, (int32_t*)hist);
+    } else {
+      k_radix_hist<<<(unsigned)tiles, kRadixThreads, 0, s>>>(ka, n, shift, tiles, hist);
+      HM_LAUNCH_CHECK();
+      scan_excl_i64(hist, offs, tiles * kBins, nullptr, s);
+    }
     HM_LAUNCH_CHECK();
-    scan_excl_i64(hist, offs, tiles * kBins, nullptr, s);
-    k_radix_scatter<<<(unsigned)tiles, kRadixThreads, 0, s>>>(ka, va, kb, vb, n, shift, tiles,
-                                                              offs);
+    k_radix_scatter<<<(unsigned)tiles, kRadixThreads, 0, s>>>(
+        ka, va, kb, vb, n, shift, tiles, offs, direct ? (const int32_t*)hist : nullptr);
     HM_LAUNCH_CHECK();
     std::swap(ka, kb);
     std::swap(va, vb);
@@ -322,7 +471,7 @@ void radix_sort_u64_i32(uint64_t* keys, int32_t* vals, int64_t n, int bits, hipS
   dfree(k2, s);
   dfree(v2, s);
   dfree(hist, s);
-  dfree(offs, s);
+  if (offs) dfree(offs, s);
 }
 
 }  // namespace hm

@@ -637,6 +637,7 @@ struct AcaArgs {
   const int32_t* list[kAcaClasses];  // block indices of each class, largest first
   int64_t cnt[kAcaClasses];
   int* head;             // queue position of each class (zero before the launches)
+  int nb;                // blocks per queue fetch (wavefront classes)
   int kmax;              // rank cap of this pass
   double eps;
   int32_t* rank;         // out: rank per block
@@ -1119,8 +1120,10 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 1 : (OP == kOpGalerkin ? 2 : 4)) v
 }
 
 // Classes 2..4: one block per wavefront; every wavefront takes its own
-// blocks from the queue, NB consecutive (similar) blocks per fetch for the
-// small classes, which have millions of blocks (no barriers).  Galerkin
+// blocks from the queue, A.nb consecutive (similar) blocks per fetch (up to
+// four for the small classes, which have millions of blocks; one when the
+// class has few blocks per wavefront: four each left three quarters of the
+// wavefronts idle at N = 1,280, 218 us; no barriers).  Galerkin
 // entries hold the row triangle in registers: two waves per SIMD for one
 // row per lane, one (with the accumulation registers as spill space) for
 // two and four.
@@ -1128,7 +1131,7 @@ template <typename T, int Q, int OP>
 __global__ __launch_bounds__(kAcaThreads, OP == kOpGalerkin ? (Q == 1 ? 2 : 1) : (Q == 1 ? 4 : (Q == 2 ? 3 : 2)))
 void k_aca_wave(AcaArgs<T> A) {
   constexpr int c = Q == 4 ? 2 : (Q == 2 ? 3 : 4);
-  constexpr int NB = Q == 4 ? 1 : (Q == 2 ? 2 : 4);
+  const int NB = A.nb;
   const int lane = threadIdx.x & 63;
   const int64_t cnt = A.cnt[c];
   while (true) {
@@ -1782,25 +1785,19 @@ void launch_aca_classes(const AcaArgs<T>& A, int* head, hipStream_t s) {
     k_aca_wg<T, 128, 5, OP><<<grid((const void*)k_aca_wg<T, 128, 5, OP>, 128, cnt[5]), 128, 0, s>>>(A);
     HM_LAUNCH_CHECK();
   }
-  {
-    if (cnt[2] > 0) {
-      k_aca_wave<T, 4, OP><<<grid((const void*)k_aca_wave<T, 4, OP>, kAcaThreads,
-                                  ceil_div(cnt[2], kAcaWaves)),
-                             kAcaThreads, 0, s>>>(A);
-      HM_LAUNCH_CHECK();
-    }
-    if (cnt[3] > 0) {
-      k_aca_wave<T, 2, OP><<<grid((const void*)k_aca_wave<T, 2, OP>, kAcaThreads,
-                                  ceil_div(cnt[3], 2 * kAcaWaves)),
-                             kAcaThreads, 0, s>>>(A);
-      HM_LAUNCH_CHECK();
-    }
-  }
-  if (cnt[4] > 0) {
-    k_aca_wave<T, 1, OP><<<grid((const void*)k_aca_wave<T, 1, OP>, kAcaThreads, ceil_div(cnt[4], 4 * kAcaWaves)),
-                       kAcaThreads, 0, s>>>(A);
+  // wavefront classes: up to `most` blocks per fetch, few enough that every
+  // wavefront fetches at least four times
+  auto wave_class = [&](auto kernel, int c, int most) {
+    if (cnt[c] == 0) return;
+    const unsigned g = grid((const void*)kernel, kAcaThreads, ceil_div(cnt[c], kAcaWaves));
+    AcaArgs<T> B = A;
+    B.nb = (int)std::max<int64_t>(1, std::min<int64_t>(most, cnt[c] / ((int64_t)g * kAcaWaves * 4)));
+    kernel<<<g, kAcaThreads, 0, s>>>(B);
     HM_LAUNCH_CHECK();
-  }
+  };
+  wave_class(k_aca_wave<T, 4, OP>, 2, 1);
+  wave_class(k_aca_wave<T, 2, OP>, 3, 2);
+  wave_class(k_aca_wave<T, 1, OP>, 4, 4);
 }
 
 // The batched ACA over the blocks of a chunk (with mask: only the marked
