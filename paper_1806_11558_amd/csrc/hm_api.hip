@@ -22,14 +22,6 @@ void launch_morton_order(const double* C, int64_t n, const int64_t* goff, int G,
 template <typename T>
 void launch_geom_sorted(const double* V, const int32_t* Tri, const int32_t* perm, int64_t n,
                         double* c, T* o, T* aw, T* sf, hipStream_t s);
-int64_t build_cluster_tree(const std::vector<int64_t>& goff, int leaf, Cluster* cl, int64_t cap,
-                           std::vector<int64_t>& level_beg, hipStream_t s);
-void launch_leaf_marks(const Cluster* cl, int64_t ncl, int64_t* mark, hipStream_t s);
-void launch_pos_leaf(const int64_t* mark, const int64_t* excl, int64_t n, int32_t* pos_leaf,
-                     hipStream_t s);
-void launch_leaf_table(const Cluster* cl, int64_t ncl, const int32_t* pos_leaf, int32_t* leaf_lo,
-                       int32_t* leaf_m, int32_t* leaf_cl, int64_t* leaf_ld, int2* cl_leaves,
-                       hipStream_t s);
 void launch_boxes(const Cluster* cl, const std::vector<int64_t>& level_beg, const int32_t* leaf_cl,
                   int64_t nleaf, const double* c, int64_t n, double* box, hipStream_t s);
 void build_block_tree(const Cluster* cl, int64_t nroots, const double* box, double eta, int leaf,
@@ -103,10 +95,20 @@ struct SolveWs {
     }
   }
   // From the library's pool (stream-ordered), freed with the workspace.
+  // One block for all buffers, each on a 256-byte boundary: freeing one to the
+  // stream-ordered pool costs 10 us.
   void alloc(int64_t n_, int nr_, int m_, bool tr_, bool f32_, hipStream_t s) {
+    size_t tot = 0;
+    auto step = [](size_t cnt) { return (cnt + 31) & ~(size_t)31; };
     layout(n_, nr_, m_, tr_, f32_, [&](size_t cnt) {
-      double* q = (double*)dalloc(cnt * sizeof(double), s);
-      mem.push_back(q);
+      tot += step(cnt);
+      return (double*)nullptr;
+    });
+    double* base = (double*)dalloc_pool(tot * sizeof(double), s);
+    mem.push_back(base);
+    layout(n_, nr_, m_, tr_, f32_, [&](size_t cnt) {
+      double* q = base;
+      base += step(cnt);
       return q;
     });
   }
@@ -257,7 +259,7 @@ struct hm_handle {
     size_t got = b;
     void* q = cache_take(b, &got);
     if (!q) {
-      q = dalloc(b, alloc_stream);
+      q = dalloc_pool(b, alloc_stream);
       got = b;
     }
     owned.push_back({q, got});
@@ -342,12 +344,6 @@ hm_status guarded(F&& f) {
 hm_status arg_error(const std::string& m) {
   g_err = m;
   return HM_ERR_ARG;
-}
-
-// Offsets + total of n int64 values (device); returns the total.
-int64_t scan_total(const int64_t* in, int64_t* out, int64_t n, int64_t* tmp, hipStream_t s) {
-  scan_excl_i64(in, out, n, tmp, s);
-  return d2h_i64(tmp, s);
 }
 
 // ---------------------------------------------------------------- the build
@@ -455,33 +451,29 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
 
   // ---- cluster tree, leaves, boxes
   t0 = clk::now();
-  const int64_t cap = 2 * n + 2 * G;
-  Cluster* cltmp = dalloc_t<Cluster>(cap, s);
-  std::vector<int64_t> level_beg;
-  h->ncl = build_cluster_tree(goff, p.leaf_size, cltmp, cap, level_beg, s);
-  h->cl = h->alloc_t<Cluster>(h->ncl);
-  HM_HIP(hipMemcpyAsync(h->cl, cltmp, h->ncl * sizeof(Cluster), hipMemcpyDeviceToDevice, s));
-  dfree(cltmp, s);
-  int64_t* mark = dalloc_t<int64_t>(n, s);
-  int64_t* excl = dalloc_t<int64_t>(n, s);
-  HM_HIP(hipMemsetAsync(mark, 0, n * sizeof(int64_t), s));
-  launch_leaf_marks(h->cl, h->ncl, mark, s);
-  h->nleaf = scan_total(mark, excl, n, tmp, s);
-  int32_t* pos_leaf = dalloc_t<int32_t>(n, s);
-  launch_pos_leaf(mark, excl, n, pos_leaf, s);
-  dfree(mark, s);
-  dfree(excl, s);
-  h->leaf_lo = h->alloc_t<int32_t>(h->nleaf);
-  h->leaf_m = h->alloc_t<int32_t>(h->nleaf);
-  h->leaf_cl = h->alloc_t<int32_t>(h->nleaf);
-  h->cl_leaves = h->alloc_t<int2>(h->ncl);
-  h->ldpre = h->alloc_t<int64_t>(h->nleaf + 1);
-  int64_t* leaf_ld = dalloc_t<int64_t>(h->nleaf, s);
-  launch_leaf_table(h->cl, h->ncl, pos_leaf, h->leaf_lo, h->leaf_m, h->leaf_cl, leaf_ld,
-                    h->cl_leaves, s);
-  scan_excl_i64(leaf_ld, h->ldpre, h->nleaf, h->ldpre + h->nleaf, s);
-  dfree(leaf_ld, s);
-  dfree(pos_leaf, s);
+  // the tables share one block and one upload (`up` lives until the
+  // synchronisation below)
+  const ClusterTables ct = build_clusters(goff, p.leaf_size);
+  const std::vector<int64_t>& level_beg = ct.level_beg;
+  h->ncl = (int64_t)ct.cl.size();
+  h->nleaf = (int64_t)ct.lo.size();
+  std::vector<char> up;
+  auto pack = [&up](const auto& v) {
+    const size_t at = (up.size() + 255) & ~(size_t)255;
+    up.resize(at + v.size() * sizeof(v[0]));
+    std::memcpy(up.data() + at, v.data(), v.size() * sizeof(v[0]));
+    return at;
+  };
+  const size_t o_cl = pack(ct.cl), o_leaves = pack(ct.leaves), o_lo = pack(ct.lo),
+               o_m = pack(ct.m), o_lc = pack(ct.leaf_cl), o_ld = pack(ct.ldpre);
+  char* tab = static_cast<char*>(h->alloc(up.size()));
+  HM_HIP(hipMemcpyAsync(tab, up.data(), up.size(), hipMemcpyHostToDevice, s));
+  h->cl = reinterpret_cast<Cluster*>(tab + o_cl);
+  h->cl_leaves = reinterpret_cast<int2*>(tab + o_leaves);
+  h->leaf_lo = reinterpret_cast<int32_t*>(tab + o_lo);
+  h->leaf_m = reinterpret_cast<int32_t*>(tab + o_m);
+  h->leaf_cl = reinterpret_cast<int32_t*>(tab + o_lc);
+  h->ldpre = reinterpret_cast<int64_t*>(tab + o_ld);
   h->box = h->alloc_t<double>(6 * h->ncl);
   launch_boxes(h->cl, level_beg, h->leaf_cl, h->nleaf, h->c, n, h->box, s);
   HM_HIP(hipStreamSynchronize(s));
@@ -497,8 +489,8 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
   free_gal_touch(gt, s);
   h->lr = h->alloc_t<int2>(h->nl);
   h->dns = h->alloc_t<int2>(h->nd);
-  if (h->nl) HM_HIP(hipMemcpyAsync(h->lr, adm, h->nl * sizeof(int2), hipMemcpyDeviceToDevice, s));
-  if (h->nd) HM_HIP(hipMemcpyAsync(h->dns, dns, h->nd * sizeof(int2), hipMemcpyDeviceToDevice, s));
+  if (h->nl) copy_d2d(h->lr, adm, h->nl * sizeof(int2), s);
+  if (h->nd) copy_d2d(h->dns, dns, h->nd * sizeof(int2), s);
   dfree(adm, s);
   dfree(dns, s);
   HM_HIP(hipStreamSynchronize(s));
@@ -571,9 +563,8 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
           h->dns, h->nd, h->lr, h->nl, h->cl, h->sto.rank, h->sto.info, dsum);
       HM_LAUNCH_CHECK();
     }
-    unsigned long long hs[7];
-    HM_HIP(hipMemcpyAsync(hs, dsum, sizeof(hs), hipMemcpyDeviceToHost, s));
-    HM_HIP(hipStreamSynchronize(s));
+    int64_t hs[7];
+    d2h_words((const int64_t*)dsum, 7, hs, s);
     dfree(dsum, s);
     st.dense_entries = (int64_t)hs[0];
     st.lr_entries = (int64_t)hs[1];
@@ -899,6 +890,7 @@ hm_status build_handle(const double* vertices, int64_t n_vertices, const int32_t
     }
     hipStream_t s = as_stream(stream);
     h->alloc_stream = s;
+    BuildArena arena(s);
     if (h->form == HM_F32_F16)
       build_impl<float, _Float16>(h.get(), vertices, n_vertices, tri, s);
     else if (h->form == HM_F32)

@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <functional>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "../../include/hm.h"
@@ -89,6 +90,16 @@ GaussRule gauss_rule01();
 
 // Cluster record: lo, hi (Morton positions), first child (-1 for a leaf), level.
 using Cluster = int4;
+
+// Host copy of the cluster forest (breadth first) and its leaf tables.
+struct ClusterTables {
+  std::vector<Cluster> cl;
+  std::vector<int64_t> level_beg;   // first cluster of every level, and the end
+  std::vector<int2> leaves;         // first and last leaf of every cluster
+  std::vector<int32_t> lo, m, leaf_cl;
+  std::vector<int64_t> ldpre;
+};
+ClusterTables build_clusters(const std::vector<int64_t>& goff, int leaf);
 
 // Galerkin admissibility: the test for triangles of two clusters that share
 // a vertex (the supports of their basis functions touch).
@@ -300,9 +311,49 @@ void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* d_total,
 void radix_sort_u64_i32(uint64_t* keys, int32_t* vals, int64_t n, int bits,
                         hipStream_t s);
 
-// Stream-ordered temporary allocation (throws HM_ERR_OOM).
+// Stream-ordered temporary allocation (throws HM_ERR_OOM).  While a BuildArena
+// of this thread and stream is alive, small requests come from it.
 void* dalloc(size_t bytes, hipStream_t s);
 void dfree(void* p, hipStream_t s);
+// The same, always from the library's pool (memory that outlives the build).
+void* dalloc_pool(size_t bytes, hipStream_t s);
+
+// Temporaries and small read-backs of one build.  A build takes about 180
+// temporaries; freeing one to the stream-ordered pool costs 10 us (it records
+// an event), 1.7 of 3.9 ms at N = 1,280.  The arena cuts them from chunks and
+// reuses freed ones at once, which is safe because everything of a build runs
+// on one stream.  Chunks come from the block cache and go back to it when the
+// arena ends, after the stream is synchronised; requests above kArenaMax go
+// to the pool as before.  host is a page of pinned memory that kernels write
+// totals to, so that reading one back is a synchronisation and no copy.
+struct BuildArena {
+  static constexpr size_t kChunk = size_t(32) << 20, kArenaMax = size_t(4) << 20;
+  explicit BuildArena(hipStream_t s);
+  ~BuildArena();
+  BuildArena(const BuildArena&) = delete;
+  BuildArena& operator=(const BuildArena&) = delete;
+  void* get(size_t bytes);
+  bool put(void* p);                    // false: not a block of this arena
+  hipStream_t stream;
+  int64_t* host = nullptr;              // kHostWords words, device-accessible
+  static constexpr int kHostWords = 512;
+  // the arena of this thread's build on stream s, or null
+  static BuildArena* current(hipStream_t s);
+
+ private:
+  static size_t round_up(size_t bytes);
+  std::vector<std::pair<char*, size_t>> chunks_;
+  size_t used_ = 0;                                     // of the last chunk
+  std::unordered_map<void*, size_t> size_;              // live and free blocks
+  std::unordered_map<size_t, std::vector<void*>> free_; // by rounded size
+  BuildArena* outer_ = nullptr;
+};
+// Pinned words for a read-back by kernels on stream s: the current arena's,
+// else null.
+inline int64_t* host_words(hipStream_t s) {
+  BuildArena* a = BuildArena::current(s);
+  return a ? a->host : nullptr;
+}
 // The library's memory pool on the current device; trim_pool() returns what
 // it caches (memory not owned by a live handle) to the device.
 hipMemPool_t lib_pool();
@@ -317,7 +368,12 @@ template <typename T>
 T* dalloc_t(size_t count, hipStream_t s) {
   return static_cast<T*>(dalloc(count * sizeof(T) + 16, s));
 }
+// Device-to-device copy by a kernel (4-byte aligned, a multiple of 4 bytes).
+void copy_d2d(void* dst, const void* src, size_t bytes, hipStream_t s);
 int64_t d2h_i64(const int64_t* d, hipStream_t s);
+void d2h_words(const int64_t* d, int n, int64_t* out, hipStream_t s);   // n <= 64 words
+// Exclusive scan and its total, read back (tmp: one word of device memory).
+int64_t scan_total(const int64_t* in, int64_t* out, int64_t n, int64_t* tmp, hipStream_t s);
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline unsigned grid_for(int64_t n, int threads, int64_t cap = 1 << 20) {

@@ -1240,11 +1240,14 @@ __global__ void k_item_width(const int32_t* __restrict__ sidx, const int32_t* __
 }
 
 // Leaf panels: first column col0[c] (in the item set's column space), width
-// W[c] and size ld_c * W[c].  ibeg holds the first sorted item of each leaf.
+// W[c] and size ld_c * W[c].  ibeg holds the first sorted item of each leaf,
+// *ptotal all columns.
 __global__ void k_leaf_panels(const int64_t* __restrict__ ibeg, const int64_t* __restrict__ gcol,
-                              int64_t np, int64_t total, const int64_t* __restrict__ ldpre,
+                              int64_t np, const int64_t* __restrict__ ptotal,
+                              const int64_t* __restrict__ ldpre,
                               int64_t nleaf, int64_t* __restrict__ col0, int64_t* __restrict__ W,
                               int64_t* __restrict__ psize) {
+  const int64_t total = *ptotal;
   for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < nleaf;
        c += (int64_t)gridDim.x * blockDim.x) {
     const int64_t a = ibeg[c] < np ? gcol[ibeg[c]] : total;
@@ -1816,8 +1819,7 @@ void run_aca(const Geom<T>& g, const int2* blk, int64_t nb, const Cluster* cl,
   for (int k = 0; k < kAcaClasses; ++k)
     scan_excl_i64(flags + k * nb, offs + k * nb, nb, tmp + k, s);
   int64_t cnt[kAcaClasses];
-  HM_HIP(hipMemcpyAsync(cnt, tmp, kAcaClasses * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  HM_HIP(hipStreamSynchronize(s));
+  d2h_words(tmp, kAcaClasses, cnt, s);
   k_split_lists<<<grid_for(nb, 256), 256, 0, s>>>(flags, offs, nb, lists);
   HM_LAUNCH_CHECK();
   AcaArgs<T> A{};
@@ -2117,10 +2119,6 @@ using clk = std::chrono::steady_clock;
 double ms_since(clk::time_point t0) {
   return std::chrono::duration<double, std::milli>(clk::now() - t0).count();
 }
-int64_t scan_total(const int64_t* in, int64_t* out, int64_t n, int64_t* tmp, hipStream_t s) {
-  scan_excl_i64(in, out, n, tmp, s);
-  return d2h_i64(tmp, s);
-}
 int bits_for(int64_t v) {
   int b = 1;
   while ((1ll << b) < v) ++b;
@@ -2154,9 +2152,10 @@ struct PanelSet {
 
 // Expands the row-leaf items of blocks blk[0..nb), sorts them by leaf and lays
 // out one panel per leaf (widths: cluster size of sigma, or rank).
+// K holds what outlives the layout (the items' columns and the inverse order).
 void panel_layout(const int2* blk, int64_t nb, const Cluster* cl, const int2* cl_leaves,
                   const int64_t* ldpre, int64_t nleaf, const int32_t* rank, int64_t* off,
-                  PanelSet& P, Temps& T, int64_t* tmp, hipStream_t s) {
+                  PanelSet& P, Temps& T, Temps& K, int64_t* tmp, hipStream_t s) {
   int64_t* cnt = T.get<int64_t>(nb);
   k_count_leaves<<<grid_for(nb, 256), 256, 0, s>>>(blk, nb, cl_leaves, 0, cnt);
   HM_LAUNCH_CHECK();
@@ -2171,26 +2170,30 @@ void panel_layout(const int2* blk, int64_t nb, const Cluster* cl, const int2* cl
   HM_LAUNCH_CHECK();
   radix_sort_u64_i32(key, P.sidx, P.np, bits_for(nleaf), s);
   P.wid = T.get<int64_t>(P.np);
-  P.gcol = T.get<int64_t>(P.np);
+  P.gcol = K.get<int64_t>(P.np);
   k_item_width<<<grid_for(P.np, 256), 256, 0, s>>>(P.sidx, P.ib, P.np, blk, cl, rank, P.wid);
   HM_LAUNCH_CHECK();
-  P.cols = scan_total(P.wid, P.gcol, P.np, tmp, s);
+  scan_excl_i64(P.wid, P.gcol, P.np, tmp, s);
   int64_t* ibeg = T.get<int64_t>(nleaf + 1);
   k_seg_begins<<<grid_for(nleaf + 1, 256), 256, 0, s>>>(key, P.np, nleaf, ibeg);
   HM_LAUNCH_CHECK();
   P.col0 = T.get<int64_t>(nleaf);
   P.W = T.get<int64_t>(nleaf);
   int64_t* psize = T.get<int64_t>(nleaf);
-  k_leaf_panels<<<grid_for(nleaf, 256), 256, 0, s>>>(ibeg, P.gcol, P.np, P.cols, ldpre, nleaf,
+  k_leaf_panels<<<grid_for(nleaf, 256), 256, 0, s>>>(ibeg, P.gcol, P.np, tmp, ldpre, nleaf,
                                                      P.col0, P.W, psize);
   HM_LAUNCH_CHECK();
   P.poff = T.get<int64_t>(nleaf);
-  P.elems = scan_total(psize, P.poff, nleaf, tmp, s);
+  scan_excl_i64(psize, P.poff, nleaf, tmp + 1, s);
   P.offI = T.get<int64_t>(P.np);
-  P.inv = T.get<int32_t>(P.np);
+  P.inv = K.get<int32_t>(P.np);
   k_item_offsets<<<grid_for(P.np, 256), 256, 0, s>>>(P.sidx, P.ilf, P.np, P.gcol, P.col0, P.poff,
                                                      ldpre, P.offI, P.inv);
   HM_LAUNCH_CHECK();
+  int64_t tot[2];                                       // columns, elements
+  d2h_words(tmp, 2, tot, s);
+  P.cols = tot[0];
+  P.elems = tot[1];
 }
 }  // namespace
 
@@ -2238,8 +2241,7 @@ static int64_t scan_units(const Storage& out, const MvLeaves& L, int ucols, int6
   HM_LAUNCH_CHECK();
   scan_excl_i64(cnt, off, L.nleaf, res, s);
   int64_t h[2];
-  HM_HIP(hipMemcpyAsync(h, res, sizeof(h), hipMemcpyDeviceToHost, s));
-  HM_HIP(hipStreamSynchronize(s));
+  d2h_words(res, 2, h, s);
   *ldmax = (int)(h[1] & 0x7fffffff);
   return h[0];
 }
@@ -2281,9 +2283,10 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   // ---- near field: dense slices in row-leaf panels
   auto t0 = clk::now();
   PanelSet PD;
-  int64_t* oD = keep.get<int64_t>(in.nd + 1);
+  out.dub = static_cast<int64_t*>(alloc((size_t)(in.nd + 1) * sizeof(int64_t)));
+  int64_t* oD = out.dub;
   Temps td{s, {}};
-  panel_layout(in.dns, in.nd, in.cl, in.cl_leaves, in.ldpre, nleaf, nullptr, oD, PD, td, tmp, s);
+  panel_layout(in.dns, in.nd, in.cl, in.cl_leaves, in.ldpre, nleaf, nullptr, oD, PD, td, keep, tmp, s);
   out.D_elems = PD.elems;
   out.dense_cols = PD.cols;
   T* D = static_cast<T*>(alloc((size_t)PD.elems * esize));
@@ -2316,23 +2319,16 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
     HM_LAUNCH_CHECK();
   }
   // slice addresses of the dense items, by (block, row leaf)
-  out.dub = static_cast<int64_t*>(alloc((size_t)(in.nd + 1) * sizeof(int64_t)));
   out.dptr = static_cast<uint64_t*>(alloc((size_t)(PD.np + 1) * sizeof(uint64_t)));
-  if (in.nd > 0)
-    HM_HIP(hipMemcpyAsync(out.dub, oD, in.nd * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
   if (PD.np > 0) {
     k_drec<<<grid_for(PD.np, 256), 256, 0, s>>>(PD.sidx, PD.ib, PD.ilf, PD.np, in.dns,
                                                 in.cl_leaves, oD, PD.offI,
                                                 (uint64_t)(uintptr_t)D, esize, out.dptr);
     HM_LAUNCH_CHECK();
   }
-  // keep what the transposed items need
-  int32_t* invD = keep.get<int32_t>(PD.np);
-  int64_t* gcolD = keep.get<int64_t>(PD.np);
-  if (PD.np) {
-    HM_HIP(hipMemcpyAsync(invD, PD.inv, PD.np * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    HM_HIP(hipMemcpyAsync(gcolD, PD.gcol, PD.np * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
-  }
+  // what the transposed items need
+  const int32_t* invD = PD.inv;
+  const int64_t* gcolD = PD.gcol;
   td.release();
   HM_HIP(hipStreamSynchronize(s));
   out.ms_near = ms_since(t0);
@@ -2389,7 +2385,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
     // operation wait for milliseconds
     size_t pool_bytes = (size_t)pool_elems * esize;
     T* pool = static_cast<T*>(cache_take(pool_bytes, &pool_bytes));
-    if (!pool) pool = static_cast<T*>(dalloc(pool_bytes, s));
+    if (!pool) pool = static_cast<T*>(dalloc_pool(pool_bytes, s));
     if (scaled) {
       // at most min(kmax, m, n) terms per block
       int64_t* kc = ta.get<int64_t>(nl);
@@ -2457,7 +2453,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
       int32_t* gidx = tg.get<int32_t>(nb);
       int64_t* gfirst = tg.get<int64_t>(nb);
       int64_t* gpos = tg.get<int64_t>(nb + 1);
-      int64_t* tsort = tg.get<int64_t>(nb + 1);
+      int64_t* tsort = tg.get<int64_t>(nb + 2);
       k_group_keys<<<grid_for(nb, 256), 256, 0, s>>>(in.lr + b0, nb, in.cl_leaves, in.ldpre, gkey,
                                                      gidx);
       HM_LAUNCH_CHECK();
@@ -2465,8 +2461,10 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
       k_group_marks<<<grid_for(nb, 256), 256, 0, s>>>(gkey, gidx, nb, out.rank + b0, rk64, gfirst);
       HM_LAUNCH_CHECK();
       scan_excl_i64(rk64, tsort, nb, tsort + nb, s);
-      const int64_t terms = d2h_i64(tsort + nb, s);
-      const int64_t ngr = scan_total(gfirst, gpos, nb, tmp, s);
+      scan_excl_i64(gfirst, gpos, nb, tsort + nb + 1, s);
+      int64_t tn[2];                                    // terms, groups
+      d2h_words(tsort + nb, 2, tn, s);
+      const int64_t terms = tn[0], ngr = tn[1];
       int64_t* gstart = tg.get<int64_t>(ngr + 1);
       int64_t* gw = tg.get<int64_t>(ngr + 1);
       int64_t* gsz = tg.get<int64_t>(ngr + 1);
@@ -2480,11 +2478,24 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
       k_group_sizes<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, nb, tsort, gidx, in.lr + b0,
                                                        in.cl_leaves, in.ldpre, gw, gsz);
       HM_LAUNCH_CHECK();
-      const int64_t velems = scan_total(gsz, goff, ngr, tmp, s);
+      scan_excl_i64(gsz, goff, ngr, tmp, s);
       k_block_vlayout<<<grid_for(nb, 256), 256, 0, s>>>(gidx, gpos, gfirst, nb, tsort, gstart, gw,
                                                         goff, in.lr + b0, in.cl_leaves, in.ldpre,
                                                         toffc, voff, vwid);
       HM_LAUNCH_CHECK();
+      // rows per granule and loads per lane of the one-column phase-1 kernel
+      // (FP16 slices: eight loads of 8 bytes)
+      const int gran = sizeof(TL) == 8 ? 2 : 4;
+      const int passes = sizeof(TL) == 2 ? 8 : 4;
+      k_group_units<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, gkey, gidx, gw, in.lr + b0,
+                                                       in.cl_leaves, in.ldpre, gran, passes,
+                                                       gcnt, gcntx);
+      HM_LAUNCH_CHECK();
+      scan_excl_i64(gcnt, guoff, ngr, tmp + 1, s);
+      scan_excl_i64(gcntx, guoffx, ngr, tmp + 2, s);
+      int64_t vn[3];                                    // V elements, phase-1 units of both widths
+      d2h_words(tmp, 3, vn, s);
+      const int64_t velems = vn[0], *nu = vn + 1;
       // V factors
       TL* varena = static_cast<TL*>(alloc((size_t)velems * lsize));
       k_pack_v<T, TL><<<grid_for(nb, 4, 1 << 20), 256, 0, s>>>(in.lr + b0, nb, in.cl, L,
@@ -2497,19 +2508,6 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
       HM_LAUNCH_CHECK();
       // phase-1 units of the chunk
       {
-        // rows per granule and loads per lane of the one-column phase-1
-        // kernel (FP16 slices: eight loads of 8 bytes)
-        const int gran = sizeof(TL) == 8 ? 2 : 4;
-        const int passes = sizeof(TL) == 2 ? 8 : 4;
-        k_group_units<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, gkey, gidx, gw, in.lr + b0,
-                                                         in.cl_leaves, in.ldpre, gran, passes,
-                                                         gcnt, gcntx);
-        HM_LAUNCH_CHECK();
-        scan_excl_i64(gcnt, guoff, ngr, tmp, s);
-        scan_excl_i64(gcntx, guoffx, ngr, tmp + 1, s);
-        int64_t nu[2];
-        HM_HIP(hipMemcpyAsync(nu, tmp, sizeof(nu), hipMemcpyDeviceToHost, s));
-        HM_HIP(hipStreamSynchronize(s));
         LrMeta* um = keep.get<LrMeta>(nu[0] + 1);
         LrMeta* umx = keep.get<LrMeta>(nu[1] + 1);
         k_emit_units<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, gkey, gidx, gw, goff, guoff,
@@ -2531,7 +2529,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
       Temps tu{s, {}};
       PanelSet PU;
       panel_layout(in.lr + b0, nb, in.cl, in.cl_leaves, in.ldpre, nleaf, out.rank + b0, oU, PU,
-                   tu, tmp, s);
+                   tu, tu, tmp, s);
       TL* uarena = static_cast<TL*>(alloc((size_t)PU.elems * lsize));
       if (scaled && nb > 0) {
         k_u_scales<T><<<grid_for(nb, 4, 1 << 20), 256, 0, s>>>(
@@ -2582,8 +2580,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
     LrMeta* dst = static_cast<LrMeta*>(alloc((size_t)(nu + 1) * sizeof(LrMeta)));
     for (auto& up : parts) {
       if (up.second)
-        HM_HIP(hipMemcpyAsync(dst + o, up.first, up.second * sizeof(LrMeta),
-                              hipMemcpyDeviceToDevice, s));
+        copy_d2d(dst + o, up.first, up.second * sizeof(LrMeta), s);
       o += up.second;
     }
     return dst;
@@ -2597,8 +2594,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   out.nruns = (int)run_parts.size();
   out.runs = static_cast<Run*>(alloc((size_t)out.nruns * nleaf * sizeof(Run)));
   for (int k = 0; k < out.nruns; ++k)
-    HM_HIP(hipMemcpyAsync(out.runs + (int64_t)k * nleaf, run_parts[k], nleaf * sizeof(Run),
-                          hipMemcpyDeviceToDevice, s));
+    copy_d2d(out.runs + (int64_t)k * nleaf, run_parts[k], nleaf * sizeof(Run), s);
   out.esize = esize;
   out.lsize = lsize;
   make_units(out, MvLeaves{in.leaf_lo, in.leaf_m, in.ldpre, nleaf}, kUnitCols, alloc, s);
@@ -2608,8 +2604,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
     int64_t o = 0;
     for (auto& pc : colmap_parts) {
       if (pc.second)
-        HM_HIP(hipMemcpyAsync(out.colmap + o, pc.first, pc.second * sizeof(int32_t),
-                              hipMemcpyDeviceToDevice, s));
+        copy_d2d(out.colmap + o, pc.first, pc.second * sizeof(int32_t), s);
       o += pc.second;
     }
   }
