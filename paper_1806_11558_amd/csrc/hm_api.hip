@@ -3,6 +3,7 @@
 // products and the GMRES loop.
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -34,59 +35,62 @@ void launch_tri_sorted(const double* V, const int32_t* Tri, const int32_t* perm,
                        double* v, int32_t* vid, hipStream_t s);
 void launch_inverse_perm(const int32_t* perm, int64_t n, int32_t* inv, hipStream_t s);
 
-int gmres_tiles(int64_t n);
-void gmres_dots(const double* Q, int64_t ldq, int nk, const double* w, int64_t n, int nr,
-                double* part, double* out, hipStream_t s);
-void gmres_orth_update(const double* Q, int64_t ldq, const double* h, int nk, int64_t n, int nr,
-                       double* w, hipStream_t s);
+void gmres_dots(const double* Q, int nk, const double* w, const GsShape& G, double* part,
+                double* out, hipStream_t s);
 void gmres_combine(const double* Q, int64_t ldq, const double* y, int nk, int64_t n, int nr,
                    double* x, hipStream_t s);
 void gmres_scale_cols(const double* a, const double* sc, int64_t n, int nr, double* out,
                       hipStream_t s);
 void gmres_sub(const double* a, const double* b, int64_t tot, double* out, hipStream_t s);
-void gmres_dots_dev(const double* Q, int64_t ldq, const int* jd, int nkmax, const double* w,
-                    int64_t n, int nr, double* part, double* out, hipStream_t s);
-void gmres_orth_update_dev(const double* Q, int64_t ldq, const double* h, const int* jd,
-                           int64_t n, int nr, double* w, hipStream_t s);
-void gmres_copy_col(const double* Q, int64_t ldq, const int* jd, double* out, hipStream_t s);
 
 // Device workspace of a solve.  With HM_SOLVE_GRAPH it stays with the handle
 // together with the instantiated graph of one Arnoldi step (product of the
-// current basis vector, two Gram-Schmidt passes, norm), which is replayed
-// for every step; the step index is read from device memory (jd).
+// current basis vector, orthogonalisation, next basis vector), which is
+// replayed for every step; the step index is counted in device memory (jd).
 //
 // Buffers: Q the basis (m + 1 vectors), fd the right-hand side of the GMRES
-// run, x its iterate, w the product / residual, xin the captured step's
-// input; with refinement also fo (the caller's right-hand side), xs (the
+// run, x its iterate, w the product / residual, xin a second vector of the
+// orthogonalisation (or the captured product's input, then w1 is the second
+// vector); with refinement also fo (the caller's right-hand side), xs (the
 // refined solution) and the float vectors xf, wf of the inner products.
+// page: pinned memory in which the host follows the steps (null: results are
+// copied back after a synchronisation).
 struct SolveWs {
   int nr = 0, m = 0;
-  bool tr = false, f32 = false;
+  bool tr = false, f32 = false, graphed = false;
   int64_t n = 0;
+  GsShape G;
   double *Q = nullptr, *fd = nullptr, *x = nullptr, *w = nullptr, *hdev = nullptr,
-         *part = nullptr, *scl = nullptr, *ydev = nullptr, *xin = nullptr, *fo = nullptr,
-         *xs = nullptr;
+         *part = nullptr, *part2 = nullptr, *scl = nullptr, *ydev = nullptr, *xin = nullptr,
+         *w1 = nullptr, *fo = nullptr, *xs = nullptr;
   float *xf = nullptr, *wf = nullptr;
-  int* jd = nullptr;
+  int64_t* jd = nullptr;
+  int64_t* page = nullptr;
+  int64_t seqv = 0;
   std::vector<void*> mem;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipStream_t free_stream = nullptr;
   // Lays the buffers out through get(count of doubles) -> double*.
   template <typename Get>
-  void layout(int64_t n_, int nr_, int m_, bool tr_, bool f32_, Get&& get) {
-    n = n_, nr = nr_, m = m_, tr = tr_, f32 = f32_;
+  void layout(int64_t n_, int nr_, int m_, bool tr_, bool f32_, bool graph_, bool coarse,
+              Get&& get) {
+    n = n_, nr = nr_, m = m_, tr = tr_, f32 = f32_, graphed = graph_;
+    G = gs_shape(n, nr, coarse);
     const int64_t nv = n * nr;
     Q = get((size_t)(m + 1) * nv);
     fd = get(nv);
     x = get(nv);
     w = get(nv);
     xin = get(nv);
+    w1 = graphed && !f32 ? get(nv) : xin;
     hdev = get((size_t)(m + 2) * nr * 2 + nr);
-    part = get((size_t)(m + 2) * gmres_tiles(n) * nr);
+    part = get((size_t)(m + 2) * G.tiles * nr);
+    // without folding the sums are taken out of part before it is written again
+    part2 = G.fold ? get((size_t)(m + 2) * G.tiles * nr) : part;
     scl = get(nr);
     ydev = get((size_t)(m + 1) * nr);
-    jd = (int*)get(1);
+    jd = (int64_t*)get(2);
     if (f32) {
       fo = get(nv);
       xs = get(nv);
@@ -94,30 +98,67 @@ struct SolveWs {
       wf = (float*)get((nv + 1) / 2);
     }
   }
-  // From the library's pool (stream-ordered), freed with the workspace.
-  // One block for all buffers, each on a 256-byte boundary: freeing one to the
-  // stream-ordered pool costs 10 us.
-  void alloc(int64_t n_, int nr_, int m_, bool tr_, bool f32_, hipStream_t s) {
+  // From the library's pool (stream-ordered), freed with the workspace: one
+  // block for all buffers, each on a 256-byte boundary (freeing one to the
+  // stream-ordered pool costs 10 us).
+  void alloc(int64_t n_, int nr_, int m_, bool tr_, bool f32_, bool graph_, bool coarse,
+             hipStream_t s) {
     size_t tot = 0;
     auto step = [](size_t cnt) { return (cnt + 31) & ~(size_t)31; };
-    layout(n_, nr_, m_, tr_, f32_, [&](size_t cnt) {
+    layout(n_, nr_, m_, tr_, f32_, graph_, coarse, [&](size_t cnt) {
       tot += step(cnt);
       return (double*)nullptr;
     });
     double* base = (double*)dalloc_pool(tot * sizeof(double), s);
     mem.push_back(base);
-    layout(n_, nr_, m_, tr_, f32_, [&](size_t cnt) {
+    layout(n_, nr_, m_, tr_, f32_, graph_, coarse, [&](size_t cnt) {
       double* q = base;
       base += step(cnt);
       return q;
     });
   }
+  // words of a step's results: |w| and the coefficients of every column
+  int64_t slot() const { return (int64_t)(m + 2) * nr; }
+  // Takes a pinned page if the results of two steps fit one.
+  void take_page(bool may_allocate) {
+    if (2 * slot() + 1 > kPageWords) return;
+    page = page_take(may_allocate);
+    if (page) page[0] = 0;
+    seqv = 0;
+  }
+  GsArgs args() const {
+    GsArgs a{};
+    a.G = G;
+    a.Q = Q;
+    a.w = w;
+    a.wf = f32 ? wf : nullptr;
+    a.w1 = w1;
+    a.xin = graphed && !f32 ? xin : nullptr;
+    a.xf = f32 ? xf : nullptr;
+    a.part = part;
+    a.part2 = part2;
+    // [nr] norms, [(m + 2) nr] first and second coefficients; the last rows
+    // of the second ones are free for the norms' sums
+    a.h1 = hdev + nr;
+    a.h2 = hdev + nr + (size_t)(m + 2) * nr;
+    a.nsum = a.h2 + (size_t)m * nr;
+    a.res = page ? (double*)(page + 1) : hdev;
+    a.res_slot = page ? slot() : 0;
+    a.seq = page;
+    a.seqv = seqv;
+    a.jd = graphed ? jd : nullptr;
+    return a;
+  }
   ~SolveWs() {
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
-    if (mem.empty()) return;
-    for (void* q : mem) (void)hipFreeAsync(q, free_stream);
-    (void)hipStreamSynchronize(free_stream);
+    if (!mem.empty()) {
+      for (void* q : mem) (void)hipFreeAsync(q, free_stream);
+      (void)hipStreamSynchronize(free_stream);
+    } else if (page) {
+      (void)hipStreamSynchronize(free_stream);
+    }
+    if (page) page_give(page);                          // no kernel writes to it any more
   }
 };
 void convert_f32_to_f64(const float* a, int64_t tot, double* out, hipStream_t s);
@@ -593,28 +634,53 @@ hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 // ------------------------------------------------------------------ GMRES core
 namespace {
+// Steps whose vectors have at most this many values are enqueued one ahead of
+// the host (gmres_core): the host's part of a step, 20 us, is hidden, while a
+// step that turns out to be unneeded costs a product.
+constexpr int64_t kLookAhead = 400000;
+
+// Waits until the step counter reaches `want`.  The wait ends with the
+// stream's work or with an error of it.
+void await_step(const int64_t* seq, int64_t want, hipStream_t s) {
+  const volatile int64_t* v = seq;
+  for (unsigned spin = 0; *v < want; ++spin) {
+    if ((spin & 0xfff) != 0xfff) continue;
+    const hipError_t e = hipStreamQuery(s);
+    if (e == hipErrorNotReady) continue;
+    HM_HIP(e);
+    if (*v < want) throw Error{HM_ERR_STATE, "a solver step ended without its results"};
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+}
+
 // Restarted GMRES on op(H) x = b for every column of b at once (the columns
 // are independent systems).  `apply` computes w = op(H) v for double vectors
-// v, w of the solve workspace; the Arnoldi basis, the Gram-Schmidt passes and
-// the Givens rotations are in double.  b is ws->fd, the iterate ws->x (read
-// as the initial guess, written back).  Returns the number of Arnoldi steps;
-// rn receives the explicit residual norms |b - op(H) x| at the end.
-// With x_zero the initial guess is known to be zero and the first residual is
-// b itself (one product fewer).
+// v, w of the solve workspace; step(j) enqueues Arnoldi step j (the product of
+// basis vector j, the orthogonalisation, basis vector j + 1).  The Arnoldi
+// basis, the Gram-Schmidt passes and the Givens rotations are in double.  b
+// is ws->fd, the iterate ws->x (read as the initial guess, written back).
+// Returns the number of Arnoldi steps; rn receives the explicit residual
+// norms |b - op(H) x| at the end.  With x_zero the initial guess is known to
+// be zero and the first residual is b itself (one product fewer).
+//
+// The basis vectors are normalised on the device, so a step needs nothing
+// from the host and the next one can be enqueued before its results are
+// seen.  That is done for small systems while the estimates, extrapolated by
+// their last reduction, do not end the cycle; a column that has converged
+// goes on without being looked at.
 template <typename Apply, typename Step>
-int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter, bool use_graph,
-               const Apply& apply, const Step& graph_step, const std::vector<double>& fn,
+int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
+               const Apply& apply, const Step& step, const std::vector<double>& fn,
                std::vector<double>& rn, std::vector<int>& conv, int& restarts, bool x_zero,
                hipStream_t s) {
   const int64_t nv = n * nr;
-  double *Q = ws->Q, *fd = ws->fd, *x = ws->x, *w = ws->w, *hdev = ws->hdev, *part = ws->part,
+  double *Q = ws->Q, *fd = ws->fd, *x = ws->x, *w = ws->w, *part = ws->part,
          *scl = ws->scl, *ydev = ws->ydev;
-  double* hnorm = hdev + (size_t)(m + 2) * nr * 2;   // |w| of the current step
-  std::vector<double> hv((size_t)(m + 2) * nr * 2 + nr);
+  std::vector<double> hv((size_t)ws->slot());
   auto norms = [&](const double* v, std::vector<double>& out) {
-    gmres_dots(v, 0, 1, v, n, nr, part, hdev, s);
+    gmres_dots(v, 1, v, ws->G, part, ws->hdev, s);
     out.resize(nr);
-    HM_HIP(hipMemcpyAsync(out.data(), hdev, nr * sizeof(double), hipMemcpyDeviceToHost, s));
+    HM_HIP(hipMemcpyAsync(out.data(), ws->hdev, nr * sizeof(double), hipMemcpyDeviceToHost, s));
     HM_HIP(hipStreamSynchronize(s));
     for (auto& z : out) z = std::sqrt(std::max(z, 0.0));
   };
@@ -626,7 +692,7 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter, 
   };
   auto rel = [&](int c, double r) { return fn[c] > 0 ? r / fn[c] : 0.0; };
   if (x_zero) {
-    HM_HIP(hipMemcpyAsync(w, fd, nv * sizeof(double), hipMemcpyDeviceToDevice, s));
+    copy_d2d(w, fd, nv * sizeof(double), s);
     rn = fn;
   } else {
     residual(rn);
@@ -639,6 +705,7 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter, 
       gv((size_t)(m + 1) * nr);
   std::vector<int> kc(nr);
   std::vector<double> sc(nr);
+  const bool ahead = ws->page && nv <= kLookAhead;
   while (total_it < max_iter) {
     bool all = true;
     for (int c = 0; c < nr; ++c) all = all && conv[c];
@@ -646,7 +713,7 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter, 
     // Q0 = r / |r| for active columns
     for (int c = 0; c < nr; ++c) sc[c] = (!conv[c] && rn[c] > 0) ? 1.0 / rn[c] : 0.0;
     HM_HIP(hipMemcpyAsync(scl, sc.data(), nr * sizeof(double), hipMemcpyHostToDevice, s));
-    gmres_scale_cols(w, scl, n, nr, Q, s);
+    gmres_start(ws->args(), w, scl, s);
     std::vector<int> active(nr);
     for (int c = 0; c < nr; ++c) {
       active[c] = !conv[c];
@@ -654,30 +721,37 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter, 
       std::fill(gv.begin() + (size_t)c * (m + 1), gv.begin() + (size_t)(c + 1) * (m + 1), 0.0);
       gv[(size_t)c * (m + 1)] = rn[c];
     }
+    int enqueued = 0;
+    double est1 = HUGE_VAL, est2 = HUGE_VAL;            // largest estimates of the last two steps
     for (int j = 0; j < m && total_it < max_iter; ++j) {
-      if (use_graph) {
-        graph_step(j);
-      } else {
-        double* qj = Q + (size_t)j * nv;
-        apply(qj, w);
-        // classical Gram-Schmidt, twice
-        for (int pass = 0; pass < 2; ++pass) {
-          gmres_dots(Q, nv, j + 1, w, n, nr, part, hdev + (size_t)pass * (m + 2) * nr, s);
-          gmres_orth_update(Q, nv, hdev + (size_t)pass * (m + 2) * nr, j + 1, n, nr, w, s);
-        }
-        gmres_dots(w, 0, 1, w, n, nr, part, hnorm, s);
+      if (enqueued == j) {
+        step(j);
+        ++enqueued;
       }
-      HM_HIP(hipMemcpyAsync(hv.data(), hdev, hv.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-      HM_HIP(hipStreamSynchronize(s));
+      // a reduction as in the last step would end the cycle: see its result first
+      const bool ends = est1 < est2 ? est1 * (est1 / est2) <= 1.5 * tol : est1 <= tol;
+      if (ahead && !ends && j + 1 < m && total_it + 1 < max_iter) {
+        step(j + 1);
+        ++enqueued;
+      }
+      const double* hj = hv.data();                     // |w| [nr], coefficients [(j + 1) nr]
+      if (ws->page) {
+        await_step(ws->page, ws->seqv + j + 1, s);
+        std::memcpy(hv.data(), (const double*)(ws->page + 1) + (j & 1) * ws->slot(),
+                    (size_t)(j + 2) * nr * sizeof(double));
+      } else {
+        HM_HIP(hipMemcpyAsync(hv.data(), ws->hdev, (size_t)(j + 2) * nr * sizeof(double),
+                              hipMemcpyDeviceToHost, s));
+        HM_HIP(hipStreamSynchronize(s));
+      }
       ++total_it;
       bool any = false;
+      double estm = 0.0;
       for (int c = 0; c < nr; ++c) {
-        const double hn = std::sqrt(std::max(hv[(size_t)(m + 2) * nr * 2 + c], 0.0));
-        sc[c] = 0.0;
+        const double hn = hj[c];
         if (!active[c]) continue;
         double* Hc = H.data() + (size_t)c * (m + 1) * m;
-        for (int k = 0; k <= j; ++k)
-          Hc[(size_t)k * m + j] = hv[(size_t)k * nr + c] + hv[(size_t)(m + 2) * nr + (size_t)k * nr + c];
+        for (int k = 0; k <= j; ++k) Hc[(size_t)k * m + j] = hj[(size_t)(k + 1) * nr + c];
         Hc[(size_t)(j + 1) * m + j] = hn;
         // previous rotations
         double* csc = cs.data() + (size_t)c * m;
@@ -701,14 +775,15 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter, 
         if (est <= tol || hn == 0.0) {
           active[c] = 0;
         } else {
-          sc[c] = 1.0 / hn;
           any = true;
+          estm = std::max(estm, est);
         }
       }
+      est2 = est1;
+      est1 = estm;
       if (!any) break;
-      HM_HIP(hipMemcpyAsync(scl, sc.data(), nr * sizeof(double), hipMemcpyHostToDevice, s));
-      gmres_scale_cols(w, scl, n, nr, Q + (size_t)(j + 1) * nv, s);
     }
+    ws->seqv += m + 2;
     // x += Q y  (upper triangular solves on the host)
     int kmaxc = 0;
     for (int c = 0; c < nr; ++c) kmaxc = std::max(kmaxc, kc[c]);
@@ -758,7 +833,7 @@ int cg_core(SolveWs* ws, int64_t n, int nr, double tol, int max_iter, const Appl
   auto residual = [&]() {
     apply(x, q);
     gmres_sub(ws->fd, q, nv, r, s);
-    gmres_dots(r, 0, 1, r, n, nr, part, rra, s);
+    gmres_dots(r, 1, r, ws->G, part, rra, s);
     HM_HIP(hipMemcpyAsync(rr.data(), rra, nr * sizeof(double), hipMemcpyDeviceToHost, s));
     HM_HIP(hipStreamSynchronize(s));
     rn.resize(nr);
@@ -783,9 +858,9 @@ int cg_core(SolveWs* ws, int64_t n, int nr, double tol, int max_iter, const Appl
     HM_HIP(hipMemcpyAsync(p, r, nv * sizeof(double), hipMemcpyDeviceToDevice, s));
     while (it < max_iter) {
       apply(p, q);
-      gmres_dots(p, 0, 1, q, n, nr, part, pq, s);
+      gmres_dots(p, 1, q, ws->G, part, pq, s);
       cg_update(x, r, p, q, rra, pq, active, n, nr, s);
-      gmres_dots(r, 0, 1, r, n, nr, part, rrb, s);
+      gmres_dots(r, 1, r, ws->G, part, rrb, s);
       HM_HIP(hipMemcpyAsync(rr.data(), rrb, nr * sizeof(double), hipMemcpyDeviceToHost, s));
       HM_HIP(hipStreamSynchronize(s));
       ++it;
@@ -1009,14 +1084,22 @@ static double* scratch_address() {
 }
 
 // Doubles the solve workspace takes, every buffer rounded up to 256 bytes.
-static size_t solve_ws_doubles(int64_t n, int nr, int m, bool refine) {
+static size_t solve_ws_doubles(int64_t n, int nr, int m, bool refine, bool coarse) {
   size_t tot = 0;
   SolveWs probe;
-  probe.layout(n, nr, m, false, refine, [&](size_t cnt) {
+  probe.layout(n, nr, m, false, refine, false, coarse, [&](size_t cnt) {
     tot += (cnt + 31) & ~(size_t)31;
     return (double*)nullptr;
   });
   return tot;
+}
+
+// Whether a solve takes the coarse row tiles: only where the fixed workspace
+// holds them and not the fine ones (by size alone, so that hm_solve and
+// hm_solve_noalloc sum in the same order).
+static bool solve_coarse(int64_t n, int nr, int m, bool refine) {
+  return solve_ws_doubles(n, nr, m, refine, false) * sizeof(double) > kScratchBytes &&
+         solve_ws_doubles(n, nr, m, refine, true) * sizeof(double) <= kScratchBytes;
 }
 
 // fixed_ws: null => the workspace comes from the library's pool; else the
@@ -1049,7 +1132,8 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
     if (sp->flags & HM_SOLVE_GRAPH)
       return arg_error(who + ": HM_SOLVE_GRAPH is not available without allocation");
     const int mm = cg ? 1 : (sp->restart > 0 ? sp->restart : 100);
-    const size_t need = solve_ws_doubles(h->n, nrhs, mm, sp->refine != 0) * sizeof(double);
+    const size_t need = solve_ws_doubles(h->n, nrhs, mm, sp->refine != 0,
+                                         solve_coarse(h->n, nrhs, mm, sp->refine != 0)) * sizeof(double);
     if (need > kScratchBytes)
       return arg_error(who + ": the workspace needs " + std::to_string(need) +
                        " bytes, more than the fixed " + std::to_string(kScratchBytes) +
@@ -1074,6 +1158,7 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
     const MvPlan P = h->plan();
     // device workspace: per call, or kept with the handle for graph replays
     const bool use_graph = (sp->flags & HM_SOLVE_GRAPH) != 0;
+    const bool coarse = solve_coarse(n, nr, m, refine);
     std::unique_ptr<SolveWs> local;
     SolveWs* ws = nullptr;
     if (no_alloc) {
@@ -1082,7 +1167,7 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
       size_t used = 0;
       local.reset(new SolveWs());
       local->free_stream = s;
-      local->layout(n, nr, m, tr, refine, [&](size_t cnt) {
+      local->layout(n, nr, m, tr, refine, false, coarse, [&](size_t cnt) {
         double* q = base + used;
         used += (cnt + 31) & ~(size_t)31;
         return q;
@@ -1093,15 +1178,17 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
           h->sws->f32 != refine) {
         if (h->sws) h->sws->free_stream = s;
         h->sws.reset(new SolveWs());
-        h->sws->alloc(n, nr, m, tr, refine, s);
+        h->sws->free_stream = s;
+        h->sws->alloc(n, nr, m, tr, refine, true, coarse, s);
       }
       ws = h->sws.get();
     } else {
       local.reset(new SolveWs());
       local->free_stream = s;
-      local->alloc(n, nr, m, tr, refine, s);
+      local->alloc(n, nr, m, tr, refine, false, coarse, s);
       ws = local.get();
     }
+    if (!cg && !ws->page) ws->take_page(!no_alloc);
     // op(H) v with double vectors and double accumulation (the plain solve
     // and the refinement residual) ...
     auto apply64 = [&](const double* in, double* out) {
@@ -1115,7 +1202,14 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
       matvec_dispatch(P, h->form, ws->xf, ws->wf, nr, 1, tr, s);
       convert_f32_to_f64(ws->wf, nv, out, s);
     };
-    const int mhd = m + 2;
+    // product of basis vector j: float vectors with refinement (its input was
+    // written by the step before)
+    auto product = [&](const MvPlan& pl, const double* q, hipStream_t st) {
+      if (refine)
+        matvec_dispatch(pl, h->form, ws->xf, ws->wf, nr, 1, tr, st);
+      else
+        matvec_dispatch(pl, h->form, q, ws->w, nr, 0, tr, st);
+    };
     if (use_graph && !ws->exec) {
       // capture one Arnoldi step on a private stream (the caller's may be the
       // null stream, which cannot capture); no profiling events inside
@@ -1128,30 +1222,21 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
         ~StreamGuard() { (void)hipStreamDestroy(st); }
       } sgd{cs};
       HM_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
-      if (refine) {
-        gmres_copy_col_f32(ws->Q, nv, ws->jd, ws->xf, cs);
-        matvec_dispatch(Pg, h->form, ws->xf, ws->wf, nr, 1, tr, cs);
-        convert_f32_to_f64(ws->wf, nv, ws->w, cs);
-      } else {
-        gmres_copy_col(ws->Q, nv, ws->jd, ws->xin, cs);
-        matvec_dispatch(Pg, h->form, ws->xin, ws->w, nr, 0, tr, cs);
-      }
-      for (int pass = 0; pass < 2; ++pass) {
-        double* hp = ws->hdev + (size_t)pass * mhd * nr;
-        gmres_dots_dev(ws->Q, nv, ws->jd, m + 1, ws->w, n, nr, ws->part, hp, cs);
-        gmres_orth_update_dev(ws->Q, nv, hp, ws->jd, n, nr, ws->w, cs);
-      }
-      gmres_dots(ws->w, 0, 1, ws->w, n, nr, ws->part, ws->hdev + (size_t)mhd * nr * 2, cs);
+      product(Pg, ws->xin, cs);
+      gmres_arnoldi(ws->args(), m - 1, m, cs);
       HM_HIP(hipStreamEndCapture(cs, &ws->graph));
       HM_HIP(hipGraphInstantiate(&ws->exec, ws->graph, nullptr, nullptr, 0));
     }
-    auto graph_step = [&](int j) {
-      const int jh = j;
-      HM_HIP(hipMemcpyAsync(ws->jd, &jh, sizeof(int), hipMemcpyHostToDevice, s));
-      HM_HIP(hipGraphLaunch(ws->exec, s));
+    auto step = [&](int j) {
+      if (use_graph) {
+        HM_HIP(hipGraphLaunch(ws->exec, s));
+      } else {
+        product(P, ws->Q + (size_t)j * nv, s);
+        gmres_arnoldi(ws->args(), j, j + 1, s);
+      }
     };
     auto norms = [&](const double* v, std::vector<double>& out) {
-      gmres_dots(v, 0, 1, v, n, nr, ws->part, ws->hdev, s);
+      gmres_dots(v, 1, v, ws->G, ws->part, ws->hdev, s);
       out.resize(nr);
       HM_HIP(hipMemcpyAsync(out.data(), ws->hdev, nr * sizeof(double), hipMemcpyDeviceToHost, s));
       HM_HIP(hipStreamSynchronize(s));
@@ -1179,8 +1264,8 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
     if (cg) {
       total_it = cg_core(ws, n, nr, sp->tol, sp->max_iter, apply64, fn, rn, conv, restarts, s);
     } else if (!refine) {
-      total_it = gmres_core(ws, n, nr, m, sp->tol, sp->max_iter, use_graph, apply64, graph_step,
-                            fn, rn, conv, restarts, false, s);
+      total_it = gmres_core(ws, n, nr, m, sp->tol, sp->max_iter, apply64, step, fn, rn, conv,
+                            restarts, !sp->use_x0, s);
     } else {
       // iterative refinement: the residual of the current solution in double
       // (vectors and accumulation), the correction from GMRES with float
@@ -1211,8 +1296,8 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
         HM_HIP(hipMemsetAsync(ws->x, 0, nv * sizeof(double), s));
         std::vector<double> fin(nr);
         for (int c = 0; c < nr; ++c) fin[c] = conv[c] ? 0.0 : rn[c];
-        total_it += gmres_core(ws, n, nr, m, inner_tol, sp->max_iter - total_it, use_graph, apply32,
-                               graph_step, fin, rin, cin, restarts, true, s);
+        total_it += gmres_core(ws, n, nr, m, inner_tol, sp->max_iter - total_it, apply32, step, fin,
+                               rin, cin, restarts, true, s);
         gmres_add(xsol, ws->x, nv, xsol, s);
         ++ir_steps;
       }

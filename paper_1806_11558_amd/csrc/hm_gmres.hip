@@ -5,73 +5,280 @@
 // its solve is GMRES with the same product.  Both are here.  All reductions
 // write per-tile partial sums that a second kernel adds in a fixed order, so
 // the solve is bitwise reproducible.
+#include <algorithm>
+
 #include "hm_internal.h"
+#include "hm_wave.h"
 
 namespace hm {
 
+// ------------------------------------------------------------------ Arnoldi step
+// Classical Gram-Schmidt, twice, in three kernels after the product:
+//   first   part = Q^T w                          (partial dots per row tile)
+//   second  w' = w - Q h1, part = Q^T w'          (h1 = the sums of part)
+//   last    w'' = w' - Q h2, part = |w''|^2       (h2 likewise)
+//   next    q = w'' / |w''| into the basis and into the product's input, the
+//           coefficients h1 + h2 and |w''| to the host
+// A dot product needs the finished vector of its own rows only, so the update
+// of one pass and the dots of the next share a kernel.  Before, a step was
+// nine kernels, two copies and a synchronisation beside its product (40 of
+// 130 us of kernels at N = 5,120); these are four and no copy.
+//
+// The rows are cut into tiles of gs_tile() rows: about 96 tiles, so that small
+// systems still spread over the chip, and at most kGsElems elements each in
+// one piece.  With few tiles (GsShape::fold) every workgroup adds the tile
+// sums it needs itself, else gs_final adds them once per pass.
 namespace {
-constexpr int kRowsPerTile = 2048;
 constexpr int kGT = 256;
+constexpr int kGsElems = 2048;     // elements of w held in LDS at a time
+constexpr int kGsVecs = 16;        // basis vectors per workgroup of the dots
+constexpr int kGsH = 512;          // coefficients held in LDS at a time
+}  // namespace
+
+GsShape gs_shape(int64_t n, int nr, bool coarse) {
+  GsShape g;
+  g.n = n;
+  g.nr = nr;
+  const int64_t tot = n * nr;
+  int64_t et = (ceil_div(tot, 96) + 127) / 128 * 128;
+  et = std::min<int64_t>(std::max<int64_t>(et, 128), kGsElems);
+  g.tr = coarse ? kGsElems : std::max<int64_t>(1, et / nr);
+  g.tiles = (int)ceil_div(n, g.tr);
+  g.fold = (int64_t)g.tiles * nr <= 160;
+  return g;
 }
 
-int gmres_tiles(int64_t n) { return (int)ceil_div(n, kRowsPerTile); }
-
-// part[(k * tiles + tile) * nr + c] = sum over the tile's rows of
-// Q[k][i][c] * w[i][c]   (Q: nk vectors of n*nr doubles, stride ldq)
-__global__ __launch_bounds__(kGT) void k_dots(const double* __restrict__ Q, int64_t ldq,
-                                              const double* __restrict__ w, int64_t n, int nr,
-                                              int tiles, double* __restrict__ part) {
-  __shared__ double lds[kGT];
-  const int tile = blockIdx.x, k = blockIdx.y;
-  const double* q = Q + (int64_t)k * ldq;
-  const int per = kGT / nr;               // threads per column (nr <= 256)
-  const int c = threadIdx.x % nr, r0 = threadIdx.x / nr;
-  double acc = 0.0;
-  if (r0 < per) {
-    const int64_t beg = (int64_t)tile * kRowsPerTile;
-    const int64_t end = min(beg + kRowsPerTile, n);
-    for (int64_t i = beg + r0; i < end; i += per) acc += q[i * nr + c] * w[i * nr + c];
-  }
-  lds[threadIdx.x] = (r0 < per) ? acc : 0.0;
-  __syncthreads();
-  if ((int)threadIdx.x < nr) {
-    double s = 0.0;
-    for (int t = 0; t < per; ++t) s += lds[t * nr + threadIdx.x];
-    part[((int64_t)k * tiles + tile) * nr + threadIdx.x] = s;
-  }
-}
-
-// out[k * nr + c] = sum_tile part[(k * tiles + tile) * nr + c]: one
-// wavefront per output, lane l adding tiles l, l + 64, ... in order, then a
-// fixed shuffle tree (the same order every call).
-__device__ inline double tile_sum(const double* __restrict__ part, int k, int c, int tiles,
-                                  int nr) {
-  const int lane = threadIdx.x & 63;
+// Sum over the tiles of partial sum e = k nr + c (part[e * tiles + t]); one
+// wavefront, lanes over the tiles, a fixed order.
+__device__ inline double gs_tile_sum(const double* __restrict__ part, int64_t e, int tiles) {
   double s = 0.0;
-  for (int t = lane; t < tiles; t += 64) s += part[((int64_t)k * tiles + t) * nr + c];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  return s;
+  for (int t = threadIdx.x & 63; t < tiles; t += 64) s += part[e * tiles + t];
+  return wsum(s);
 }
-__global__ __launch_bounds__(256) void k_dots_final(const double* __restrict__ part, int nk,
-                                                    int tiles, int nr,
-                                                    double* __restrict__ out) {
+
+// Partial dots of the basis vectors [k0, k1) with the cnt elements of w held
+// in LDS (they start at element e0 of every vector): one wavefront per vector
+// and group of columns.  A power of two of columns up to 64 keeps every
+// lane's column fixed (lane mod nr) with contiguous reads; any other count
+// takes its columns one by one.  add: the tile's earlier pieces are there.
+__device__ inline void gs_dots(const double* __restrict__ Q, int64_t ldq, int k0, int k1,
+                               const double* __restrict__ ws, int64_t e0, int cnt, int nr,
+                               int tiles, int tile, bool add, double* __restrict__ part) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool pow2 = nr <= 64 && (nr & (nr - 1)) == 0;
+  const int per = pow2 ? 1 : nr;
+  for (int task = wave; task < (k1 - k0) * per; task += kGT / 64) {
+    const int k = k0 + task / per;
+    const int c0 = pow2 ? 0 : task % per;
+    const double* q = Q + (int64_t)k * ldq + e0;
+    double acc = 0.0;
+    if (pow2) {
+#pragma unroll 4
+      for (int e = lane; e < cnt; e += 64) acc += q[e] * ws[e];
+      if (nr == 1) {
+        acc = wsum(acc);
+      } else {
+        for (int off = 32; off >= nr; off >>= 1) acc += __shfl_xor(acc, off, 64);
+      }
+    } else {
+      for (int e = lane * nr + c0; e < cnt; e += 64 * nr) acc += q[e] * ws[e];
+      acc = wsum(acc);
+    }
+    const int cols = pow2 ? nr : 1;
+    if (lane < cols) {
+      double* o = part + ((int64_t)k * nr + c0 + lane) * tiles + tile;
+      *o = add ? *o + acc : acc;
+    }
+  }
+}
+
+// j: the step, from the argument or, in a captured graph, from jd[0].
+__device__ inline int gs_step(const int64_t* jd, int j) { return jd ? (int)jd[0] : j; }
+
+template <typename W>
+__global__ __launch_bounds__(kGT) void k_gs_first(const double* __restrict__ Q, int64_t ldq,
+                                                  const int64_t* __restrict__ jd, int nk,
+                                                  const W* __restrict__ w, GsShape G,
+                                                  double* __restrict__ part) {
+  __shared__ double ws[kGsElems];
+  const int nv = jd ? (int)jd[0] + 1 : nk;
+  const int k0 = blockIdx.y * kGsVecs, k1 = min(k0 + kGsVecs, nv);
+  if (k0 >= nv) return;                                 // uniform over the workgroup
+  const int64_t r0 = (int64_t)blockIdx.x * G.tr, r1 = min(r0 + G.tr, G.n);
+  const int sr = kGsElems / G.nr;
+  for (int64_t r = r0; r < r1; r += sr) {
+    const int cnt = (int)min((int64_t)sr, r1 - r) * G.nr;
+    const int64_t e0 = r * G.nr;
+    __syncthreads();                                    // the previous piece is consumed
+    for (int e = threadIdx.x; e < cnt; e += kGT) ws[e] = (double)w[e0 + e];
+    __syncthreads();
+    gs_dots(Q, ldq, k0, k1, ws, e0, cnt, G.nr, G.tiles, blockIdx.x, r > r0, part);
+  }
+}
+
+// out = in - Q h for the tile, h the sums of part_in (fold) or hsum, then the
+// partial dots Q^T out (LAST = false) or |out|^2 (LAST = true) into part_out.
+// With several workgroups per tile (blockIdx.y: groups of basis vectors for
+// the dots) each updates the tile for itself and the first one stores it; in
+// and out differ then.  h goes to hout, which may be hsum (the same values),
+// and part_out may be part_in when it is not read (no folding).
+template <typename W, bool LAST>
+__global__ __launch_bounds__(kGT) void k_gs_update(const double* __restrict__ Q, int64_t ldq,
+                                                   const int64_t* __restrict__ jd, int nk,
+                                                   const W* in, double* out, GsShape G,
+                                                   const double* part_in, const double* hsum,
+                                                   double* hout, double* part_out) {
+  __shared__ double ws[kGsElems];
+  __shared__ double hl[kGsH];
+  __shared__ double half[kGT];
+  const int nv = jd ? (int)jd[0] + 1 : nk;
+  const int nr = G.nr;
+  const int k0 = LAST ? 0 : (gridDim.y > 1 ? blockIdx.y * kGsVecs : 0);
+  const int k1 = LAST ? 0 : (gridDim.y > 1 ? min(k0 + kGsVecs, nv) : nv);
+  if (!LAST && k0 >= nv) return;                        // uniform over the workgroup
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t r0 = (int64_t)blockIdx.x * G.tr, r1 = min(r0 + G.tr, G.n);
+  const int sr = kGsElems / nr;
+  const int kc = kGsH / nr;                             // vectors whose h fits (nr <= 256)
+  for (int64_t r = r0; r < r1; r += sr) {
+    const int cnt = (int)min((int64_t)sr, r1 - r) * nr;
+    const int64_t e0 = r * nr;
+    // pieces of at most 128 elements: two threads per element, each half of
+    // the vectors of a chunk
+    const bool two = cnt <= kGT / 2;
+    __syncthreads();                                    // the previous piece is consumed
+    for (int e = threadIdx.x; e < cnt; e += kGT) ws[e] = (double)in[e0 + e];
+    double acc = 0.0;
+    for (int kb = 0; kb < nv; kb += kc) {
+      const int ke = min(kb + kc, nv);
+      __syncthreads();                                  // the previous chunk is consumed
+      if (G.fold) {
+        for (int i = wave; i < (ke - kb) * nr; i += kGT / 64) {
+          const double v = gs_tile_sum(part_in, (int64_t)kb * nr + i, G.tiles);
+          if (lane == 0) hl[i] = v;
+        }
+      } else {
+        for (int i = threadIdx.x; i < (ke - kb) * nr; i += kGT) hl[i] = hsum[(int64_t)kb * nr + i];
+      }
+      __syncthreads();
+      if (blockIdx.x == 0 && blockIdx.y == 0 && r == r0)
+        for (int i = threadIdx.x; i < (ke - kb) * nr; i += kGT) hout[(int64_t)kb * nr + i] = hl[i];
+      if (two) {
+        const int e = threadIdx.x & (kGT / 2 - 1), g = threadIdx.x / (kGT / 2);
+        if (e < cnt) {
+          const int c = e % nr;
+#pragma unroll 8
+          for (int k = kb + g; k < ke; k += 2) acc += Q[(int64_t)k * ldq + e0 + e] * hl[(k - kb) * nr + c];
+        }
+      } else {
+        for (int e = threadIdx.x; e < cnt; e += kGT) {
+          const int c = e % nr;
+          double v = ws[e];
+#pragma unroll 8
+          for (int k = kb; k < ke; ++k) v -= Q[(int64_t)k * ldq + e0 + e] * hl[(k - kb) * nr + c];
+          ws[e] = v;
+        }
+      }
+    }
+    if (two) {
+      half[threadIdx.x] = acc;
+      __syncthreads();
+      if ((int)threadIdx.x < cnt) ws[threadIdx.x] -= half[threadIdx.x] + half[threadIdx.x + kGT / 2];
+    }
+    __syncthreads();
+    if (blockIdx.y == 0)
+      for (int e = threadIdx.x; e < cnt; e += kGT) out[e0 + e] = ws[e];
+    if (!LAST) {
+      gs_dots(Q, ldq, k0, k1, ws, e0, cnt, nr, G.tiles, blockIdx.x, r > r0, part_out);
+    } else {
+      for (int c = wave; c < nr; c += kGT / 64) {
+        double v = 0.0;
+        for (int e = lane * nr + c; e < cnt; e += 64 * nr) v += ws[e] * ws[e];
+        v = wsum(v);
+        if (lane == 0) {
+          double* o = part_out + (int64_t)c * G.tiles + blockIdx.x;
+          *o = r > r0 ? *o + v : v;
+        }
+      }
+    }
+  }
+}
+
+// out[e] = sum of the tiles of part[e * tiles + t], one wavefront per output.
+__global__ __launch_bounds__(256) void k_gs_final(const double* __restrict__ part,
+                                                  const int64_t* __restrict__ jd, int nk, int nr,
+                                                  int tiles, double* __restrict__ out) {
+  const int nv = jd ? (int)jd[0] + 1 : nk;
   const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (e >= nk * nr) return;                          // uniform over the wavefront
-  const double s = tile_sum(part, e / nr, e % nr, tiles, nr);
+  if (e >= nv * nr) return;                             // uniform over the wavefront
+  const double s = gs_tile_sum(part, e, tiles);
   if ((threadIdx.x & 63) == 0) out[e] = s;
 }
 
-// w[i][c] -= sum_{k < nk} Q[k][i][c] h[k][c]   (h on the device)
-__global__ void k_orth_update(const double* __restrict__ Q, int64_t ldq, const double* __restrict__ h,
-                              int nk, int64_t n, int nr, double* __restrict__ w) {
-  const int64_t tot = n * nr;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < tot;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(e % nr);
-    double v = w[e];
-    for (int k = 0; k < nk; ++k) v -= Q[(int64_t)k * ldq + e] * h[k * nr + c];
-    w[e] = v;
+// q = w / |w| into basis vector j + 1 and into the next product's input (xq,
+// double or float; may be null), 0 for a column of norm 0.  |w|^2 is the sum
+// of part (fold) or nsum.  The first workgroup also writes the step's
+// coefficients h1 + h2 and |w| per column to res ([(j + 1) nr], [nr]) and
+// then, if seq is given, the number seqv + j + 1 to *seq: res and seq are
+// then host memory that the host polls (else res is device memory whose
+// coefficients may be h1 itself).
+template <typename X>
+__global__ __launch_bounds__(kGT) void k_gs_next(double* __restrict__ Q, int64_t ldq,
+                                                 const int64_t* __restrict__ jd, int j0,
+                                                 const double* __restrict__ w, GsShape G,
+                                                 const double* __restrict__ part,
+                                                 const double* __restrict__ nsum, const double* h1,
+                                                 const double* h2, X* __restrict__ xq, double* res,
+                                                 int64_t res_slot, int64_t* seq, int64_t seqv) {
+  __shared__ double hn[256];                            // nr <= 256
+  const int j = jd ? (int)jd[0] : j0;
+  if (jd) seqv = jd[1];
+  const int nr = G.nr, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int c = wave; c < nr; c += kGT / 64) {
+    const double v = G.fold ? gs_tile_sum(part, c, G.tiles) : nsum[c];
+    if (lane == 0) hn[c] = sqrt(fmax(v, 0.0));
   }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    double* o = res + (int64_t)(j & 1) * res_slot;
+    for (int i = threadIdx.x; i < (j + 1) * nr; i += kGT) o[nr + i] = h1[i] + h2[i];
+    for (int i = threadIdx.x; i < nr; i += kGT) o[i] = hn[i];
+    if (seq) {
+      __threadfence_system();
+      __syncthreads();
+      if (threadIdx.x == 0)
+        __hip_atomic_store(seq, seqv + j + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
+  double* q = Q + (int64_t)(j + 1) * ldq;
+  for (int64_t e = blockIdx.x * (int64_t)kGT + threadIdx.x; e < ldq;
+       e += (int64_t)gridDim.x * kGT) {
+    const double h = hn[e % nr];
+    const double v = h > 0.0 ? w[e] * (1.0 / h) : 0.0;
+    q[e] = v;
+    if (xq) xq[e] = (X)v;
+  }
+}
+
+// q0 = r * scale per column, into the basis and the product's input.
+template <typename X>
+__global__ __launch_bounds__(kGT) void k_gs_start(const double* __restrict__ r,
+                                                  const double* __restrict__ sc, int64_t tot,
+                                                  int nr, double* __restrict__ q,
+                                                  X* __restrict__ xq, int64_t* jd, int64_t seqv) {
+  for (int64_t e = blockIdx.x * (int64_t)kGT + threadIdx.x; e < tot;
+       e += (int64_t)gridDim.x * kGT) {
+    const double v = r[e] * sc[e % nr];
+    q[e] = v;
+    if (xq) xq[e] = (X)v;
+  }
+  if (jd && blockIdx.x == 0 && threadIdx.x == 0) {      // graph replays count their steps here
+    jd[0] = 0;
+    jd[1] = seqv;
+  }
+}
+__global__ void k_gs_advance(int64_t* jd) {
+  if (threadIdx.x == 0) jd[0] += 1;
 }
 
 // x[i][c] += sum_{k < nk} Q[k][i][c] y[k][c]
@@ -119,77 +326,6 @@ __global__ void k_convert(const S* __restrict__ a, int64_t tot, D* __restrict__ 
     out[e] = (D)a[e];
 }
 
-// Variants for graph replays: the Arnoldi step j is read from device memory
-// (jd[0]); the grids cover the largest step, blocks past it return at once.
-__global__ __launch_bounds__(kGT) void k_dots_dev(const double* __restrict__ Q, int64_t ldq,
-                                                  const int* __restrict__ jd,
-                                                  const double* __restrict__ w, int64_t n, int nr,
-                                                  int tiles, double* __restrict__ part) {
-  if ((int)blockIdx.y > jd[0]) return;               // uniform over the block
-  __shared__ double lds[kGT];
-  const int tile = blockIdx.x, k = blockIdx.y;
-  const double* q = Q + (int64_t)k * ldq;
-  const int per = kGT / nr;
-  const int c = threadIdx.x % nr, r0 = threadIdx.x / nr;
-  double acc = 0.0;
-  if (r0 < per) {
-    const int64_t beg = (int64_t)tile * kRowsPerTile;
-    const int64_t end = min(beg + kRowsPerTile, n);
-    for (int64_t i = beg + r0; i < end; i += per) acc += q[i * nr + c] * w[i * nr + c];
-  }
-  lds[threadIdx.x] = (r0 < per) ? acc : 0.0;
-  __syncthreads();
-  if ((int)threadIdx.x < nr) {
-    double s = 0.0;
-    for (int t = 0; t < per; ++t) s += lds[t * nr + threadIdx.x];
-    part[((int64_t)k * tiles + tile) * nr + threadIdx.x] = s;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_dots_final_dev(const double* __restrict__ part,
-                                                        const int* __restrict__ jd, int nkmax,
-                                                        int tiles, int nr,
-                                                        double* __restrict__ out) {
-  const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int nk = jd[0] + 1;
-  if (e >= nk * nr || e >= nkmax * nr) return;       // uniform over the wavefront
-  const double s = tile_sum(part, e / nr, e % nr, tiles, nr);
-  if ((threadIdx.x & 63) == 0) out[e] = s;
-}
-
-__global__ void k_orth_update_dev(const double* __restrict__ Q, int64_t ldq,
-                                  const double* __restrict__ h, const int* __restrict__ jd,
-                                  int64_t n, int nr, double* __restrict__ w) {
-  const int nk = jd[0] + 1;
-  const int64_t tot = n * nr;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < tot;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(e % nr);
-    double v = w[e];
-    for (int k = 0; k < nk; ++k) v -= Q[(int64_t)k * ldq + e] * h[k * nr + c];
-    w[e] = v;
-  }
-}
-
-// out = Q[jd[0]] (the Arnoldi vector of step j, into a fixed buffer)
-__global__ void k_copy_col(const double* __restrict__ Q, int64_t ldq, const int* __restrict__ jd,
-                           double* __restrict__ out) {
-  const double* q = Q + (int64_t)jd[0] * ldq;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < ldq;
-       e += (int64_t)gridDim.x * blockDim.x)
-    out[e] = q[e];
-}
-
-// out = (float) Q[jd[0]]: the Arnoldi vector of step j rounded to single
-// precision, the input of a product with float vectors
-__global__ void k_copy_col_f32(const double* __restrict__ Q, int64_t ldq, const int* __restrict__ jd,
-                               float* __restrict__ out) {
-  const double* q = Q + (int64_t)jd[0] * ldq;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < ldq;
-       e += (int64_t)gridDim.x * blockDim.x)
-    out[e] = (float)q[e];
-}
-
 // ---- conjugate gradients (Sec. 4.1), every column its own recurrence.
 // alpha_c = rr[c] / pq[c] for active columns (0 for inactive ones and for
 // pq = 0); x += alpha p, r -= alpha q.
@@ -230,41 +366,67 @@ void cg_dir(double* p, const double* r, const double* rr_new, const double* rr_o
   k_cg_dir<<<grid_for(n * nr, 256, 8192), 256, 0, s>>>(p, r, rr_new, rr_old, active, n, nr);
   HM_LAUNCH_CHECK();
 }
-void gmres_dots_dev(const double* Q, int64_t ldq, const int* jd, int nkmax, const double* w,
-                    int64_t n, int nr, double* part, double* out, hipStream_t s) {
-  const int tiles = gmres_tiles(n);
-  dim3 grid(tiles, nkmax);
-  k_dots_dev<<<grid, kGT, 0, s>>>(Q, ldq, jd, w, n, nr, tiles, part);
+// The orthogonalisation of step j (or jd[0] in a capture) after the product
+// win = op(H) q_j, and the next basis vector.  nkmax: basis vectors the
+// grids cover (j + 1, or the most a replay can need).
+template <typename W, typename X>
+static void gs_arnoldi(const GsArgs& a, const W* win, X* xq, int j, int nkmax, hipStream_t s) {
+  const GsShape& G = a.G;
+  const int64_t tot = G.n * G.nr;
+  const int nk = j + 1;
+  const unsigned kg = (unsigned)ceil_div(nkmax, kGsVecs);
+  const unsigned fin = (unsigned)ceil_div((int64_t)nkmax * G.nr, 4);
+  double *h1 = a.h1, *h2 = a.h2;
+  auto total = [&](const double* part, int cnt, const int64_t* jd, double* out) {
+    if (G.fold) return;
+    k_gs_final<<<fin, 256, 0, s>>>(part, jd, cnt, G.nr, G.tiles, out);
+    HM_LAUNCH_CHECK();
+  };
+  k_gs_first<W><<<dim3(G.tiles, kg), kGT, 0, s>>>(a.Q, tot, a.jd, nk, win, G, a.part);
   HM_LAUNCH_CHECK();
-  k_dots_final_dev<<<(unsigned)ceil_div(nkmax * nr, 4), 256, 0, s>>>(part, jd, nkmax, tiles, nr,
-                                                                      out);
+  total(a.part, nk, a.jd, h2);
+  // several workgroups per tile only where tiles alone leave the chip idle:
+  // each repeats the update, which reads the whole basis
+  k_gs_update<W, false><<<dim3(G.tiles, G.fold ? kg : 1), kGT, 0, s>>>(
+      a.Q, tot, a.jd, nk, win, a.w1, G, a.part, h2, h1, a.part2);
+  HM_LAUNCH_CHECK();
+  total(a.part2, nk, a.jd, h2);
+  k_gs_update<double, true><<<dim3(G.tiles, 1), kGT, 0, s>>>(a.Q, tot, a.jd, nk, a.w1, a.w1, G,
+                                                             a.part2, h2, h2, a.part);
+  HM_LAUNCH_CHECK();
+  total(a.part, 1, nullptr, a.nsum);
+  k_gs_next<X><<<grid_for(tot, kGT, 2048), kGT, 0, s>>>(a.Q, tot, a.jd, j, a.w1, G, a.part,
+                                                        a.nsum, h1, h2, xq, a.res, a.res_slot, a.seq,
+                                                        a.seqv);
+  HM_LAUNCH_CHECK();
+  if (a.jd) {
+    k_gs_advance<<<1, 64, 0, s>>>(a.jd);
+    HM_LAUNCH_CHECK();
+  }
+}
+void gmres_arnoldi(const GsArgs& a, int j, int nkmax, hipStream_t s) {
+  if (a.wf)
+    gs_arnoldi<float, float>(a, a.wf, a.xf, j, nkmax, s);
+  else
+    gs_arnoldi<double, double>(a, a.w, a.xin, j, nkmax, s);
+}
+void gmres_start(const GsArgs& a, const double* r, const double* sc, hipStream_t s) {
+  const int64_t tot = a.G.n * a.G.nr;
+  const unsigned g = grid_for(tot, kGT, 2048);
+  if (a.wf)
+    k_gs_start<float><<<g, kGT, 0, s>>>(r, sc, tot, a.G.nr, a.Q, a.xf, a.jd, a.seqv);
+  else
+    k_gs_start<double><<<g, kGT, 0, s>>>(r, sc, tot, a.G.nr, a.Q, a.xin, a.jd, a.seqv);
   HM_LAUNCH_CHECK();
 }
-void gmres_orth_update_dev(const double* Q, int64_t ldq, const double* h, const int* jd,
-                           int64_t n, int nr, double* w, hipStream_t s) {
-  k_orth_update_dev<<<grid_for(n * nr, 256, 8192), 256, 0, s>>>(Q, ldq, h, jd, n, nr, w);
+// out[k nr + c] = Q_k . w per column
+void gmres_dots(const double* Q, int nk, const double* w, const GsShape& G, double* part,
+                double* out, hipStream_t s) {
+  k_gs_first<double><<<dim3(G.tiles, (unsigned)ceil_div(nk, kGsVecs)), kGT, 0, s>>>(
+      Q, G.n * G.nr, nullptr, nk, w, G, part);
   HM_LAUNCH_CHECK();
-}
-void gmres_copy_col(const double* Q, int64_t ldq, const int* jd, double* out, hipStream_t s) {
-  k_copy_col<<<grid_for(ldq, 256, 8192), 256, 0, s>>>(Q, ldq, jd, out);
-  HM_LAUNCH_CHECK();
-}
-void gmres_copy_col_f32(const double* Q, int64_t ldq, const int* jd, float* out, hipStream_t s) {
-  k_copy_col_f32<<<grid_for(ldq, 256, 8192), 256, 0, s>>>(Q, ldq, jd, out);
-  HM_LAUNCH_CHECK();
-}
-void gmres_dots(const double* Q, int64_t ldq, int nk, const double* w, int64_t n, int nr,
-                double* part, double* out, hipStream_t s) {
-  const int tiles = gmres_tiles(n);
-  dim3 grid(tiles, nk);
-  k_dots<<<grid, kGT, 0, s>>>(Q, ldq, w, n, nr, tiles, part);
-  HM_LAUNCH_CHECK();
-  k_dots_final<<<(unsigned)ceil_div(nk * nr, 4), 256, 0, s>>>(part, nk, tiles, nr, out);
-  HM_LAUNCH_CHECK();
-}
-void gmres_orth_update(const double* Q, int64_t ldq, const double* h, int nk, int64_t n, int nr,
-                       double* w, hipStream_t s) {
-  k_orth_update<<<grid_for(n * nr, 256, 8192), 256, 0, s>>>(Q, ldq, h, nk, n, nr, w);
+  k_gs_final<<<(unsigned)ceil_div((int64_t)nk * G.nr, 4), 256, 0, s>>>(part, nullptr, nk, G.nr,
+                                                                       G.tiles, out);
   HM_LAUNCH_CHECK();
 }
 void gmres_combine(const double* Q, int64_t ldq, const double* y, int nk, int64_t n, int nr,

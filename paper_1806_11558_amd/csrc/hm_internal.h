@@ -303,6 +303,36 @@ void launch_unpack(const int2* lr, int64_t b, const Cluster* cl, const int32_t* 
 void matvec_dispatch(const MvPlan& P, int storage, const void* x, void* y, int nrhs,
                      int vec_f32, bool transposed, hipStream_t s);
 
+// ---------------------------------------------------------------- Arnoldi step
+// Row tiles of the solver's dot products (see hm_gmres.hip); coarse: 2,048
+// rows a tile, for a fixed workspace that the finer tiles would not fit.
+struct GsShape {
+  int64_t n = 0, tr = 0;    // rows, rows per tile
+  int nr = 0, tiles = 0;
+  bool fold = false;        // every workgroup adds the tile sums it needs itself
+};
+GsShape gs_shape(int64_t n, int nr, bool coarse);
+struct GsArgs {
+  GsShape G;
+  double* Q;                // basis, vectors of n nr
+  double* w;                // product (double), or wf (float) with refinement
+  const float* wf;
+  double* w1;               // the vector after the first pass (not w)
+  double* xin;              // the next product's input: double (may be null) ...
+  float* xf;                // ... or float
+  double *part, *part2;     // partial sums [nk nr][tiles]
+  double *h1, *h2;          // coefficients of both passes; h2 also takes the sums of
+                            // a pass when they are not folded
+  double* nsum;             // sums of the norm, not folded
+  double* res;              // results per step, two slots of res_slot
+  int64_t res_slot;
+  int64_t* seq;             // step counter the host polls, or null
+  int64_t seqv;             // its value before step 0
+  int64_t* jd;              // device step counter of a graph, or null
+};
+void gmres_arnoldi(const GsArgs& a, int j, int nkmax, hipStream_t s);
+void gmres_start(const GsArgs& a, const double* r, const double* sc, hipStream_t s);
+
 // ---------------------------------------------------------------- primitives
 // Exclusive scan of int64 values; *d_total (device) receives the sum.
 void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* d_total,
@@ -326,6 +356,9 @@ void* dalloc_pool(size_t bytes, hipStream_t s);
 // arena ends, after the stream is synchronised; requests above kArenaMax go
 // to the pool as before.  host is a page of pinned memory that kernels write
 // totals to, so that reading one back is a synchronisation and no copy.
+constexpr int kPageWords = 4096;
+int64_t* page_take(bool may_allocate);  // null if none is kept and none may be allocated
+void page_give(int64_t* p);
 struct BuildArena {
   static constexpr size_t kChunk = size_t(32) << 20, kArenaMax = size_t(4) << 20;
   explicit BuildArena(hipStream_t s);
@@ -335,8 +368,7 @@ struct BuildArena {
   void* get(size_t bytes);
   bool put(void* p);                    // false: not a block of this arena
   hipStream_t stream;
-  int64_t* host = nullptr;              // kHostWords words, device-accessible
-  static constexpr int kHostWords = 512;
+  int64_t* host = nullptr;              // kPageWords words, device-accessible
   // the arena of this thread's build on stream s, or null
   static BuildArena* current(hipStream_t s);
 

@@ -118,27 +118,46 @@ void dfree(void* p, hipStream_t s) {
 // ---- arena of a build
 namespace {
 thread_local BuildArena* t_arena = nullptr;
-// pinned pages not in use, at most kKeepPages (one per build running at once)
+// pinned pages not in use, at most kKeepPages (one per build or solve running
+// at once)
 constexpr size_t kKeepPages = 8;
 std::mutex g_page_mu;
 std::vector<int64_t*> g_pages;
 }  // namespace
+
+int64_t* page_take(bool may_allocate) {
+  {
+    std::lock_guard<std::mutex> lk(g_page_mu);
+    if (!g_pages.empty()) {
+      int64_t* p = g_pages.back();
+      g_pages.pop_back();
+      return p;
+    }
+  }
+  int64_t* p = nullptr;
+  if (may_allocate)
+    HM_HIP(hipHostMalloc((void**)&p, kPageWords * sizeof(int64_t),
+                         hipHostMallocPortable | hipHostMallocMapped));
+  return p;
+}
+
+void page_give(int64_t* p) {
+  {
+    std::lock_guard<std::mutex> lk(g_page_mu);
+    if (g_pages.size() < kKeepPages) {
+      g_pages.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
 
 BuildArena* BuildArena::current(hipStream_t s) {
   return t_arena && t_arena->stream == s ? t_arena : nullptr;
 }
 
 BuildArena::BuildArena(hipStream_t s) : stream(s) {
-  {
-    std::lock_guard<std::mutex> lk(g_page_mu);
-    if (!g_pages.empty()) {
-      host = g_pages.back();
-      g_pages.pop_back();
-    }
-  }
-  if (!host)
-    HM_HIP(hipHostMalloc((void**)&host, kHostWords * sizeof(int64_t),
-                         hipHostMallocPortable | hipHostMallocMapped));
+  host = page_take(true);
   outer_ = t_arena;
   t_arena = this;
 }
@@ -148,11 +167,7 @@ BuildArena::~BuildArena() {
   // nothing in flight may still use the chunks or the page
   (void)hipStreamSynchronize(stream);
   for (auto& c : chunks_) cache_put(c.first, c.second);
-  std::lock_guard<std::mutex> lk(g_page_mu);
-  if (g_pages.size() < kKeepPages)
-    g_pages.push_back(host);
-  else
-    (void)hipHostFree(host);
+  page_give(host);
 }
 
 // Sizes rounded up to four steps per power of two, at least 256 bytes, so
