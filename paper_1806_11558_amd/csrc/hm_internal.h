@@ -172,13 +172,15 @@ struct MvProfile {
 // of one run of a row leaf, so that a leaf with a wide panel is shared by
 // several workgroups.  Everything a workgroup needs to start its loads is in
 // the record: the address of the first column, the first column's index
-// (colmap, w), the leaf's first position, size and ld, and whether the panel
-// is dense (else U slices).  Units of a leaf are consecutive.
+// (colmap, w), the leaf's first position, first padded row (ldpre), size and
+// ld, and whether the panel is dense (else U slices).  Units of a leaf are
+// consecutive.
 struct Unit {
   uint64_t data;
   int64_t col;
   int32_t w, lo;
-  uint16_t ld, m, dense, pad;
+  uint32_t ldp;
+  uint8_t ld, m, dense, pad;
 };
 constexpr int kUnitCols = 1024;
 // Columns of a phase-1 unit on the matrix cores: four tiles of 16 terms share

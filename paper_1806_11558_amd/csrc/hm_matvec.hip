@@ -117,15 +117,14 @@ __device__ inline int64_t xcd_item(int64_t li, int64_t per) {
 
 // ------------------------------------------------------------------ gather
 template <typename VT, typename A>
-__global__ void k_gather(const VT* __restrict__ x, int nrhs, int k0, int nr, int nv,
+__global__ void k_gather(const VT* __restrict__ x, int nrhs, int k0, int nr,
                          const int32_t* __restrict__ perm, int64_t n, A* __restrict__ z) {
-  // columns nv .. nr - 1 (a pass wider than what is left) are zero
   const int64_t tot = n * nr;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < tot;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t p = e / nr;
     const int k = (int)(e % nr);
-    z[e] = k < nv ? (A)x[(int64_t)perm[p] * nrhs + k0 + min(k, nv - 1)] : (A)0;
+    z[e] = (A)x[(int64_t)perm[p] * nrhs + k0 + k];
   }
 }
 
@@ -591,6 +590,27 @@ __device__ inline void fwd1x_rows(const T* __restrict__ S, const A* __restrict__
       for (int t = 0; t < NTL; ++t) acc[t] = mfma16((A)av[u][t][e], bv[u][e], acc[t]);
 }
 
+// All rows of one leaf: the columns tc of the slice S against the leaf's x.
+template <typename T, typename A, int NTL>
+__device__ inline void fwd1x_leaf(const T* __restrict__ S, const A* __restrict__ xb, int ld,
+                                  const int (&tc)[NTL], int xo, int lq,
+                                  typename Mfma<A>::V (&acc)[4]) {
+  // tiles of 16 rows, two at a time where their registers fit
+  constexpr int IU = sizeof(T) == 8 ? 1 : 2;
+  int i0 = 0;
+  for (; i0 + 16 * IU <= ld; i0 += 16 * IU)
+    fwd1x_rows<T, A, NTL, 4, IU>(S, xb, ld, i0, tc, xo, lq, acc);
+  if (IU == 2 && i0 + 16 <= ld) {
+    fwd1x_rows<T, A, NTL, 4, 1>(S, xb, ld, i0, tc, xo, lq, acc);
+    i0 += 16;
+  }
+  if (ld & 8) {
+    fwd1x_rows<T, A, NTL, 2, 1>(S, xb, ld, i0, tc, xo, lq, acc);
+    i0 += 8;
+  }
+  if (ld & 4) fwd1x_rows<T, A, NTL, 1, 1>(S, xb, ld, i0, tc, xo, lq, acc);
+}
+
 template <typename T, typename A, int NR, int NTL>
 __device__ inline void fwd1x_pass(const LrMeta& M, const MvLeaves& L, const A* __restrict__ xt,
                                   int tg, int r, int lr, int lq,
@@ -599,28 +619,41 @@ __device__ inline void fwd1x_pass(const LrMeta& M, const MvLeaves& L, const A* _
   int tc[NTL];                            // clamped term of each tile
 #pragma unroll
   for (int t = 0; t < NTL; ++t) tc[t] = min(tg + t * 16 + lr, r - 1);
-  const int xo = lr & (NR - 1);           // NR = 8: columns 8 .. 15 repeat, not stored
+  const int xo = lr & (NR - 1);           // NR < 16: columns repeat, not stored
   int64_t lp = L.ldpre[M.sf];
   for (int lf = M.sf; lf <= M.sl; ++lf) {
     const int64_t lpn = L.ldpre[lf + 1];
     const int ld = (int)(lpn - lp);
-    const A* xb = xt + lp * NR;
-    // tiles of 16 rows, two at a time where their registers fit
-    constexpr int IU = sizeof(T) == 8 ? 1 : 2;
-    int i0 = 0;
-    for (; i0 + 16 * IU <= ld; i0 += 16 * IU)
-      fwd1x_rows<T, A, NTL, 4, IU>(S, xb, ld, i0, tc, xo, lq, acc);
-    if (IU == 2 && i0 + 16 <= ld) {
-      fwd1x_rows<T, A, NTL, 4, 1>(S, xb, ld, i0, tc, xo, lq, acc);
-      i0 += 16;
-    }
-    if (ld & 8) {
-      fwd1x_rows<T, A, NTL, 2, 1>(S, xb, ld, i0, tc, xo, lq, acc);
-      i0 += 8;
-    }
-    if (ld & 4) fwd1x_rows<T, A, NTL, 1, 1>(S, xb, ld, i0, tc, xo, lq, acc);
+    fwd1x_leaf<T, A, NTL>(S, xt + lp * NR, ld, tc, xo, lq, acc);
     S += (int64_t)ld * M.vw;
     lp = lpn;
+  }
+}
+
+// Calls put(row, rhs, value) for the rows and right-hand sides of a 16-row
+// result tile.  In double and for 16 columns the lanes of one call already
+// lie side by side in memory; with fewer float columns a call per item would
+// write 16- or 32-byte pieces, so the items are exchanged first and a call
+// covers 16 / NR rows of every quad.
+template <typename A, int NR, typename Put>
+__device__ inline void tile_out(const typename Mfma<A>::V& acc, int lr, int lq, const Put& put) {
+  if constexpr (sizeof(A) == 8 || NR == 16) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (lr < NR) put(Mfma<A>::row(j, lq), lr, acc[j]);
+  } else {
+    constexpr int GR = 16 / NR;                  // rows per call
+    const int g = lr / NR, k = lr & (NR - 1);
+#pragma unroll
+    for (int h = 0; h < 4; h += GR) {
+      A v = 0;
+#pragma unroll
+      for (int q = 0; q < GR; ++q) {
+        const A o = __shfl(acc[h + q], lq * 16 + k, 64);
+        v = g == q ? o : v;
+      }
+      put(4 * lq + h + g, k, v);
+    }
   }
 }
 
@@ -653,14 +686,13 @@ __global__ __launch_bounds__(256) void k_fwd1x(const LrMeta* __restrict__ meta, 
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         if (t < ntile) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int term = tg + t * 16 + Mfma<A>::row(j, lq);
-            if (term < r && lr < NR) {
+          tile_out<A, NR>(acc[t], lr, lq, [&](int row, int k, A v) {
+            const int term = tg + t * 16 + row;
+            if (term < r) {
               const A sc = su ? (A)su[M.toff + term] : (A)1;
-              zt[(n + M.toff + term) * NR + lr] = acc[t][j] * sc;
+              zt[(n + M.toff + term) * NR + k] = v * sc;
             }
-          }
+          });
         }
       }
     }
@@ -694,13 +726,14 @@ template <typename E, typename A, int NR, int KQ, int NT>
 struct ColBatch {
   E av[KQ][NT];
   A bv[KQ];
-  // columns c0 + 4 u + lq; mc: the map entries of the batch (lane = column);
-  // r1, r2: the lane's first rows
+  // columns c0 + 4 u + lq; mc: the map entries of the batch (lane = column),
+  // or, without a map, the z row of column 0; r1, r2: the lane's first rows
+  template <bool MAP>
   __device__ inline void load(const E* __restrict__ P, const A* __restrict__ z, int mc, int c0,
                               int w, int ld, int r1, int r2, int xo, int lq) {
 #pragma unroll
     for (int u = 0; u < KQ; ++u) {
-      const int zi = __shfl(mc, 4 * u + lq, 64);
+      const int zi = MAP ? __shfl(mc, 4 * u + lq, 64) : mc + min(c0 + 4 * u + lq, w - 1);
       const uint32_t pc = (uint32_t)(min(c0 + 4 * u + lq, w - 1) * ld);   // 32 bits hold a unit
       if constexpr (NT == 4 && sizeof(E) < 8) {
         load_n<E, 4, true>(at32(P, pc + r1), av[u]);
@@ -756,14 +789,14 @@ __device__ inline void fwd2x_cols(const E* __restrict__ P, const int32_t* __rest
   int c = wave * CB;
   if (c + CB <= w) {
     int ma = at(c), mb = at(c + STEP);
-    b0.load(P, z, ma, c, w, ld, r1, r2, xo, lq);
+    b0.template load<true>(P, z, ma, c, w, ld, r1, r2, xo, lq);
     for (; c + STEP + CB <= w; c += 2 * STEP) {         // two batches, no branch between them
       ma = at(c + 2 * STEP);
-      b1.load(P, z, mb, c + STEP, w, ld, r1, r2, xo, lq);
+      b1.template load<true>(P, z, mb, c + STEP, w, ld, r1, r2, xo, lq);
       __builtin_amdgcn_sched_barrier(0);
       b0.mul(acc);
       mb = at(c + 3 * STEP);
-      b0.load(P, z, ma, c + 2 * STEP, w, ld, r1, r2, xo, lq);
+      b0.template load<true>(P, z, ma, c + 2 * STEP, w, ld, r1, r2, xo, lq);
       __builtin_amdgcn_sched_barrier(0);
       b1.mul(acc);
     }
@@ -773,7 +806,7 @@ __device__ inline void fwd2x_cols(const E* __restrict__ P, const int32_t* __rest
     }
   }
   if (c < w) {
-    b0.load(P, z, at(c), c, w, ld, r1, r2, xo, lq);
+    b0.template load<true>(P, z, at(c), c, w, ld, r1, r2, xo, lq);
     b0.mask(c, w, lq);
     b0.mul(acc);
   }
@@ -958,6 +991,67 @@ __global__ __launch_bounds__(256) void k_tr1(const Unit* __restrict__ units, int
   }
 }
 
+// The same on the matrix cores for 4 to 16 right-hand sides: the columns of a
+// unit, 64 at a time per wavefront, are the terms of phase 1 (one leaf, the
+// panel in place of the V slice).  On the vector units every column cost its
+// own reduction over the rows.  Whole products at N = 32,000, leaf 64: FP64
+// 4 columns 1,107 -> 447 us, 8 2,222 -> 509, 16 5,196 -> 686; FP32 4 columns
+// 288 -> 247, 16 1,055 -> 395 (leaf 32, 4 columns: 235 and 238).  Bound by HBM and by w itself, which is as many
+// bytes as 2/5 of an FP32 panel of 40 rows at 16 columns.
+template <typename T, typename A, int NR>
+__device__ inline void tr1x_unit(const Unit& U, const A* __restrict__ xt, A* __restrict__ w,
+                                 int wave, int lane) {
+  using V = typename Mfma<A>::V;
+  const int lr = lane & 15, lq = lane >> 4;
+  const int xo = lr & (NR - 1), ld = U.ld;
+  const T* S = reinterpret_cast<const T*>((uintptr_t)U.data);
+  const A* xb = xt + (int64_t)U.ldp * NR;
+  for (int c0 = wave * 64; c0 < U.w; c0 += 256) {
+    const int r = min(64, U.w - c0), ntile = (r + 15) / 16;
+    V acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = V{0, 0, 0, 0};
+    const T* Sc = S + (int64_t)c0 * ld;
+    auto go = [&](auto nt) {
+      constexpr int NTL = decltype(nt)::value;
+      int tc[NTL];
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) tc[t] = min(t * 16 + lr, r - 1);
+      fwd1x_leaf<T, A, NTL>(Sc, xb, ld, tc, xo, lq, acc);
+    };
+    switch (ntile) {                        // uniform over the wavefront
+      case 1: go(std::integral_constant<int, 1>{}); break;
+      case 2: go(std::integral_constant<int, 2>{}); break;
+      case 3: go(std::integral_constant<int, 3>{}); break;
+      default: go(std::integral_constant<int, 4>{}); break;
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (t < ntile)
+        tile_out<A, NR>(acc[t], lr, lq, [&](int row, int k, A v) {
+          const int col = t * 16 + row;
+          if (col < r) w[(U.col + c0 + col) * NR + k] = v;
+        });
+  }
+}
+
+template <typename TD, typename TL, typename A, int NR>
+__global__ __launch_bounds__(256) void k_tr1x(const Unit* __restrict__ units, int64_t nunits,
+                                              const A* __restrict__ xt, A* __restrict__ w) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t per = (nunits + kXcds - 1) / kXcds;
+  for (int64_t li = blockIdx.x; li < per * kXcds; li += gridDim.x) {
+    const int64_t u = xcd_item(li, per);
+    if (u >= nunits) continue;
+    const Unit U = units[u];
+    if (std::is_same<TD, TL>::value || U.dense)
+      tr1x_unit<TD, A, NR>(U, xt, w, wave, lane);
+    else
+      tr1x_unit<TL, A, NR>(U, xt, w, wave, lane);
+  }
+}
+
 // s_b[l] = sum over the row leaves of b of w[ucol + l]  ->  z[n + toff + l].
 // The sums of one block, lane = (group, term): with r <= 16 (32) the
 // wavefront splits into four (two) groups of 16 (32) lanes; group g adds the
@@ -1065,7 +1159,7 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
                                              const TItem* __restrict__ items, MvLeaves L,
                                              const A* __restrict__ w, const A* __restrict__ z,
                                              int64_t n, const int32_t* __restrict__ perm,
-                                             VT* __restrict__ y, int nrhs, int k0, int nv, int S,
+                                             VT* __restrict__ y, int nrhs, int k0, int S,
                                              A* __restrict__ ypart, int ldmax) {
   constexpr int G = Gran<T>::G;
   __shared__ A ybuf[4][kMaxLeaf][NR];
@@ -1182,6 +1276,103 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
       const A v = ((ybuf[0][row][k] + ybuf[1][row][k]) + ybuf[2][row][k]) + ybuf[3][row][k];
       if (S > 1)
         yp[e] = v;
+      else
+        y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
+    }
+    __syncthreads();
+  }
+}
+
+// The same on the matrix cores for 4 to 16 right-hand sides: V items are
+// column batches as in the forward phase 2, with consecutive z rows; the w
+// entries of dense items, NR values per row of the leaf, are read as one
+// contiguous run, value e by lane e mod 64.
+template <typename T, typename A, int NR, int NT>
+__device__ inline void tr2x_items(const TItem* __restrict__ items, int it0, int b1, int step,
+                                  int ld, const A* __restrict__ w, const A* __restrict__ z,
+                                  int64_t n, int lane, A (*ybuf)[NR]) {
+  constexpr int KQ = sizeof(A) == 8 ? 2 : 4, CB = 4 * KQ;
+  const int lr = lane & 15, lq = lane >> 4;
+  const int f1 = fwd2x_row<T, NT>(0, lr), f2 = NT >= 3 ? fwd2x_row<T, NT>(2, lr) : 0;
+  const int r1 = min(f1, ld - (NT == 1 ? 1 : (NT == 4 && sizeof(T) < 8 ? 4 : 2)));
+  const int r2 = NT >= 3 ? min(f2, ld - (NT - 2)) : 0;
+  const int xo = lr & (NR - 1);
+  typename Mfma<A>::V acc[NT];
+  A yd[NR];                                     // dense items: values lane + 64 k of rows x NR
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = typename Mfma<A>::V{0, 0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < NR; ++k) yd[k] = 0;
+  TItem In;
+  if (it0 < b1) In = items[it0];
+  for (int it = it0; it < b1; it += step) {
+    const TItem I = In;
+    if (it + step < b1) In = items[it + step];          // one iteration ahead
+    if (I.kind == 0) {
+      const A* ws = w + I.src * NR;
+#pragma unroll
+      for (int k = 0; k < NR; ++k)
+        if (lane + 64 * k < I.w * NR) yd[k] += ws[lane + 64 * k];
+    } else {
+      const T* P = reinterpret_cast<const T*>((uintptr_t)I.data);
+      const A* zb = z + (n + I.src) * NR;
+      ColBatch<T, A, NR, KQ, NT> b0, b1b;
+      for (int c = 0; c < I.w; c += 2 * CB) {
+        b0.template load<false>(P, zb, 0, c, I.w, ld, r1, r2, xo, lq);
+        b1b.template load<false>(P, zb, 0, c + CB, I.w, ld, r1, r2, xo, lq);
+        if (c + 2 * CB > I.w) {                         // uniform over the wavefront
+          b0.mask(c, I.w, lq);
+          b1b.mask(c + CB, I.w, lq);
+        }
+        b0.mul(acc);
+        b1b.mul(acc);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (lr < NR) ybuf[fwd2x_row<T, NT>(t, Mfma<A>::row(j, lq))][lr] = acc[t][j];
+  wave_lds_order();
+  A* yf = &ybuf[0][0];
+#pragma unroll
+  for (int k = 0; k < NR; ++k)                          // 64 NR values, rows past the tiles unused
+    if (lane + 64 * k < NT * 16 * NR) yf[lane + 64 * k] += yd[k];
+}
+
+template <typename T, typename A, typename VT, int NR>
+__global__ __launch_bounds__(256) void k_tr2x(const int32_t* __restrict__ beg,
+                                              const TItem* __restrict__ items, MvLeaves L,
+                                              const A* __restrict__ w, const A* __restrict__ z,
+                                              int64_t n, const int32_t* __restrict__ perm,
+                                              VT* __restrict__ y, int nrhs, int k0, int nv, int S,
+                                              A* __restrict__ ypart, int ldmax) {
+  __shared__ A ybuf[4][kMaxLeaf][NR];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t nwork = L.nleaf * S;
+  const int64_t per = (nwork + kXcds - 1) / kXcds;
+  for (int64_t li = blockIdx.x; li < per * kXcds; li += gridDim.x) {
+    const int64_t q = xcd_item(li, per);
+    if (q >= nwork) continue;                           // uniform over the workgroup
+    const int64_t c = q / S;
+    const int sp = (int)(q - c * S);
+    const int ld = (int)(L.ldpre[c + 1] - L.ldpre[c]);
+    const int m = L.m[c], lo = L.lo[c];
+    const int it0 = beg[c] + 4 * sp + wave, b1 = beg[c + 1];
+    switch ((ld + 15) / 16) {                           // uniform over the workgroup
+      case 1: tr2x_items<T, A, NR, 1>(items, it0, b1, 4 * S, ld, w, z, n, lane, ybuf[wave]); break;
+      case 2: tr2x_items<T, A, NR, 2>(items, it0, b1, 4 * S, ld, w, z, n, lane, ybuf[wave]); break;
+      case 3: tr2x_items<T, A, NR, 3>(items, it0, b1, 4 * S, ld, w, z, n, lane, ybuf[wave]); break;
+      default: tr2x_items<T, A, NR, 4>(items, it0, b1, 4 * S, ld, w, z, n, lane, ybuf[wave]); break;
+    }
+    __syncthreads();
+    A* yp = ypart + q * ldmax * NR;
+    for (int e = threadIdx.x; e < m * NR; e += blockDim.x) {
+      const int row = e / NR, k = e % NR;
+      const A v = ((ybuf[0][row][k] + ybuf[1][row][k]) + ybuf[2][row][k]) + ybuf[3][row][k];
+      if (S > 1)
+        yp[e] = v;
       else if (k < nv)
         y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
     }
@@ -1217,14 +1408,11 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
   A* xt = static_cast<A*>(P.xt);
   MvProfile* pr = P.prof;
   if (pr) HM_HIP(hipEventRecord(pr->ev[0], s));
-  if (NR >= 4 && !transposed) {
-    if constexpr (NR >= 4)
-      k_gather_x<VT, A, NR><<<(unsigned)std::min<int64_t>(P.L.nleaf, 1 << 20), 256, 0, s>>>(
-          x, nrhs, k0, nv, P.perm, P.L, z, xt);
-  } else {
-    k_gather<VT, A><<<grid_for(P.n * NR, 256, 4096), 256, 0, s>>>(x, nrhs, k0, NR, nv, P.perm, P.n,
-                                                                  z);
-  }
+  if constexpr (NR >= 4)
+    k_gather_x<VT, A, NR><<<(unsigned)std::min<int64_t>(P.L.nleaf, 1 << 20), 256, 0, s>>>(
+        x, nrhs, k0, nv, P.perm, P.L, z, xt);
+  else
+    k_gather<VT, A><<<grid_for(P.n * NR, 256, 4096), 256, 0, s>>>(x, nrhs, k0, NR, P.perm, P.n, z);
   HM_LAUNCH_CHECK();
   if (pr) HM_HIP(hipEventRecord(pr->ev[1], s));
   if (!transposed) {
@@ -1259,7 +1447,10 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
   } else {
     if (P.nunits > 0) {
       const unsigned gu = (unsigned)std::min<int64_t>(ceil_div(P.nunits, kXcds) * kXcds, P.grid);
-      k_tr1<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, z, w);
+      if constexpr (NR >= 4)
+        k_tr1x<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, xt, w);
+      else
+        k_tr1<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, z, w);
       HM_LAUNCH_CHECK();
     }
     if (pr) HM_HIP(hipEventRecord(pr->ev[2], s));
@@ -1278,8 +1469,12 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
     const int S = (int)std::max<int64_t>(1, std::min<int64_t>(8, cap / std::max<int64_t>(1, P.L.nleaf)));
     // leaves carry similar work: the grid covers the XCD-ordered index range
     const unsigned gt = (unsigned)std::min<int64_t>(ceil_div(P.L.nleaf * S, kXcds) * kXcds, P.grid);
-    k_tr2<TL, A, VT, NR><<<gt, 256, 0, s>>>(P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs, k0,
-                                            nv, S, static_cast<A*>(P.ypart), P.ldmax);
+    if constexpr (NR >= 4)
+      k_tr2x<TL, A, VT, NR><<<gt, 256, 0, s>>>(P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs,
+                                               k0, nv, S, static_cast<A*>(P.ypart), P.ldmax);
+    else
+      k_tr2<TL, A, VT, NR><<<gt, 256, 0, s>>>(P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs,
+                                              k0, S, static_cast<A*>(P.ypart), P.ldmax);
     HM_LAUNCH_CHECK();
     if (S > 1) {
       k_tr2_sum<A, VT, NR><<<(unsigned)std::min<int64_t>(ceil_div(P.L.nleaf, sum_leaves<NR>()), P.grid), 256, 0, s>>>(
@@ -1312,9 +1507,7 @@ static int pass_width(int left, int cap) {
 
 template <typename TD, typename TL, typename A, typename VT>
 void matvec_impl(const MvPlan& P, const VT* x, VT* y, int nrhs, bool transposed, hipStream_t s) {
-  // the transposed kernels are vector code: 16 columns cost more than twice 8
-  // (N = 81,920, FP32: 549, 607, 697, 1,047 and 2,385 us for 1 to 16 columns)
-  const int cap = transposed ? std::min(P.max_nr_t, 8) : 16;
+  const int cap = transposed ? P.max_nr_t : 16;
   for (int k0 = 0; k0 < nrhs;) {
     const int w = pass_width(nrhs - k0, cap), nv = std::min(w, nrhs - k0);
     switch (w) {

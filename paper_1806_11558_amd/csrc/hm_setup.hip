@@ -2184,8 +2184,8 @@ __global__ void k_unit_emit(const Run* __restrict__ runs, int nruns, MvLeaves L,
       const Run R = runs[(int64_t)r * L.nleaf + c];
       for (int a = 0; a < R.w; a += ucols)
         *u++ = Unit{R.data + (uint64_t)(a * ld * (r == 0 ? esize : lsize)), R.col0 + a,
-                    min(ucols, R.w - a), L.lo[c], (uint16_t)ld, (uint16_t)L.m[c],
-                    (uint16_t)(r == 0), 0};
+                    min(ucols, R.w - a), L.lo[c], (uint32_t)L.ldpre[c], (uint8_t)ld,
+                    (uint8_t)L.m[c], (uint8_t)(r == 0), 0};
     }
   }
 }
@@ -2571,10 +2571,10 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   }
   {
     Temps tt{s, {}};
-    const int64_t nb_all = in.nd + out.nu1;
+    const int64_t nb_all = in.nd + out.nux;
     int64_t* cnt = tt.get<int64_t>(nb_all);
     int64_t* off = tt.get<int64_t>(nb_all + 1);
-    k_titem_counts<<<grid_for(nb_all, 256), 256, 0, s>>>(in.dns, in.nd, out.meta1, out.nu1,
+    k_titem_counts<<<grid_for(nb_all, 256), 256, 0, s>>>(in.dns, in.nd, out.metax, out.nux,
                                                          in.cl_leaves, cnt);
     HM_LAUNCH_CHECK();
     out.ntitems = scan_total(cnt, off, nb_all, tmp, s);
@@ -2582,8 +2582,8 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
     TItem* raw = tt.get<TItem>(out.ntitems);
     uint64_t* key = tt.get<uint64_t>(out.ntitems);
     int32_t* idx = tt.get<int32_t>(out.ntitems);
-    k_titem_expand<<<grid_for(nb_all, 64), 64, 0, s>>>(in.dns, in.nd, out.nu1, in.cl, L, off, invD,
-                                                       oD, gcolD, out.meta1, lsize, raw, key, idx);
+    k_titem_expand<<<grid_for(nb_all, 64), 64, 0, s>>>(in.dns, in.nd, out.nux, in.cl, L, off, invD,
+                                                       oD, gcolD, out.metax, lsize, raw, key, idx);
     HM_LAUNCH_CHECK();
     radix_sort_u64_i32(key, idx, out.ntitems, bits_for(nleaf), s);
     out.titems = static_cast<TItem*>(alloc((out.ntitems + 1) * sizeof(TItem)));
