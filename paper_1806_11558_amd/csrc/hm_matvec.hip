@@ -204,15 +204,24 @@ __device__ inline void fwd1_uniform(const LrMeta& M, const MvLeaves& L, const A*
   for (int q = 0; q < P; ++q) fwd1_flush<A, NR>(acc[q], g, R, q * C, C, r, lane, tl);
 }
 
+// Wavefronts per SIMD: all eight (64 registers), but for the 16 accumulators
+// of two columns of FP16 slices, which take up to 128.
 template <typename T, typename A, int NR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_fwd1(const LrMeta* __restrict__ meta, int64_t nl,
-                                              MvLeaves L, A* __restrict__ z, int64_t n,
-                                              const float* __restrict__ su) {
+constexpr int fwd1_waves() {
+  return NR == 2 && sizeof(T) == 2 ? 4 : 8;
+}
+
+template <typename T, typename A, int NR>
+__global__ __launch_bounds__(256, (fwd1_waves<T, A, NR>())) void k_fwd1(
+    const LrMeta* __restrict__ meta, int64_t nl, MvLeaves L, A* __restrict__ z, int64_t n,
+    const float* __restrict__ su) {
   constexpr int G = Gran<T>::G;
-  // loads per lane of the one-pass form; the phase-1 units of FP16 slices
-  // are sized for eight, of FP32 and FP64 ones for four
   static_assert(NR <= 2, "more right-hand sides go to the matrix cores");
-  constexpr int PMAX = (NR == 1 && sizeof(T) == 2) ? 8 : 4;
+  // loads per lane of the one-pass form: the phase-1 units of FP16 slices are
+  // sized for eight, of FP32 and FP64 ones for four; a unit with more passes
+  // than this would reduce every slice on its own (FP16, 2 columns, N =
+  // 81,920, leaf 64: phase 1 394 us with four, 82 with eight)
+  constexpr int PMAX = sizeof(T) == 2 ? 8 : 4;
   const int lane = threadIdx.x & 63;
   // wave-uniform block index: descriptors and leaf data come in by scalar loads
   const int64_t wid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -634,7 +643,7 @@ __device__ inline void fwd1x_pass(const LrMeta& M, const MvLeaves& L, const A* _
 // result tile.  In double and for 16 columns the lanes of one call already
 // lie side by side in memory; with fewer float columns a call per item would
 // write 16- or 32-byte pieces, so the items are exchanged first and a call
-// covers 16 / NR rows of every quad.
+// covers 16 / NR of the four rows of every quad.
 template <typename A, int NR, typename Put>
 __device__ inline void tile_out(const typename Mfma<A>::V& acc, int lr, int lq, const Put& put) {
   if constexpr (sizeof(A) == 8 || NR == 16) {
@@ -642,7 +651,7 @@ __device__ inline void tile_out(const typename Mfma<A>::V& acc, int lr, int lq, 
     for (int j = 0; j < 4; ++j)
       if (lr < NR) put(Mfma<A>::row(j, lq), lr, acc[j]);
   } else {
-    constexpr int GR = 16 / NR;                  // rows per call
+    constexpr int GR = NR < 4 ? 4 : 16 / NR;     // rows per call
     const int g = lr / NR, k = lr & (NR - 1);
 #pragma unroll
     for (int h = 0; h < 4; h += GR) {
@@ -652,7 +661,7 @@ __device__ inline void tile_out(const typename Mfma<A>::V& acc, int lr, int lq, 
         const A o = __shfl(acc[h + q], lq * 16 + k, 64);
         v = g == q ? o : v;
       }
-      put(4 * lq + h + g, k, v);
+      if (g < GR) put(4 * lq + h + g, k, v);
     }
   }
 }
@@ -991,13 +1000,14 @@ __global__ __launch_bounds__(256) void k_tr1(const Unit* __restrict__ units, int
   }
 }
 
-// The same on the matrix cores for 4 to 16 right-hand sides: the columns of a
-// unit, 64 at a time per wavefront, are the terms of phase 1 (one leaf, the
-// panel in place of the V slice).  On the vector units every column cost its
-// own reduction over the rows.  Whole products at N = 32,000, leaf 64: FP64
-// 4 columns 1,107 -> 447 us, 8 2,222 -> 509, 16 5,196 -> 686; FP32 4 columns
-// 288 -> 247, 16 1,055 -> 395 (leaf 32, 4 columns: 235 and 238).  Bound by HBM and by w itself, which is as many
-// bytes as 2/5 of an FP32 panel of 40 rows at 16 columns.
+// The same on the matrix cores, for 4 to 16 right-hand sides and for small
+// trees (see kTrMfmaLeaves): the columns of a unit, 64 at a time per
+// wavefront, are the terms of phase 1 (one leaf, the panel in place of the V
+// slice).  On the vector units every column cost its own reduction over the
+// rows.  Whole products at N = 32,000, leaf 64: FP64 4 columns 1,107 -> 447 us,
+// 8 2,222 -> 509, 16 5,196 -> 686; FP32 4 columns 288 -> 247, 16 1,055 -> 395
+// (leaf 32, 4 columns: 235 and 238).  Bound by HBM and by w itself, which is
+// as many bytes as 2/5 of an FP32 panel of 40 rows at 16 columns.
 template <typename T, typename A, int NR>
 __device__ inline void tr1x_unit(const Unit& U, const A* __restrict__ xt, A* __restrict__ w,
                                  int wave, int lane) {
@@ -1199,48 +1209,32 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
         }
       } else {
         const T* S = reinterpret_cast<const T*>((uintptr_t)I.data);
-        if constexpr (sizeof(T) < 8) {
-          for (int j0 = 0; j0 < I.w; j0 += C) {
-            const int j = j0 + cg;
-            if (act && j < I.w) {
-              typename Gran<T>::E s[G];
-              Gran<T>::load(S + (int64_t)j * ld + g * G, s);
-              A zz[NR];
-              load_row<A, NR>(z + (n + I.src + j) * NR, zz);
+        // UNR column groups at a time with unconditional loads (a lane without
+        // a column reads the slice's last one and adds zero), so all their
+        // loads are in flight together: one column at N = 32,000, leaf 32 and
+        // 64, FP32 183 -> 174 and 190 -> 185 us, FP16 129 -> 121 and 150 -> 142
+        // against a column group at a time
+        constexpr int UNR = 4;
+        const int ngrp = (I.w + C - 1) / C;
+        for (int q0 = 0; q0 < ngrp; q0 += UNR) {
+          typename Gran<T>::E s[UNR][G];
+          A zz[UNR][NR];
+          bool ok[UNR];
 #pragma unroll
-              for (int e = 0; e < G; ++e)
-#pragma unroll
-                for (int k = 0; k < NR; ++k) acc[e][k] += (A)s[e] * zz[k];
-            }
+          for (int u = 0; u < UNR; ++u) {
+            const int j = (q0 + u) * C + cg;
+            ok[u] = act && q0 + u < ngrp && j < I.w;
+            const int jj = ok[u] ? j : I.w - 1;
+            Gran<T>::load(S + (int64_t)jj * ld + g * G, s[u]);
+            load_row<A, NR>(z + (n + I.src + jj) * NR, zz[u]);
           }
-        } else {
-          // FP64 slices: UNR column groups at a time with unconditional loads
-          // (a lane without a column reads the slice's last one and adds zero),
-          // so all their loads are in flight together (16% faster; slower for
-          // FP32 and FP16 slices, which keep the loop above)
-          constexpr int UNR = NR <= 2 ? 4 : 1;
-          const int ngrp = (I.w + C - 1) / C;
-          for (int q0 = 0; q0 < ngrp; q0 += UNR) {
-            typename Gran<T>::E s[UNR][G];
-            A zz[UNR][NR];
-            bool ok[UNR];
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-              const int j = (q0 + u) * C + cg;
-              ok[u] = act && q0 + u < ngrp && j < I.w;
-              const int jj = ok[u] ? j : I.w - 1;
-              Gran<T>::load(S + (int64_t)jj * ld + g * G, s[u]);
-              load_row<A, NR>(z + (n + I.src + jj) * NR, zz[u]);
-            }
+          for (int u = 0; u < UNR; ++u)
 #pragma unroll
-            for (int u = 0; u < UNR; ++u)
+            for (int e = 0; e < G; ++e)
 #pragma unroll
-              for (int e = 0; e < G; ++e) {
-                const A sv = ok[u] ? (A)s[u][e] : (A)0;
-#pragma unroll
-                for (int k = 0; k < NR; ++k) acc[e][k] += sv * zz[u][k];
-              }
-          }
+              for (int k = 0; k < NR; ++k)
+                acc[e][k] += (A)s[u][e] * (ok[u] ? zz[u][k] : (A)0);
         }
       }
     }
@@ -1283,7 +1277,7 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
   }
 }
 
-// The same on the matrix cores for 4 to 16 right-hand sides: V items are
+// The same on the matrix cores, where phase 1 runs there: V items are
 // column batches as in the forward phase 2, with consecutive z rows; the w
 // entries of dense items, NR values per row of the leaf, are read as one
 // contiguous run, value e by lane e mod 64.
@@ -1400,6 +1394,18 @@ __global__ __launch_bounds__(256) void k_tr2_sum(MvLeaves L, int S, const A* __r
 }
 
 // ------------------------------------------------------------------ host side
+// Transposed products of one or two columns run on the matrix cores up to this
+// many leaves (64 for one column in single precision), on the vector units above.  Small products wait for loads, and
+// the matrix kernels have all the loads of 64 columns in flight; large ones are
+// bound by HBM, where the vector kernels use fewer, longer wavefronts.  One and
+// two columns, vector -> matrix: 64 leaves of 53 rows, FP64 64 -> 41 and 71 ->
+// 43 us, FP32 41 -> 29 and 50 -> 33; 128 leaves of 45 rows, FP64 57 -> 43 and
+// 64 -> 47, FP32 33 -> 32 and 41 -> 35, of 62 rows, FP32 40 -> 43 and 55 -> 47;
+// 256 leaves of 45 rows, FP64 105 -> 112 and 120 -> 126, FP32 65 -> 67 and
+// 70 -> 69; N = 81,920, leaf 64, FP32 538 -> 614 and 598 -> 665.
+template <typename A, int NR>
+constexpr int64_t kTrMfmaLeaves = sizeof(A) == 4 && NR == 1 ? 64 : 128;
+
 template <typename TD, typename TL, typename A, typename VT, int NR>
 static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int nv,
                      bool transposed, hipStream_t s) {
@@ -1408,7 +1414,8 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
   A* xt = static_cast<A*>(P.xt);
   MvProfile* pr = P.prof;
   if (pr) HM_HIP(hipEventRecord(pr->ev[0], s));
-  if constexpr (NR >= 4)
+  const bool tmx = NR >= 4 || P.L.nleaf <= kTrMfmaLeaves<A, NR>;   // transposed, on the matrix cores
+  if (transposed ? tmx : NR >= 4)
     k_gather_x<VT, A, NR><<<(unsigned)std::min<int64_t>(P.L.nleaf, 1 << 20), 256, 0, s>>>(
         x, nrhs, k0, nv, P.perm, P.L, z, xt);
   else
@@ -1447,9 +1454,9 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
   } else {
     if (P.nunits > 0) {
       const unsigned gu = (unsigned)std::min<int64_t>(ceil_div(P.nunits, kXcds) * kXcds, P.grid);
-      if constexpr (NR >= 4)
+      if (tmx)
         k_tr1x<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, xt, w);
-      else
+      else if constexpr (NR < 4)
         k_tr1<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, z, w);
       HM_LAUNCH_CHECK();
     }
@@ -1469,10 +1476,10 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
     const int S = (int)std::max<int64_t>(1, std::min<int64_t>(8, cap / std::max<int64_t>(1, P.L.nleaf)));
     // leaves carry similar work: the grid covers the XCD-ordered index range
     const unsigned gt = (unsigned)std::min<int64_t>(ceil_div(P.L.nleaf * S, kXcds) * kXcds, P.grid);
-    if constexpr (NR >= 4)
+    if (tmx)
       k_tr2x<TL, A, VT, NR><<<gt, 256, 0, s>>>(P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs,
                                                k0, nv, S, static_cast<A*>(P.ypart), P.ldmax);
-    else
+    else if constexpr (NR < 4)
       k_tr2<TL, A, VT, NR><<<gt, 256, 0, s>>>(P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs,
                                               k0, S, static_cast<A*>(P.ypart), P.ldmax);
     HM_LAUNCH_CHECK();
