@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "hm_internal.h"
+#include "hm_wave.h"
 
 namespace hm {
 
@@ -881,16 +882,10 @@ __global__ __launch_bounds__(256) void k_fwd2x(const Unit* __restrict__ units, i
 // reads them from the wavefront's own LDS area (a shift-down tree over the
 // R lanes cost about four times the instructions per column).  Only the
 // wavefront itself reads what it wrote: program order of its LDS
-// instructions is enough, and wave_lds_order keeps the compiler from
+// instructions is enough, and wave_order keeps the compiler from
 // moving LDS accesses across the exchange.
 template <int NR>
 constexpr int tr1_unr() { return NR <= 2 ? 4 : 1; }   // column groups per wavefront in flight
-
-__device__ inline void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 template <typename T, typename A, int NR, int G>
 __device__ inline void tr1_run(const Unit& U, int ld, int R, int C, int cg, int g,
@@ -929,12 +924,12 @@ __device__ inline void tr1_run(const Unit& U, int ld, int R, int C, int cg, int 
         for (int k = 0; k < NR; ++k) ps[u][k] += x * xg[e][k];
       }
     }
-    wave_lds_order();                                   // the last step's reads are done
+    wave_order();                                   // the last step's reads are done
 #pragma unroll
     for (int u = 0; u < UNR; ++u)
 #pragma unroll
       for (int k = 0; k < NR; ++k) red[(u * 64 + lane) * NR + k] = ps[u][k];
-    wave_lds_order();
+    wave_order();
     for (int t = lane; t < ncol; t += 64) {
       int u = ur, c = cr;
       if (t >= 64) {
@@ -1328,7 +1323,7 @@ __device__ inline void tr2x_items(const TItem* __restrict__ items, int it0, int 
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (lr < NR) ybuf[fwd2x_row<T, NT>(t, Mfma<A>::row(j, lq))][lr] = acc[t][j];
-  wave_lds_order();
+  wave_order();
   A* yf = &ybuf[0][0];
 #pragma unroll
   for (int k = 0; k < NR; ++k)                          // 64 NR values, rows past the tiles unused

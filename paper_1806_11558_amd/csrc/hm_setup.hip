@@ -195,88 +195,96 @@ __device__ inline T op_entry(const Tgt<T, kOpGalerkin>& t, int i, const Src<T>& 
 // ---- singular Galerkin entries (Sec. 4.1: higher-order quadrature and the
 // Duffy trick), in double.
 // int_T dsigma_y / |x - y| for the flat triangle T with vertices v[0..2]
-// and any point x: T is the signed sum of the triangles (x', a, b) over its
-// edges, x' the projection of x onto the plane of T at signed height d; in
-// polar coordinates about x' every edge gives, between its end points,
-// h asinh(l / c) + |d| atan(|d| l / (h R)) - |d| atan(l / h)
-// (h distance of x' to the edge line, l coordinate along it, c^2 = h^2 + d^2,
-// R distance from x to the end point).  Evaluated here in an equivalent
-// form with one logarithm and two arc tangents per edge:
+// and any point x: the sum over the edges of
+//   h (asinh(l_b / c) - asinh(l_a / c)),
+// signed by the side of the edge on which the projection x' of x lies, minus
+// |d| Omega (h distance of x' to the edge line, l coordinate along it, d
+// height of x over the plane of T, c^2 = h^2 + d^2, Omega the solid angle of
+// T seen from x).  With R the distance from x to a vertex,
 //   asinh(l_b / c) - asinh(l_a / c) = log((l_b + R_b) / (l_a + R_a))  (l_a >= 0),
 //   = log((|l_a| + R_a) / (|l_b| + R_b)) (l_b <= 0), and
 //   log((l_b + R_b)(|l_a| + R_a) / c^2) when the edge spans the foot point
-//   (R^2 = l^2 + c^2; no cancellation in any case);
-//   atan(|d| l / (h R)) - atan(l / h) = atan(z),
-//   z = -l h (l^2 + h^2) / ((R + |d|)(h^2 R + |d| l^2))
-//   (the two arguments have a non-negative product, and R - |d| is written
-//   as (l^2 + h^2) / (R + |d|)).
-// What depends only on T -- its unit normal, the unit edge tangents t_k,
-// the in-plane edge normals m_k = t_k x n and the edge lengths -- is set up
-// once per pair.
+//   (R^2 = l^2 + c^2; no cancellation in any case),
+// and Omega comes from its half-angle tangent (van Oosterom and Strackee,
+// IEEE Trans. Biomed. Eng. 30, 1983), the triple product as |d| times twice
+// the area.  One arc tangent per point in place of two per edge (the arc
+// tangents of the polar form, atan(|d| l / (h R)) - atan(l / h) between the
+// end points) and one logarithm per edge for all three cases.
+//
+// The outer points are x = p + s a + s t b, so d and the h and l_a of every
+// edge are affine in (s, s t); their coefficients are what is set up per pair
+// (25 values; the triangle with its normals and tangents took 43).  Vertices
+// enter as differences to p: the rounding scales with the triangles, not with
+// their distance from the origin.  Against extended precision the entries are
+// off by 3e-16 on average wherever the pair lies, in the form above by 2e-16
+// at the origin and 1e-15 to 1e-14 at a hundred edge lengths from it.
+struct Aff {
+  double c, s, t;
+  __device__ inline double at(double u, double ut) const { return c - u * s - ut * t; }
+};
 struct TriJ {
-  double v[3][3], n[3], t[3][3], m[3][3], le[3];
+  Aff d, h[3], l[3];
+  double le[3], area2, jac;              // jac: |a x b|
 };
 
-__device__ inline void tri_setup(const double v[3][3], TriJ& J) {
-  double e1[3], e2[3];
+__device__ inline double dot3(const double a[3], const double b[3]) {
+  return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+}
+__device__ inline void sub3(const double a[3], const double b[3], double o[3]) {
+  for (int c = 0; c < 3; ++c) o[c] = a[c] - b[c];
+}
+__device__ inline void cross3(const double a[3], const double b[3], double o[3]) {
+  o[0] = a[1] * b[2] - a[2] * b[1];
+  o[1] = a[2] * b[0] - a[0] * b[2];
+  o[2] = a[0] * b[1] - a[1] * b[0];
+}
+
+// Inner triangle v, outer points p + s a + s t b.
+__device__ inline void tri_setup(const double v[3][3], const double p[3], const double a[3],
+                                 const double b[3], TriJ& J) {
+  double e[3][3], n[3], r[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) sub3(v[(k + 1) % 3], v[k], e[k]);
+  cross3(e[0], e[1], n);
+  J.area2 = sqrt(dot3(n, n));
+  for (int c = 0; c < 3; ++c) n[c] /= J.area2;
+  sub3(v[0], p, r);
+  J.d = Aff{dot3(r, n), dot3(a, n), dot3(b, n)};
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
-    e1[k] = v[1][k] - v[0][k];
-    e2[k] = v[2][k] - v[0][k];
-    for (int c = 0; c < 3; ++c) J.v[k][c] = v[k][c];
-  }
-  double n[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
-                 e1[0] * e2[1] - e1[1] * e2[0]};
-  const double nn = sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-  for (int c = 0; c < 3; ++c) J.n[c] = n[c] / nn;
-  for (int k = 0; k < 3; ++k) {
-    const double* a = v[k];
-    const double* b = v[(k + 1) % 3];
-    double e[3] = {b[0] - a[0], b[1] - a[1], b[2] - a[2]};
-    const double le = sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]);
-    J.le[k] = le;
-    for (int c = 0; c < 3; ++c) J.t[k][c] = e[c] / le;
-    J.m[k][0] = J.t[k][1] * J.n[2] - J.t[k][2] * J.n[1];
-    J.m[k][1] = J.t[k][2] * J.n[0] - J.t[k][0] * J.n[2];
-    J.m[k][2] = J.t[k][0] * J.n[1] - J.t[k][1] * J.n[0];
+    double m[3];
+    J.le[k] = sqrt(dot3(e[k], e[k]));
+    for (int c = 0; c < 3; ++c) e[k][c] /= J.le[k];
+    cross3(e[k], n, m);
+    sub3(v[k], p, r);
+    J.h[k] = Aff{dot3(r, m), dot3(a, m), dot3(b, m)};
+    J.l[k] = Aff{dot3(r, e[k]), dot3(a, e[k]), dot3(b, e[k])};
   }
 }
 
-__device__ inline double tri_inner_integral(const double x[3], const TriJ& J) {
-  const double d = (x[0] - J.v[0][0]) * J.n[0] + (x[1] - J.v[0][1]) * J.n[1] +
-                   (x[2] - J.v[0][2]) * J.n[2];
-  const double ad = fabs(d);
-  double R[3];
+__device__ inline double tri_inner_integral(double u, double ut, const TriJ& J) {
+  const double ad = fabs(J.d.at(u, ut));
+  double hs[3], la[3], c2[3], R[3];
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const double dx = x[0] - J.v[k][0], dy = x[1] - J.v[k][1], dz = x[2] - J.v[k][2];
-    R[k] = sqrt(dx * dx + dy * dy + dz * dz);
+    hs[k] = J.h[k].at(u, ut);            // positive: x' on the inner side of the edge
+    la[k] = J.l[k].at(u, ut);
+    c2[k] = hs[k] * hs[k] + ad * ad;
+    R[k] = sqrt(la[k] * la[k] + c2[k]);
   }
-  double total = 0.0;
+  double total = 0.0, den = R[0] * R[1] * R[2];
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const double ax = J.v[k][0] - x[0], ay = J.v[k][1] - x[1], az = J.v[k][2] - x[2];
-    // signed distance of x' to the edge line (positive: x' on the inner side)
-    const double hs = ax * J.m[k][0] + ay * J.m[k][1] + az * J.m[k][2];
-    const double h = fabs(hs);
-    if (!(h > 0.0)) continue;                            // x' on the edge line
-    const double la = ax * J.t[k][0] + ay * J.t[k][1] + az * J.t[k][2];
-    const double lb = la + J.le[k];
-    const double Ra = R[k], Rb = R[(k + 1) % 3];
-    double lg;
-    if (la >= 0.0)
-      lg = log((lb + Rb) / (la + Ra));
-    else if (lb <= 0.0)
-      lg = log((Ra - la) / (Rb - lb));
-    else
-      lg = log((lb + Rb) * (Ra - la) / (h * h + d * d));
-    double val = h * lg;
-    if (ad > 0.0) {
-      const double h2 = h * h;
-      const double za = -la * h * (la * la + h2) / ((Ra + ad) * (h2 * Ra + ad * la * la));
-      const double zb = -lb * h * (lb * lb + h2) / ((Rb + ad) * (h2 * Rb + ad * lb * lb));
-      val += ad * (atan(zb) - atan(za));
-    }
-    total += hs > 0.0 ? val : -val;
+    const double Ra = R[k], Rb = R[(k + 1) % 3], lb = la[k] + J.le[k];
+    const bool after = la[k] >= 0.0, before = lb <= 0.0;
+    const double pb = lb + Rb, pa = Ra - la[k];
+    const double ln = after ? pb : (before ? pa : pb * pa);
+    const double ld = after ? la[k] + Ra : (before ? Rb - lb : c2[k]);
+    // x' on the edge line (also x on the edge, where ld is 0): no contribution
+    if (fabs(hs[k]) > 0.0) total += hs[k] * log(ln / ld);
+    den += (la[k] * lb + c2[k]) * R[(k + 2) % 3];        // (r_a . r_b) R_c
   }
-  return total;
+  return total - 2.0 * ad * atan2(ad * J.area2, den);
 }
 
 template <typename T>
@@ -291,36 +299,34 @@ __device__ inline void load_tri(const Geom<T>& g, int i, double v[3][3]) {
 // x = v0 + s (v1 - v0) + s t (v2 - v1), weight w_s w_t s |(v1 - v0) x (v2 - v1)|,
 // the inner integral over T_j in closed form.
 template <typename T>
-__device__ inline double galerkin_singular_part(const Geom<T>& g, const GaussRule& R, int i, int j,
-                                                int k0, int step) {
-  double ti[3][3], tj[3][3];
+__device__ inline void singular_setup(const Geom<T>& g, int i, int j, TriJ& J) {
+  double ti[3][3], tj[3][3], a[3], b[3], cr[3];
   load_tri(g, i, ti);
   load_tri(g, j, tj);
-  TriJ J;
-  tri_setup(tj, J);
-  double a[3], b[3];
-  for (int c = 0; c < 3; ++c) {
-    a[c] = ti[1][c] - ti[0][c];
-    b[c] = ti[2][c] - ti[1][c];
-  }
-  const double cx = a[1] * b[2] - a[2] * b[1], cy = a[2] * b[0] - a[0] * b[2],
-               cz = a[0] * b[1] - a[1] * b[0];
-  const double jac = sqrt(cx * cx + cy * cy + cz * cz);
+  sub3(ti[1], ti[0], a);
+  sub3(ti[2], ti[1], b);
+  tri_setup(tj, ti[0], a, b, J);
+  cross3(a, b, cr);
+  J.jac = sqrt(dot3(cr, cr));
+}
+// Outer points k0, k0 + step, ...
+__device__ inline double singular_points(const GaussRule& R, const TriJ& J, int k0, int step) {
   double acc = 0.0;
+#pragma unroll 1
   for (int k = k0; k < kGalQ * kGalQ; k += step) {
+    asm volatile("" ::: "memory");       // J in LDS: read per point, not held in registers
     const int ks = k / kGalQ, kt = k % kGalQ;
-    const double s = R.x[ks], t = R.x[kt];
-    double x[3];
-    for (int c = 0; c < 3; ++c) x[c] = ti[0][c] + s * a[c] + s * t * b[c];
-    acc += R.w[ks] * R.w[kt] * s * jac * tri_inner_integral(x, J);
+    const double s = R.x[ks];
+    acc += R.w[ks] * R.w[kt] * s * tri_inner_integral(s, s * R.x[kt], J);
   }
-  return acc * 0.079577471545947667884441881686257181;   // 1/(4 pi)
+  return acc * J.jac * 0.079577471545947667884441881686257181;   // 1/(4 pi)
 }
 template <typename T>
 __device__ inline double galerkin_singular(const Geom<T>& g, const GaussRule& R, int i, int j) {
-  return wsum(galerkin_singular_part(g, R, i, j, threadIdx.x & 63, 64));
+  TriJ J;
+  singular_setup(g, i, j, J);
+  return wsum(singular_points(R, J, threadIdx.x & 63, 64));
 }
-
 
 // Do triangles i and j share a vertex (or coincide)?
 template <typename T>
@@ -457,10 +463,14 @@ __global__ __launch_bounds__(256) void k_near(Geom<T> g, const int32_t* __restri
 }
 
 // Singular Galerkin entries of the near field (pairs that share a vertex,
-// left at 0 by k_near): one workgroup per slice as in k_near.  Every
-// wavefront looks at 64 consecutive entries at a time and evaluates the
-// touching ones among them one after the other, all its lanes together
-// (the trip count of its loop is the same for all lanes).
+// left at 0 by k_near): one workgroup per slice as in k_near.  The touching
+// pairs of up to kSingChunk entries are listed in LDS, then each row of 16
+// lanes takes one pair, nine of its 144 outer points per lane.  Bound by
+// FP64 arithmetic.  N = 81,920 (1.07 million pairs): 10.8 ms with a wavefront
+// per pair, whose third round of points fills 16 of 64 lanes and which repeats
+// the set-up of the inner triangle in 64 lanes, 5.0 ms with a row.
+constexpr int kSingChunk = 4096;
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_near_singular(Geom<T> g, GaussRule R,
                                                        const int32_t* __restrict__ sidx,
@@ -471,6 +481,9 @@ __global__ __launch_bounds__(256) void k_near_singular(Geom<T> g, GaussRule R,
                                                        const int64_t* __restrict__ offI,
                                                        T* __restrict__ D) {
   __shared__ int32_t vr[3][kMaxLeaf], vc[3][kMaxLeaf];
+  __shared__ uint16_t pair[kSingChunk];
+  __shared__ int npair;
+  __shared__ TriJ tri[16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int64_t p = blockIdx.x; p < np; p += gridDim.x) {
     const int32_t u = sidx[p];
@@ -486,30 +499,47 @@ __global__ __launch_bounds__(256) void k_near_singular(Geom<T> g, GaussRule R,
       for (int i = threadIdx.x; i < m; i += blockDim.x)
         for (int k = 0; k < 3; ++k) vr[k][i] = g.vid[(int64_t)k * g.n + lo + i];
     }
-    __syncthreads();
-    for (int e0 = wave * 64; e0 < ld * n; e0 += blockDim.x) {
-      const int e = e0 + lane;
-      const int i = e % ld, j = e / ld;
-      bool t = false;
-      if (e < ld * n && i < m) {
-        if (staged) {
-          t = lo + i == sig.x + j;
-          for (int a = 0; a < 3; ++a)
-            for (int c = 0; c < 3; ++c) t = t || vr[a][i] == vc[c][j];
-        } else {
-          t = touching(g, lo + i, sig.x + j);
+    for (int c0 = 0; c0 < ld * n; c0 += kSingChunk) {
+      if (threadIdx.x == 0) npair = 0;
+      __syncthreads();
+      const int c1 = min(c0 + kSingChunk, ld * n);
+      for (int e0 = c0 + wave * 64; e0 < c1; e0 += blockDim.x) {
+        const int e = e0 + lane;
+        const int i = e % ld, j = e / ld;
+        bool t = false;
+        if (e < c1 && i < m) {
+          if (staged) {
+            t = lo + i == sig.x + j;
+            for (int a = 0; a < 3; ++a)
+              for (int c = 0; c < 3; ++c) t = t || vr[a][i] == vc[c][j];
+          } else {
+            t = touching(g, lo + i, sig.x + j);
+          }
         }
+        const unsigned long long mask = __ballot(t);
+        int at = 0;
+        if (lane == 0 && mask) at = atomicAdd(&npair, __popcll(mask));
+        at = __shfl(at, 0, 64) + __popcll(mask & ((1ull << lane) - 1));
+        if (t) pair[at] = (uint16_t)(e - c0);
       }
-      unsigned long long mask = __ballot(t);
-      while (mask) {
-        const int l = __ffsll(mask) - 1;
-        mask &= mask - 1;
-        const int el = e0 + l;
-        const double v = galerkin_singular(g, R, lo + el % ld, sig.x + el / ld);
-        if (lane == 0) dst[el] = (T)v;
+      __syncthreads();
+      const int np16 = npair;
+      for (int q0 = wave * 4; q0 < np16; q0 += 16) {       // uniform over the wavefront
+        const int q = q0 + lane / 16;
+        const int e = c0 + pair[min(q, np16 - 1)];
+        TriJ& J = tri[threadIdx.x / 16];
+        {
+          TriJ Jr;                                         // the same in all lanes of a row
+          singular_setup(g, lo + e % ld, sig.x + e / ld, Jr);
+          wave_order();                                // after the last pair's reads
+          if ((lane & 15) == 0) J = Jr;
+          wave_order();
+        }
+        const double v = rowsum(singular_points(R, J, lane & 15, 16));
+        if (q < np16 && (lane & 15) == 0) dst[e] = (T)v;
       }
+      __syncthreads();                                  // before the list and the slice are replaced
     }
-    __syncthreads();                                  // before the next slice is staged
   }
 }
 

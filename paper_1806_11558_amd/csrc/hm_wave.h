@@ -34,16 +34,32 @@ __device__ inline double rdl_v(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Sum over the wavefront, uniform result, fixed order.
+// Sum over each row of 16 lanes, in every lane of the row, fixed order.
 template <typename A>
-__device__ inline A wsum(A v) {
+__device__ inline A rowsum(A v) {
   v += dpp_v<0xB1, 0xF>(v);    // quad_perm [1,0,3,2]
   v += dpp_v<0x4E, 0xF>(v);    // quad_perm [2,3,0,1]
   v += dpp_v<0x141, 0xF>(v);   // row_half_mirror
   v += dpp_v<0x140, 0xF>(v);   // row_mirror
+  return v;
+}
+
+// Sum over the wavefront, uniform result, fixed order.
+template <typename A>
+__device__ inline A wsum(A v) {
+  v = rowsum(v);
   v += dpp_v<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
   v += dpp_v<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
   return rdl_v(v, 63);
 }
 
+// Orders a wavefront's own memory accesses: what its lanes wrote before, all
+// of them read after (no instruction: a wavefront's accesses go in order).
+__device__ inline void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace hm
+
