@@ -218,6 +218,9 @@ struct MvPlan {
   MvProfile* prof;          // null unless profiling
 };
 
+// XCDs of the device, each with its own L2; workgroup w runs on XCD w mod 8.
+constexpr int kXcds = 8;
+
 // Binning of the batched ACA: blocks fall into size bins by max(m, n) (upper
 // edges kAcaBinEdge), and every bin is run by one kernel class: 0 one
 // 1,024-thread workgroup per block, 1 one 256-thread workgroup, 2..4 one

@@ -111,7 +111,6 @@ __device__ inline A seg_sum(A v, int g, int R) {
 // range of leaves, so neighbouring leaves, which
 // gather mostly the same x and t values, share one L2.  A bijection of
 // [0, 8 per) onto itself; items >= the count are skipped.
-constexpr int kXcds = 8;
 __device__ inline int64_t xcd_item(int64_t li, int64_t per) {
   return (li % kXcds) * per + li / kXcds;
 }

@@ -32,14 +32,18 @@ struct Src {
 
 // base[k] at a byte offset of 32 bits from a wavefront-uniform base: the
 // load then takes the base in scalar registers and one vector offset, with
-// no 64-bit address arithmetic per load
+// no 64-bit address arithmetic per load.  The pointer is cast to the global
+// address space: one that was stored as an integer (a block's slot) would
+// otherwise be read by flat loads, which have no such form and also wait for
+// the LDS.
+#define HM_GLOBAL __attribute__((address_space(1)))
 template <typename T>
 __device__ inline T ld_at(const T* base, uint32_t byte_off) {
-  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte_off);
+  return *(const HM_GLOBAL T*)((const HM_GLOBAL char*)base + byte_off);
 }
 template <typename T>
 __device__ inline void st_at(T* base, uint32_t byte_off, T v) {
-  *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off) = v;
+  *(HM_GLOBAL T*)((HM_GLOBAL char*)base + byte_off) = v;
 }
 
 template <typename T>
@@ -557,46 +561,69 @@ __device__ inline double uni(double v) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+template <typename T>
+__device__ inline T* uni_ptr(uint64_t p) {
+  const unsigned lo = (unsigned)uni((int)(unsigned)p), hi = (unsigned)uni((int)(unsigned)(p >> 32));
+  return reinterpret_cast<T*>((uintptr_t)(((uint64_t)hi << 32) | lo));
+}
+
 // Pivot search: key = bit pattern of |value| (monotone for non-negative
-// floats), larger key wins, ties go to the smaller index (stored as ~index,
-// larger wins).  {0, 0} is the "no candidate" sentinel and loses to every
-// real candidate, including a zero value.
-struct Piv {
-  unsigned long long k;
-  unsigned ni;
-};
-__device__ inline unsigned long long key_bits(float a) { return (unsigned)__float_as_int(a); }
+// floats, as wide as the value), larger key wins, ties go to the smaller index
+// (stored as ~index, larger wins).  {0, 0} is the "no candidate" sentinel and
+// loses to every real candidate, including a zero value.
+__device__ inline unsigned key_bits(float a) { return (unsigned)__float_as_int(a); }
 __device__ inline unsigned long long key_bits(double a) {
   return (unsigned long long)__double_as_longlong(a);
 }
-__device__ inline void piv_merge(Piv& a, unsigned long long k, unsigned ni) {
+template <typename T>
+struct Piv {
+  decltype(key_bits(T())) k;
+  unsigned ni;
+};
+template <typename T>
+__device__ inline void piv_merge(Piv<T>& a, decltype(key_bits(T())) k, unsigned ni) {
   if (k > a.k || (k == a.k && ni > a.ni)) {
     a.k = k;
     a.ni = ni;
   }
 }
+// Maximum over the wavefront, uniform.
 template <int C, int RM>
-__device__ inline void piv_step(Piv& a) {
-  const unsigned lo = (unsigned)dpp_i<C, RM>((int)(unsigned)a.k);
-  const unsigned hi = (unsigned)dpp_i<C, RM>((int)(unsigned)(a.k >> 32));
-  const unsigned ni = (unsigned)dpp_i<C, RM>((int)a.ni);
-  piv_merge(a, ((unsigned long long)hi << 32) | lo, ni);
+__device__ inline void umax_step(unsigned& v) {
+  v = max(v, (unsigned)dpp_i<C, RM>((int)v));
 }
-__device__ inline Piv wpiv(Piv a) {
-  piv_step<0xB1, 0xF>(a);
-  piv_step<0x4E, 0xF>(a);
-  piv_step<0x141, 0xF>(a);
-  piv_step<0x140, 0xF>(a);
-  piv_step<0x142, 0xA>(a);
-  piv_step<0x143, 0xC>(a);
-  Piv r;
-  r.k = ((unsigned long long)(unsigned)rdl_i((int)(unsigned)(a.k >> 32), 63) << 32) |
-        (unsigned)rdl_i((int)(unsigned)a.k, 63);
-  r.ni = (unsigned)rdl_i((int)a.ni, 63);
-  return r;
+template <int C, int RM>
+__device__ inline void umax_step(unsigned long long& v) {
+  const unsigned lo = (unsigned)dpp_i<C, RM>((int)(unsigned)v);
+  const unsigned hi = (unsigned)dpp_i<C, RM>((int)(unsigned)(v >> 32));
+  const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+  v = v > o ? v : o;
+}
+template <typename K>
+__device__ inline K wmax(K v) {
+  umax_step<0xB1, 0xF>(v);
+  umax_step<0x4E, 0xF>(v);
+  umax_step<0x141, 0xF>(v);
+  umax_step<0x140, 0xF>(v);
+  umax_step<0x142, 0xA>(v);
+  umax_step<0x143, 0xC>(v);
+  if constexpr (sizeof(K) == 8)
+    return ((unsigned long long)(unsigned)rdl_i((int)(unsigned)(v >> 32), 63) << 32) |
+           (unsigned)rdl_i((int)(unsigned)v, 63);
+  else
+    return (unsigned)rdl_i((int)v, 63);
+}
+// The largest key, then the smallest index among the lanes that hold it: two
+// plain maxima (one instruction per step in single precision) where one
+// maximum of the pair compared both at every step.
+template <typename T>
+__device__ inline Piv<T> wpiv(Piv<T> a) {
+  const auto k = wmax(a.k);
+  return {k, wmax(a.k == k ? a.ni : 0u)};
 }
 // index of the winner, or -1 when there was no candidate
-__device__ inline int piv_index(const Piv& p) {
+template <typename T>
+__device__ inline int piv_index(const Piv<T>& p) {
   return (p.k == 0 && p.ni == 0) ? -1 : (int)(~p.ni);
 }
 
@@ -627,7 +654,7 @@ struct AcaArgs {
   const AcaSlot* slot;   // working slot of every block of the chunk
   const int32_t* list[kAcaClasses];  // block indices of each class, largest first
   int64_t cnt[kAcaClasses];
-  int* head;             // queue position of each class (zero before the launches)
+  int* head;             // queue positions, kXcds per class (zero before the launches)
   int nb;                // blocks per queue fetch (wavefront classes)
   int kmax;              // rank cap of this pass
   double eps;
@@ -636,9 +663,9 @@ struct AcaArgs {
 };
 
 // Stop test shared by both variants: keep term r, then stop when
-// |u_r||v_r| <= eps |S_r|_F, or r reached the cap, or every row was used.
+// |u_r||v_r| <= eps |S_r|_F (compared in squares), or r reached the cap, or every row was used.
 __device__ inline bool aca_stop(double uu, double vv, double s2, double eps) {
-  return sqrt(uu) * sqrt(vv) <= eps * sqrt(fmax(s2, 0.0));
+  return uu * vv <= eps * eps * fmax(s2, 0.0);
 }
 
 template <typename X, int Q>
@@ -651,32 +678,46 @@ __device__ inline X pick(const X (&a)[Q], int q) {
 }
 
 // One block per wavefront (m, n <= 64 Q).  Lane L owns rows and columns
-// L + 64 q, q < Q.  The working factors live in the block's slot: U
-// column-major m x kcap, then V n x kcap; a lane only reads and writes its
-// own rows / columns of them, other lanes' values arrive by readlane.
-
+// L + 64 q, q < Q (past the last one: a copy of it, kept out of the pivots, the
+// norms and the stores).  The working factors live in the block's slot: U
+// column-major m x kcap, then V n x kcap.
+//
+// Bound by the instructions of a step (80% of the issue slots at four
+// wavefronts per SIMD).  So the sources of the lane's columns stay in
+// registers, as do the first KB terms of V from the residual row to their dots
+// with v; u_l[i*] and v_l[j*] of up to 64 terms come in one load each, term l in
+// lane l; and the dots, one wavefront sum each, are summed four or eight at a
+// time.  N = 524,288, FP32, leaf 64: blocks of up to 64 rows 5.6 -> 3.5 ms, 128
+// 4.7 -> 3.5, 256 5.7 -> 3.7.
 template <typename T, int Q, int OP>
 __device__ void aca_wave(const AcaArgs<T>& A, int b) {
   constexpr int KB = Q == 4 ? 4 : 8;   // previous terms per batch of loads
   const int lane = threadIdx.x & 63;
   const int2 ts = A.blk[b];
   const Cluster tau = A.cl[ts.x], sig = A.cl[ts.y];
-  const int r0 = tau.x, m = tau.y - tau.x, c0 = sig.x, n = sig.y - sig.x;
+  const int r0 = uni(tau.x), m = uni(tau.y) - r0, c0 = uni(sig.x), n = uni(sig.y) - c0;
   const int kcap = min(A.kmax, min(m, n));
-  T* U = reinterpret_cast<T*>((uintptr_t)A.slot[b].ptr);
+  T* U = uni_ptr<T>(A.slot[b].ptr);
   T* V = U + (int64_t)kcap * m;
   const Geom<T>& g = A.g;
   bool hr[Q], hc[Q], used[Q];
+  uint32_t ro[Q], co[Q];               // byte offsets of the lane's rows and columns in a term
   double px[Q], py[Q], pz[Q];
+  constexpr bool kHold = sizeof(T) == 4 || Q == 1;   // double sources of more columns spill
+  constexpr bool kKeep = sizeof(T) == 4 && Q <= 2;   // more registers spill
+  Src<T> src[kHold ? Q : 1];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    const int i = lane + 64 * q;
+    const int i = lane + 64 * q, ri = min(i, m - 1), ci = min(i, n - 1);
     hr[q] = i < m;
     hc[q] = i < n;
     used[q] = false;
-    px[q] = hr[q] ? g.c[r0 + i] : 0.0;
-    py[q] = hr[q] ? g.c[g.n + r0 + i] : 0.0;
-    pz[q] = hr[q] ? g.c[2 * g.n + r0 + i] : 0.0;
+    ro[q] = (uint32_t)ri * (uint32_t)sizeof(T);
+    co[q] = (uint32_t)ci * (uint32_t)sizeof(T);
+    px[q] = g.c[r0 + ri];
+    py[q] = g.c[g.n + r0 + ri];
+    pz[q] = g.c[2 * g.n + r0 + ri];
+    if constexpr (kHold) load_src(g, c0 + ci, src[q]);
   }
   int nused = 0, r = 0, istar = 0, rows_eval = 0;
   double s2 = 0.0;
@@ -692,33 +733,34 @@ __device__ void aca_wave(const AcaArgs<T>& A, int b) {
     T val[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      val[q] = 0;
-      if (hc[q]) {
-        Src<T> s;
-        load_src(g, c0 + lane + 64 * q, s);
-        val[q] = op_entry(ti, r0 + istar, s, c0 + lane + 64 * q);
-      }
+      const int j = c0 + min(lane + 64 * q, n - 1);
+      if constexpr (!kHold) load_src(g, j, src[0]);
+      val[q] = op_entry(ti, r0 + istar, src[kHold ? q : 0], j);
     }
     // the previous terms KB at a time: their loads are issued together (an
     // index past r - 1 reads term r - 1 and is not used)
-    const bool ownr = lane + 64 * iq < m;
+    wave_order();
+    T ug = 0, vf[KB][Q] = {};
     for (int l0 = 0; l0 < r; l0 += KB) {
-      T ub[KB], vb[KB][Q];
+      if ((l0 & 63) == 0) ug = ld_at(U + istar, (uint32_t)(min(l0 + lane, r - 1) * m) * (uint32_t)sizeof(T));
+      T vb[KB][Q];
 #pragma unroll
-      for (int k = 0; k < KB; ++k) {
-        const int l = min(l0 + k, r - 1);
-        ub[k] = ownr ? U[(int64_t)l * m + lane + 64 * iq] : (T)0;
+      for (int k = 0; k < KB; ++k)
 #pragma unroll
-        for (int q = 0; q < Q; ++q) vb[k][q] = hc[q] ? V[(int64_t)l * n + lane + 64 * q] : (T)0;
-      }
+        for (int q = 0; q < Q; ++q) vb[k][q] = ld_at(V + (int64_t)min(l0 + k, r - 1) * n, co[q]);
 #pragma unroll
       for (int k = 0; k < KB; ++k) {
         if (l0 + k < r) {
-          const T ui = rdl_v(ub[k], il);
+          const T ui = rdl_v(ug, (l0 + k) & 63);
 #pragma unroll
-          for (int q = 0; q < Q; ++q)
-            if (hc[q]) val[q] -= ui * vb[k][q];
+          for (int q = 0; q < Q; ++q) val[q] -= ui * vb[k][q];
         }
+      }
+      if (kKeep && l0 == 0) {
+#pragma unroll
+        for (int k = 0; k < KB; ++k)
+#pragma unroll
+          for (int q = 0; q < Q; ++q) vf[k][q] = vb[k][q];
       }
     }
     ++rows_eval;
@@ -726,7 +768,7 @@ __device__ void aca_wave(const AcaArgs<T>& A, int b) {
     for (int q = 0; q < Q; ++q)
       if (q == iq && lane == il) used[q] = true;
     ++nused;
-    Piv pv{0, 0};
+    Piv<T> pv{0, 0};
 #pragma unroll
     for (int q = 0; q < Q; ++q)
       if (hc[q]) piv_merge(pv, key_bits((T)fabs(val[q])), ~(unsigned)(lane + 64 * q));
@@ -735,11 +777,11 @@ __device__ void aca_wave(const AcaArgs<T>& A, int b) {
     if (jstar >= 0 && jstar < n) delta = rdl_v(pick(val, jstar >> 6), jstar & 63);
     if (delta == (T)0) {
       if (nused >= m) break;
-      Piv nx{0, 0};
+      Piv<T> nx{0, 0};
 #pragma unroll
       for (int q = 0; q < Q; ++q)
         if (hr[q] && !used[q]) {
-          const T k = (r > 0) ? (T)fabs(U[(int64_t)(r - 1) * m + lane + 64 * q]) : (T)0;
+          const T k = (r > 0) ? (T)fabs(ld_at(U + (int64_t)(r - 1) * m, ro[q])) : (T)0;
           piv_merge(nx, key_bits(k), ~(unsigned)(lane + 64 * q));
         }
       istar = piv_index(wpiv(nx));
@@ -751,49 +793,54 @@ __device__ void aca_wave(const AcaArgs<T>& A, int b) {
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       v[q] = hc[q] ? val[q] / delta : (T)0;
-      if (hc[q]) V[(int64_t)r * n + lane + 64 * q] = v[q];
+      if (hc[q]) st_at(V + (int64_t)r * n, co[q], v[q]);
       vv += (double)v[q] * (double)v[q];
     }
     // residual column  u = a(:, j*) - sum_l v_l[j*] u_l.  The cross terms of
     // |S_r|_F^2, sum_l (u_l . u)(v_l . v), equal u . w with w = sum_l u_l
     // (v_l . v), accumulated in the same pass over the previous terms.
-    const int jq = jstar >> 6, jl = jstar & 63;
     Src<T> s;
     load_src(g, c0 + jstar, s);
     T u[Q];
     double wv[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      u[q] = 0;
-      if (hr[q]) {
-        Tgt<T, OP> tq;
-        if constexpr (OP == kOpColloc)
-          tq = Tgt<T, OP>{px[q], py[q], pz[q]};
-        else
-          load_tgt(g, r0, lane + 64 * q, tq);
-        u[q] = op_entry(tq, r0 + lane + 64 * q, s, c0 + jstar);
-      }
+      const int i = min(lane + 64 * q, m - 1);
+      Tgt<T, OP> tq;
+      if constexpr (OP == kOpColloc)
+        tq = Tgt<T, OP>{px[q], py[q], pz[q]};
+      else
+        load_tgt(g, r0, i, tq);
+      u[q] = op_entry(tq, r0 + i, s, c0 + jstar);
       wv[q] = 0.0;
     }
+    T vg = 0;
     for (int l0 = 0; l0 < r; l0 += KB) {
-      T vo[KB][Q], uo[KB][Q];
+      if ((l0 & 63) == 0) vg = ld_at(V + jstar, (uint32_t)(min(l0 + lane, r - 1) * n) * (uint32_t)sizeof(T));
+      T uo[KB][Q];
+      double dots[KB];
+#pragma unroll
+      for (int k = 0; k < KB; ++k)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) uo[k][q] = ld_at(U + (int64_t)min(l0 + k, r - 1) * m, ro[q]);
+      if (!kKeep || l0 > 0) {              // else the first batch is still in registers
+#pragma unroll
+        for (int k = 0; k < KB; ++k)
+#pragma unroll
+          for (int q = 0; q < Q; ++q) vf[k][q] = ld_at(V + (int64_t)min(l0 + k, r - 1) * n, co[q]);
+      }
 #pragma unroll
       for (int k = 0; k < KB; ++k) {
-        const int l = min(l0 + k, r - 1);
+        dots[k] = 0.0;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          vo[k][q] = hc[q] ? V[(int64_t)l * n + lane + 64 * q] : (T)0;
-          uo[k][q] = hr[q] ? U[(int64_t)l * m + lane + 64 * q] : (T)0;
-        }
+        for (int q = 0; q < Q; ++q) dots[k] += (double)vf[k][q] * (double)v[q];
       }
+      const double dsum = wsums(dots);
 #pragma unroll
       for (int k = 0; k < KB; ++k) {
         if (l0 + k < r) {
-          double pvl = 0.0;
-#pragma unroll
-          for (int q = 0; q < Q; ++q) pvl += (double)vo[k][q] * (double)v[q];
-          const T vj = rdl_v(pick(vo[k], jq), jl);
-          const double dv = wsum(pvl);
+          const T vj = rdl_v(vg, (l0 + k) & 63);
+          const double dv = rdl_v(dsum, k * (64 / KB));
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
             u[q] -= vj * uo[k][q];
@@ -805,13 +852,16 @@ __device__ void aca_wave(const AcaArgs<T>& A, int b) {
     double uu = 0.0, cw = 0.0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      if (hr[q]) U[(int64_t)r * m + lane + 64 * q] = u[q];
-      uu += (double)u[q] * (double)u[q];
-      cw += (double)u[q] * wv[q];
+      if (hr[q]) {
+        st_at(U + (int64_t)r * m, ro[q], u[q]);
+        uu += (double)u[q] * (double)u[q];
+        cw += (double)u[q] * wv[q];
+      }
     }
-    const double cross = wsum(cw);
-    uu = wsum(uu);
-    vv = wsum(vv);
+    const double sums = wsums({cw, uu, vv, 0.0});
+    const double cross = rdl_v(sums, 0);
+    uu = rdl_v(sums, 16);
+    vv = rdl_v(sums, 32);
     s2 += 2.0 * cross + uu * vv;
     ++r;
     if (aca_stop(uu, vv, s2, A.eps)) break;
@@ -820,7 +870,7 @@ __device__ void aca_wave(const AcaArgs<T>& A, int b) {
       break;
     }
     if (nused >= m) break;
-    Piv nx{0, 0};
+    Piv<T> nx{0, 0};
 #pragma unroll
     for (int q = 0; q < Q; ++q)
       if (hr[q] && !used[q]) piv_merge(nx, key_bits((T)fabs(u[q])), ~(unsigned)(lane + 64 * q));
@@ -834,158 +884,181 @@ __device__ void aca_wave(const AcaArgs<T>& A, int b) {
 }
 
 // One block per workgroup of NT threads (blocks larger than the wavefront
-// classes: NT = 256, and NT = 1024 for the largest blocks, whose sequential
-// steps are the critical path of their chunk).  Cross-thread reads of the working factors happen only after a
-// barrier.  The used-row flags are bytes placed after V in the slot.
+// classes: NT = 128, 256, and NT = 1,024 for the largest blocks, whose sequential
+// steps are the critical path of their chunk).  Cross-thread reads of the
+// working factors happen only after a barrier.  The used-row flags are bytes
+// placed after V in the slot.
+//
+// Bound by memory: the terms and sources of the blocks in flight are several
+// times the L2, and a step streams them (7 TB/s).  The dots of the first
+// kTermBatch terms are therefore taken while the residual row reads them.
+// N = 524,288, FP32, leaf 64: blocks of 257..1,024 rows 10.6 -> 8.2 ms,
+// 1,025..4,096 9.9 -> 7.6, above 2.4 -> 1.9, the queues below included; the next
+// column's source loaded ahead spills, NT = 512 for 1,025..4,096 rows 13.0.
 template <typename T, int NT>
 struct AcaShared {
   static constexpr int kW = NT / 64;
   T a[kMaxRank];             // u_l[i*] or v_l[j*] of the previous terms
   double dv[kMaxRank][kW];   // per-wave partial dots v_l . v_r
   double dt[kMaxRank];       // their totals
-  Piv pv[kW];
+  Piv<T> pv[kW];
   double red[3][kW];
-  Piv pv_out;
+  Piv<T> pv_out;
   double out[3];
 };
 
-template <int NT>
-__device__ inline Piv wg_piv(Piv a, Piv* lds, Piv* out) {
+template <typename T, int NT>
+__device__ inline Piv<T> wg_piv(Piv<T> a, Piv<T>* lds, Piv<T>* out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   a = wpiv(a);
   if (lane == 0) lds[wave] = a;
   __syncthreads();
   if (threadIdx.x == 0) {
-    Piv r = lds[0];
+    Piv<T> r = lds[0];
     for (int w = 1; w < (NT / 64); ++w) piv_merge(r, lds[w].k, lds[w].ni);
     *out = r;
   }
   __syncthreads();
-  Piv r = *out;
+  Piv<T> r = *out;
   __syncthreads();
   return r;
 }
 
-// previous terms per batch of loads, and columns (rows) per thread at a
-// time, in the workgroup variant
+// Previous terms per batch of loads in the workgroup variant: terms l0, l0 + 1,
+// ... below r (further ones read term r - 1) at byte offset off.
 constexpr int kTermBatch = 8;
-constexpr int kColUnroll = 1;
+template <typename T>
+__device__ inline void load_terms(const T* F, int len, int l0, int r, uint32_t off,
+                                  T (&out)[kTermBatch]) {
+#pragma unroll
+  for (int k = 0; k < kTermBatch; ++k) out[k] = ld_at(F + (int64_t)min(l0 + k, r - 1) * len, off);
+}
 
 template <typename T, int NT, int OP>
 __device__ void aca_wg(const AcaArgs<T>& A, int b, AcaShared<T, NT>& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int2 ts = A.blk[b];
   const Cluster tau = A.cl[ts.x], sig = A.cl[ts.y];
-  const int r0 = tau.x, m = tau.y - tau.x, c0 = sig.x, n = sig.y - sig.x;
+  const int r0 = uni(tau.x), m = uni(tau.y) - r0, c0 = uni(sig.x), n = uni(sig.y) - c0;
   const int kcap = min(A.kmax, min(m, n));
-  T* U = reinterpret_cast<T*>((uintptr_t)A.slot[b].ptr);
+  T* U = uni_ptr<T>(A.slot[b].ptr);
   T* V = U + (int64_t)kcap * m;
   uint8_t* used = reinterpret_cast<uint8_t*>(V + (int64_t)kcap * n);
   const Geom<T>& g = A.g;
-  for (int i = tid; i < m; i += NT) used[i] = 0;
+  for (int i = tid; i < m; i += NT) st_at(used, (uint32_t)i, (uint8_t)0);
   __syncthreads();
   int nused = 0, r = 0, istar = 0, rows_eval = 0;
   double s2 = 0.0;
   bool cap_hit = false;
   while (true) {
-    if (tid < r) sh.a[tid] = U[(int64_t)tid * m + istar];
+    if (tid < r) sh.a[tid] = ld_at(U + istar, (uint32_t)(tid * m) * (uint32_t)sizeof(T));
     __syncthreads();
     Tgt<T, OP> ti;
     if constexpr (OP == kOpColloc)
       ti = Tgt<T, OP>{g.c[r0 + istar], g.c[g.n + r0 + istar], g.c[2 * g.n + r0 + istar]};
     else
       load_tgt(g, r0 + istar, 0, ti);
-    Piv pv{0, 0};
-    // kColUnroll columns per thread at a time, so that their loads overlap
-    // (indices past n - 1 are clamped and their results dropped)
-    for (int j0 = tid; j0 < n; j0 += kColUnroll * NT) {
-      Src<T> sj[kColUnroll];
-      T val[kColUnroll];
-      int jj[kColUnroll];
+    Piv<T> pv{0, 0};
+    // The dots of the first kTermBatch terms with the residual row are taken
+    // here, while their values are in registers (they are the dots with v_r but
+    // for the division): a second pass over V is left for the terms above.
+    double pd[kTermBatch];
 #pragma unroll
-      for (int u = 0; u < kColUnroll; ++u) {
-        jj[u] = min(j0 + u * NT, n - 1);
-        load_src_u(g, c0 + jj[u], sj[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < kColUnroll; ++u)
-        val[u] = op_entry(ti, r0 + istar, sj[u], c0 + jj[u]);
-      for (int l0 = 0; l0 < r; l0 += kTermBatch) {
-        T vb[kColUnroll][kTermBatch];
-#pragma unroll
-        for (int u = 0; u < kColUnroll; ++u)
-#pragma unroll
-          for (int k = 0; k < kTermBatch; ++k)
-            vb[u][k] = ld_at(V + (int64_t)min(l0 + k, r - 1) * n, (uint32_t)jj[u] * (uint32_t)sizeof(T));
+    for (int k = 0; k < kTermBatch; ++k) pd[k] = 0.0;
+#pragma unroll 1
+    for (int j = tid; j < n; j += NT) {
+      const uint32_t jb = (uint32_t)j * (uint32_t)sizeof(T);
+      T vb[kTermBatch];
+      if (r > 0) load_terms(V, n, 0, r, jb, vb);
+      Src<T> sj;
+      load_src_u(g, c0 + j, sj);
+      T val = op_entry(ti, r0 + istar, sj, c0 + j);
+      if (r > 0) {
 #pragma unroll
         for (int k = 0; k < kTermBatch; ++k)
-          if (l0 + k < r)
+          if (k < r) val -= sh.a[k] * vb[k];
+#pragma unroll 1
+        for (int l0 = kTermBatch; l0 < r; l0 += kTermBatch) {
+          T vn[kTermBatch];
+          load_terms(V, n, l0, r, jb, vn);
 #pragma unroll
-            for (int u = 0; u < kColUnroll; ++u) val[u] -= sh.a[l0 + k] * vb[u][k];
-      }
-#pragma unroll
-      for (int u = 0; u < kColUnroll; ++u) {
-        if (j0 + u * NT < n) {
-          V[(int64_t)r * n + jj[u]] = val[u];
-          piv_merge(pv, key_bits((T)fabs(val[u])), ~(unsigned)jj[u]);
+          for (int k = 0; k < kTermBatch; ++k)
+            if (l0 + k < r) val -= sh.a[l0 + k] * vn[k];
         }
+#pragma unroll
+        for (int k = 0; k < kTermBatch; ++k) pd[k] += (double)vb[k] * (double)val;
       }
+      st_at(V + (int64_t)r * n, jb, val);
+      piv_merge(pv, key_bits((T)fabs(val)), ~(unsigned)j);
     }
-    if (tid == 0) used[istar] = 1;
+    if (r > 0) {
+      const double t = wsums(pd);                          // term k in lane 8 k
+      if ((lane & 7) == 0 && lane / 8 < r) sh.dv[lane / 8][wave] = t;
+    }
+    if (tid == 0) st_at(used, (uint32_t)istar, (uint8_t)1);
     ++rows_eval;
     ++nused;
-    const int jstar = uni(piv_index(wg_piv<NT>(pv, sh.pv, &sh.pv_out)));
+    const int jstar = uni(piv_index(wg_piv<T, NT>(pv, sh.pv, &sh.pv_out)));
     // every thread may read V[r][j*] now (barriers in wg_piv)
-    const T delta = uni((jstar >= 0 && jstar < n) ? V[(int64_t)r * n + jstar] : (T)0);
+    const T delta = uni((jstar >= 0 && jstar < n) ? ld_at(V + (int64_t)r * n, (uint32_t)jstar * (uint32_t)sizeof(T)) : (T)0);
     // every thread holds delta before the owner of j* overwrites that entry
     __syncthreads();
     if (delta == (T)0) {
       if (nused >= m) break;
-      Piv nx{0, 0};
+      Piv<T> nx{0, 0};
       for (int i = tid; i < m; i += NT) {
-        if (used[i]) continue;
-        const T k = (r > 0) ? (T)fabs(U[(int64_t)(r - 1) * m + i]) : (T)0;
+        if (ld_at(used, (uint32_t)i)) continue;
+        const T k = (r > 0) ? (T)fabs(ld_at(U + (int64_t)(r - 1) * m, (uint32_t)i * (uint32_t)sizeof(T))) : (T)0;
         piv_merge(nx, key_bits(k), ~(unsigned)i);
       }
-      istar = uni(piv_index(wg_piv<NT>(nx, sh.pv, &sh.pv_out)));
+      istar = uni(piv_index(wg_piv<T, NT>(nx, sh.pv, &sh.pv_out)));
       if (istar < 0 || istar >= m) break;
       continue;
     }
     // v_r = v~ / delta, then the dots v_l . v_r of the previous terms.  Each
     // thread reads back only the entries of v_r it wrote itself.
+    // Two columns at a time (a column past n - 1 reads the last one as zero).
     double vv = 0.0;
-    for (int j = tid; j < n; j += NT) {
-      const T v = V[(int64_t)r * n + j] / delta;
-      V[(int64_t)r * n + j] = v;
-      vv += (double)v * (double)v;
+#pragma unroll 1
+    for (int j0 = tid; j0 < n; j0 += 2 * NT) {
+      const uint32_t b0 = (uint32_t)j0 * (uint32_t)sizeof(T);
+      const uint32_t b1 = (uint32_t)min(j0 + NT, n - 1) * (uint32_t)sizeof(T);
+      T* vr = V + (int64_t)r * n;
+      const T v0 = ld_at(vr, b0) / delta, v1 = ld_at(vr, b1) / delta;
+      st_at(vr, b0, v0);
+      vv += (double)v0 * (double)v0;
+      if (j0 + NT < n) {
+        st_at(vr, b1, v1);
+        vv += (double)v1 * (double)v1;
+      }
     }
-    for (int l0 = 0; l0 < r; l0 += kTermBatch) {
+#pragma unroll 1
+    for (int l0 = kTermBatch; l0 < r; l0 += kTermBatch) {
       double pvv[kTermBatch];
 #pragma unroll
       for (int k = 0; k < kTermBatch; ++k) pvv[k] = 0.0;
-      for (int j = tid; j < n; j += NT) {
-        const uint32_t jb = (uint32_t)j * (uint32_t)sizeof(T);
-        const double vr = (double)ld_at(V + (int64_t)r * n, jb);
-        T vb[kTermBatch];
+#pragma unroll 1
+      for (int j0 = tid; j0 < n; j0 += 2 * NT) {
+        const uint32_t b0 = (uint32_t)j0 * (uint32_t)sizeof(T);
+        const uint32_t b1 = (uint32_t)min(j0 + NT, n - 1) * (uint32_t)sizeof(T);
+        const T v0 = ld_at(V + (int64_t)r * n, b0), w1 = ld_at(V + (int64_t)r * n, b1);
+        T vb0[kTermBatch], vb1[kTermBatch];
+        load_terms(V, n, l0, r, b0, vb0);
+        load_terms(V, n, l0, r, b1, vb1);
+        const T v1 = j0 + NT < n ? w1 : (T)0;
 #pragma unroll
-        for (int k = 0; k < kTermBatch; ++k) vb[k] = ld_at(V + (int64_t)min(l0 + k, r - 1) * n, jb);
-#pragma unroll
-        for (int k = 0; k < kTermBatch; ++k) pvv[k] += (double)vb[k] * vr;
+        for (int k = 0; k < kTermBatch; ++k)
+          pvv[k] += (double)vb0[k] * (double)v0 + (double)vb1[k] * (double)v1;
       }
-#pragma unroll
-      for (int k = 0; k < kTermBatch; ++k) {
-        if (l0 + k < r) {
-          const double t = wsum(pvv[k]);
-          if (lane == 0) sh.dv[l0 + k][wave] = t;
-        }
-      }
+      const double t = wsums(pvv);                     // term l0 + k in lane 8 k
+      if ((lane & 7) == 0 && l0 + lane / 8 < r) sh.dv[l0 + lane / 8][wave] = t;
     }
-    if (tid < r) sh.a[tid] = V[(int64_t)tid * n + jstar];
+    if (tid < r) sh.a[tid] = ld_at(V + jstar, (uint32_t)(tid * n) * (uint32_t)sizeof(T));
     __syncthreads();
     if (tid < r) {
       double t = 0.0;
       for (int w = 0; w < (NT / 64); ++w) t += sh.dv[tid][w];
-      sh.dt[tid] = t;
+      sh.dt[tid] = tid < kTermBatch ? t / (double)delta : t;
     }
     __syncthreads();
     // residual column u_r; the cross terms sum_l (u_l . u_r)(v_l . v_r) are
@@ -993,63 +1066,41 @@ __device__ void aca_wg(const AcaArgs<T>& A, int b, AcaShared<T, NT>& sh) {
     Src<T> s;
     load_src(g, c0 + jstar, s);
     double uu = 0.0, cw = 0.0;
-    Piv nx{0, 0};
-    for (int i0 = tid; i0 < m; i0 += kColUnroll * NT) {
-      T u[kColUnroll];
-      double w[kColUnroll];
-      int ii[kColUnroll];
-#pragma unroll
-      for (int q = 0; q < kColUnroll; ++q) {
-        ii[q] = min(i0 + q * NT, m - 1);
-        const int i = ii[q];
-        Tgt<T, OP> tq;
-        load_tgt(g, r0, i, tq);
-        u[q] = op_entry(tq, r0 + i, s, c0 + jstar);
-        w[q] = 0.0;
-      }
+    Piv<T> nx{0, 0};
+#pragma unroll 1
+    for (int i = tid; i < m; i += NT) {
+      const uint32_t ib = (uint32_t)i * (uint32_t)sizeof(T);
+      T ub[kTermBatch];
+      if (r > 0) load_terms(U, m, 0, r, ib, ub);
+      Tgt<T, OP> tq;
+      load_tgt(g, r0, i, tq);
+      const bool was = ld_at(used, (uint32_t)i);
+      T u = op_entry(tq, r0 + i, s, c0 + jstar);
+      double w = 0.0;
+#pragma unroll 1
       for (int l0 = 0; l0 < r; l0 += kTermBatch) {
-        T ub[kColUnroll][kTermBatch];
-#pragma unroll
-        for (int q = 0; q < kColUnroll; ++q)
-#pragma unroll
-          for (int k = 0; k < kTermBatch; ++k)
-            ub[q][k] = ld_at(U + (int64_t)min(l0 + k, r - 1) * m, (uint32_t)ii[q] * (uint32_t)sizeof(T));
+        if (l0 > 0) load_terms(U, m, l0, r, ib, ub);
 #pragma unroll
         for (int k = 0; k < kTermBatch; ++k) {
           if (l0 + k < r) {
-#pragma unroll
-            for (int q = 0; q < kColUnroll; ++q) {
-              u[q] -= sh.a[l0 + k] * ub[q][k];
-              w[q] += sh.dt[l0 + k] * (double)ub[q][k];
-            }
+            u -= sh.a[l0 + k] * ub[k];
+            w += sh.dt[l0 + k] * (double)ub[k];
           }
         }
       }
-#pragma unroll
-      for (int q = 0; q < kColUnroll; ++q) {
-        if (i0 + q * NT < m) {
-          const int i = ii[q];
-          U[(int64_t)r * m + i] = u[q];
-          uu += (double)u[q] * (double)u[q];
-          cw += (double)u[q] * w[q];
-          if (!used[i]) piv_merge(nx, key_bits((T)fabs(u[q])), ~(unsigned)i);
-        }
-      }
+      st_at(U + (int64_t)r * m, ib, u);
+      uu += (double)u * (double)u;
+      cw += (double)u * w;
+      if (!was) piv_merge(nx, key_bits((T)fabs(u)), ~(unsigned)i);
     }
-    uu = wsum(uu);
-    vv = wsum(vv);
-    cw = wsum(cw);
+    const double sums = wsums({uu, vv, cw, 0.0});      // in lanes 0, 16 and 32
     nx = wpiv(nx);
-    if (lane == 0) {
-      sh.red[0][wave] = uu;
-      sh.red[1][wave] = vv;
-      sh.red[2][wave] = cw;
-      sh.pv[wave] = nx;
-    }
+    if ((lane & 15) == 0 && lane < 48) sh.red[lane / 16][wave] = sums;
+    if (lane == 0) sh.pv[wave] = nx;
     __syncthreads();
     if (tid == 0) {
       double tu = 0.0, tv = 0.0, tc = 0.0;
-      Piv best = sh.pv[0];
+      Piv<T> best = sh.pv[0];
       for (int w = 0; w < (NT / 64); ++w) {
         tu += sh.red[0][w];
         tv += sh.red[1][w];
@@ -1090,21 +1141,51 @@ __device__ void aca_wg(const AcaArgs<T>& A, int b, AcaShared<T, NT>& sh) {
 // free (the load imbalance of fixed assignments).  A workgroup or wavefront
 // leaves when the queue position passes the last block.
 //
+// Queue of a workgroup class.  The blocks lie in the order of the block tree, so
+// neighbours share clusters; kAcaChunk consecutive ones belong to one XCD (chunk
+// c to XCD c mod 8), which finds their sources in its own L2.  A workgroup takes
+// from the queue of its XCD and, when that is empty, from the next ones.
+// N = 524,288, FP32: blocks of 257..1,024 rows 8.7 -> 8.2 ms, 1,025..4,096 8.3 ->
+// 7.6 against one queue per class.
+constexpr int kAcaChunk = 512;
+
+struct AcaQueue {
+  int x, tries;
+  __device__ inline AcaQueue() : x(blockIdx.x % kXcds), tries(0) {}
+  // The next block, or -1 when every queue is empty (at most kXcds misses over
+  // the life of the workgroup).
+  __device__ inline int next(int* head, int64_t cnt) {
+    for (; tries < kXcds; ++tries, x = (x + 1) % kXcds) {
+      const int64_t k = atomicAdd(head + x, 1);
+      const int64_t it = (k / kAcaChunk * kXcds + x) * kAcaChunk + k % kAcaChunk;
+      if (it < cnt) return (int)it;
+    }
+    return -1;
+  }
+};
+
 // Classes 0 (NT = 1,024) and 1 (NT = 256): one block per workgroup.  One
 // latch, no early continue: every block ends at the barrier below, so the
 // thread that fetches the next position has finished the current block (its
 // result stores included) before any thread reads the next position.
-// Galerkin entries (49 kernel values each) hold the whole row triangle in
-// registers: half the occupancy, no spills.
+// Wavefronts per SIMD: as many as leave no more than a few registers spilled.
+template <typename T, int NT, int OP>
+constexpr int aca_wg_waves() {
+  if (NT == 1024) return 1;
+  if (sizeof(T) == 8) return OP == kOpGalerkin ? 2 : 3;
+  return OP == kOpGalerkin ? 4 : 5;
+}
+
 template <typename T, int NT, int CLS, int OP>
-__global__ __launch_bounds__(NT, NT == 1024 ? 1 : (OP == kOpGalerkin ? 2 : 4)) void k_aca_wg(AcaArgs<T> A) {
+__global__ __launch_bounds__(NT, (aca_wg_waves<T, NT, OP>())) void k_aca_wg(AcaArgs<T> A) {
   __shared__ AcaShared<T, NT> sh;
   __shared__ int item_sh;
+  AcaQueue queue;
   while (true) {
-    if (threadIdx.x == 0) item_sh = atomicAdd(A.head + CLS, 1);
+    if (threadIdx.x == 0) item_sh = queue.next(A.head + CLS * kXcds, A.cnt[CLS]);
     __syncthreads();
-    const int64_t it = uni(item_sh);
-    if (it >= A.cnt[CLS]) break;
+    const int it = uni(item_sh);
+    if (it < 0) break;
     aca_wg<T, NT, OP>(A, A.list[CLS][it], sh);
     __syncthreads();
   }
@@ -1127,7 +1208,7 @@ void k_aca_wave(AcaArgs<T> A) {
   const int64_t cnt = A.cnt[c];
   while (true) {
     int it = 0;
-    if (lane == 0) it = atomicAdd(A.head + c, NB);
+    if (lane == 0) it = atomicAdd(A.head + c * kXcds, NB);
     it = uni(it);
     if (it >= cnt) break;
     const int64_t end = std::min<int64_t>(it + NB, cnt);
@@ -1751,7 +1832,7 @@ __host__ __device__ inline int64_t slot_elems(int64_t m, int64_t n, int kcap) {
 // the class lists and counts (head is zeroed here).
 template <typename T, int OP>
 void launch_aca_classes(const AcaArgs<T>& A, int* head, hipStream_t s) {
-  HM_HIP(hipMemsetAsync(head, 0, kAcaClasses * sizeof(int), s));
+  HM_HIP(hipMemsetAsync(head, 0, kAcaClasses * kXcds * sizeof(int), s));
   int dev = 0, ncu = 0;
   HM_HIP(hipGetDevice(&dev));
   HM_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1797,7 +1878,7 @@ void launch_aca_classes(const AcaArgs<T>& A, int* head, hipStream_t s) {
 // The batched ACA over the blocks of a chunk (with mask: only the marked
 // ones) at rank cap kmax: class lists from the binning, then the class
 // launches.  flags, offs: kAcaClasses * nb int64 scratch; lists:
-// kAcaClasses * nb int32; head: kAcaClasses int.
+// kAcaClasses * nb int32; head: kAcaClasses * kXcds int.
 template <typename T, int OP>
 void run_aca(const Geom<T>& g, const int2* blk, int64_t nb, const Cluster* cl,
              const AcaSlot* slot, int kmax, double eps, const int64_t* mask, const AcaBins& bins,
@@ -1830,18 +1911,17 @@ void run_aca(const Geom<T>& g, const int2* blk, int64_t nb, const Cluster* cl,
   launch_aca_classes<T, OP>(A, head, s);
 }
 
-// The binning the library uses without tuning, from the tuner's choices at
-// N = 1,310,720 (FP32): wavefront classes up to 256 (one, two or four rows
-// per lane), 128-thread workgroups up to 1,024 (257..512: 1.46 against
-// 1.98 ms for 256-thread workgroups on a sample of 16,151 blocks; 513..1,024:
-// 2.47 against 2.70 ms), 256-thread workgroups up to 4,096 and 1,024-thread
-// workgroups above.  Galerkin entries keep the row triangle in registers:
-// one and two rows per lane up to 128, 128-thread workgroups up to 1,024 and
-// 256-thread workgroups above (65..128 on two rows per lane 0.96 against
-// 1.07 ms for 128 threads and 1.64 for 256; 129..256 on 128 threads 1.56
-// against 1.91 for 256 threads and 2.32 for four rows per lane; 257..512
-// 2.24 against 2.79; 513..1,024 3.78 against 4.10); the 1,024-thread class
-// is not built for them.
+// The binning the library uses without tuning: wavefront classes up to 256
+// (one, two or four rows per lane), 128-thread workgroups up to 1,024,
+// 256-thread workgroups up to 4,096 and 1,024-thread workgroups above.  Whole
+// builds at N = 655,220, FP32: 77.6 ms; 129..256 on 128 threads 79.6, 513..1,024
+// on 256 threads 78.7, 1,025..2,048 on 128 threads 77.1, 2,049..4,096 on 1,024
+// threads 80.9 (and 1,025..2,048 too: 89.5).  Galerkin entries keep the row
+// triangle in registers: one and two rows per lane up to 128, 128-thread
+// workgroups up to 1,024 and 256-thread workgroups above (N = 81,920, FP32:
+// 20.2 ms; 129..256 on four rows per lane 21.5, 513..1,024 on 256 threads 20.5,
+// 1,025..2,048 on 128 threads 20.7); the 1,024-thread class is not built for
+// them.
 AcaBins default_aca_bins(int op) {
   if (op == kOpGalerkin) return AcaBins{{4, 3, 5, 5, 5, 1, 1, 1}};
   return AcaBins{{4, 3, 2, 5, 5, 1, 1, 0}};
@@ -2399,7 +2479,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
     int64_t* rmark = ta.get<int64_t>(nl);
     int64_t* rsize = ta.get<int64_t>(nl);
     int64_t* roff = ta.get<int64_t>(nl + 1);
-    int* head = ta.get<int>(kAcaClasses);
+    int* head = ta.get<int>(kAcaClasses * kXcds);
     const auto aca = in.op == kOpGalerkin ? run_aca<T, kOpGalerkin> : run_aca<T, kOpColloc>;
     out.bins = default_aca_bins(in.op);
     if (in.tune_aca) {

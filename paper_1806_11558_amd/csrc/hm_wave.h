@@ -53,6 +53,55 @@ __device__ inline A wsum(A v) {
   return rdl_v(v, 63);
 }
 
+// Sums of N = 4 or 8 values over the wavefront together: every step halves the
+// values by handing each half of the lanes one value of a pair, first between
+// the halves and quarters of the wavefront by lane swaps (three instructions
+// per pair), then within rows of 16 lanes.  The sum of value k is in lane
+// k * 64 / N, in a fixed order; 34 instructions for eight values where eight
+// wsum take 144.
+__device__ inline double swap_add32(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a);
+  const unsigned long long y = (unsigned long long)__double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+__device__ inline double swap_add16(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a);
+  const unsigned long long y = (unsigned long long)__double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+__device__ inline double swap_add8(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a);
+  const unsigned long long y = (unsigned long long)__double_as_longlong(b);
+  int r[2], k[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int u = (int)(unsigned)(x >> (32 * h)), v = (int)(unsigned)(y >> (32 * h));
+    r[h] = __builtin_amdgcn_update_dpp(0, u, 0x128, 0xF, 0x3, false);      // row_ror:8
+    r[h] = __builtin_amdgcn_update_dpp(r[h], v, 0x128, 0xF, 0xC, false);
+    k[h] = __builtin_amdgcn_update_dpp(u, v, 0xE4, 0xF, 0xC, false);       // lanes 8..15: v
+  }
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)k[1] << 32) | (unsigned)k[0])) +
+         __longlong_as_double((long long)(((unsigned long long)(unsigned)r[1] << 32) | (unsigned)r[0]));
+}
+__device__ inline double wsums(const double (&p)[4]) {
+  return rowsum(swap_add16(swap_add32(p[0], p[2]), swap_add32(p[1], p[3])));
+}
+__device__ inline double wsums(const double (&p)[8]) {
+  const double a = swap_add16(swap_add32(p[0], p[4]), swap_add32(p[2], p[6]));
+  const double b = swap_add16(swap_add32(p[1], p[5]), swap_add32(p[3], p[7]));
+  double v = swap_add8(a, b);
+  v += dpp_v<0xB1, 0xF>(v);
+  v += dpp_v<0x4E, 0xF>(v);
+  v += dpp_v<0x141, 0xF>(v);
+  return v;
+}
+
 // Orders a wavefront's own memory accesses: what its lanes wrote before, all
 // of them read after (no instruction: a wavefront's accesses go in order).
 __device__ inline void wave_order() {
@@ -62,4 +111,3 @@ __device__ inline void wave_order() {
 }
 
 }  // namespace hm
-
