@@ -547,61 +547,68 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_scatter(
 }
 }  // namespace
 
-// Up to kSortOne pairs: a bitonic sort of (key, position) in the LDS of one
-// workgroup, stable because the position breaks ties (keys have no bits at or
-// above `bits`, rounded up to eight, so comparing them whole is the same
-// order).  One launch where eight radix passes take sixteen or more.
-constexpr int kSortOne = 4096, kSortOneThreads = 1024;
-__global__ __launch_bounds__(kSortOneThreads) void k_sort_one(uint64_t* keys, int32_t* vals, int n,
-                                                              int np2) {
-  __shared__ uint64_t k[kSortOne];
-  __shared__ int32_t p[kSortOne];
-  for (int i = threadIdx.x; i < np2; i += kSortOneThreads) {
-    k[i] = i < n ? keys[i] : ~uint64_t(0);
-    p[i] = i;                                           // padding sorts last: its positions are the largest
+// Up to kSortRank pairs: the position of a pair is the number of pairs in front
+// of it, counted against all keys (equal keys: by index, so the order is
+// stable; keys have no bits at or above `bits`, so comparing them whole is the
+// same order).  Lane = pair, the wavefronts of a workgroup share the keys,
+// which come as scalar loads, two instructions per comparison (keys staged in
+// LDS or handed round by readlane took longer: 14 and 12 us at 2,880 pairs).
+// 1,280 pairs 7 us and 2,880 12 us, in one workgroup's LDS by a bitonic network
+// 39 us, by eight radix passes more than 100; at 16,000 pairs it saves nothing
+// over the radix passes.
+constexpr int kSortRank = 8192, kSortThreads = 1024, kSortWaves = kSortThreads / 64;
+__global__ __launch_bounds__(kSortThreads) void k_sort_rank(const uint64_t* __restrict__ keys,
+                                                            const int32_t* __restrict__ vals, int n,
+                                                            uint64_t* __restrict__ kout,
+                                                            int32_t* __restrict__ vout) {
+  __shared__ int part[kSortWaves][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = blockIdx.x * 64, i = i0 + lane;
+  const uint64_t mine = keys[min(i, n - 1)];
+  const int per = (n + kSortWaves - 1) / kSortWaves;
+  const int j0 = min(n, wave * per), j1 = min(n, j0 + per);
+  int r = 0;
+  // keys in front of, among and behind the workgroup's own
+#pragma unroll 8
+  for (int j = j0; j < min(j1, i0); ++j) r += keys[j] <= mine;
+  for (int j = max(j0, i0); j < min(j1, i0 + 64); ++j) {
+    const uint64_t k = keys[j];
+    r += k < mine || (k == mine && j < i);
   }
+#pragma unroll 8
+  for (int j = max(j0, i0 + 64); j < j1; ++j) r += keys[j] < mine;
+  part[wave][lane] = r;
   __syncthreads();
-  for (int len = 2; len <= np2; len <<= 1)
-    for (int d = len >> 1; d > 0; d >>= 1) {
-      for (int t = threadIdx.x; t < np2 / 2; t += kSortOneThreads) {
-        const int i = 2 * t - (t & (d - 1)), j = i + d;
-        const bool up = (i & len) == 0;
-        const uint64_t ki = k[i], kj = k[j];
-        const int32_t pi = p[i], pj = p[j];
-        const bool gt = ki > kj || (ki == kj && pi > pj);
-        if (gt == up) {
-          k[i] = kj;
-          k[j] = ki;
-          p[i] = pj;
-          p[j] = pi;
-        }
-      }
-      __syncthreads();
-    }
-  int32_t v[kSortOne / kSortOneThreads];
+  if (wave == 0 && i < n) {
+    int pos = 0;
 #pragma unroll
-  for (int q = 0; q < kSortOne / kSortOneThreads; ++q) {
-    const int i = threadIdx.x + q * kSortOneThreads;
-    v[q] = i < n ? vals[p[i]] : 0;
+    for (int w = 0; w < kSortWaves; ++w) pos += part[w][lane];
+    kout[pos] = mine;
+    vout[pos] = vals[i];
   }
-  __syncthreads();                                      // every value is read
-#pragma unroll
-  for (int q = 0; q < kSortOne / kSortOneThreads; ++q) {
-    const int i = threadIdx.x + q * kSortOneThreads;
-    if (i < n) {
-      keys[i] = k[i];
-      vals[i] = v[q];
-    }
+}
+
+__global__ void k_copy_pairs(const uint64_t* __restrict__ ki, const int32_t* __restrict__ vi, int n,
+                             uint64_t* __restrict__ ko, int32_t* __restrict__ vo) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) {
+    ko[i] = ki[i];
+    vo[i] = vi[i];
   }
 }
 
 void radix_sort_u64_i32(uint64_t* keys, int32_t* vals, int64_t n, int bits, hipStream_t s) {
   if (n <= 1 || bits <= 0) return;
-  if (n <= kSortOne) {
-    int np2 = 2;
-    while (np2 < n) np2 <<= 1;
-    k_sort_one<<<1, kSortOneThreads, 0, s>>>(keys, vals, (int)n, np2);
+  if (n <= kSortRank) {
+    uint64_t* k2 = dalloc_t<uint64_t>(n, s);
+    int32_t* v2 = dalloc_t<int32_t>(n, s);
+    k_sort_rank<<<(unsigned)ceil_div(n, 64), kSortThreads, 0, s>>>(keys, vals, (int)n, k2, v2);
     HM_LAUNCH_CHECK();
+    k_copy_pairs<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(k2, v2, (int)n, keys, vals);
+    HM_LAUNCH_CHECK();
+    dfree(k2, s);
+    dfree(v2, s);
     return;
   }
   const int passes = (bits + 7) / 8;

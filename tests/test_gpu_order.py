@@ -1,5 +1,5 @@
 """Morton order bit-exact at the sizes where the sort and the scans change form
-(one workgroup up to 4,096 pairs, tile counts added in the scatter up to 65,536,
+(counted up to 8,192 pairs, tile counts added in the scatter up to 65,536,
 scanned above), with tied keys, and for several geometries of uneven size."""
 import numpy as np
 import pytest
@@ -22,7 +22,7 @@ def _mesh(n, seed):
     return with_near_duplicates(V, T, d, 1e-9, seed) if d else (V, T)
 
 
-@pytest.mark.parametrize("n", [2, 4095, 4096, 4097, 65536, 65537])
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 4096, 4097, 8191, 8192, 8193, 65536, 65537])
 def test_order_at_sort_edges(n):
     import paper_1806_11558_amd as hm
     from oracle import bem, cluster
