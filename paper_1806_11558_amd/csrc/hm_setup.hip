@@ -466,17 +466,21 @@ __global__ __launch_bounds__(256) void k_near(Geom<T> g, const int32_t* __restri
   }
 }
 
-// Singular Galerkin entries of the near field (pairs that share a vertex,
-// left at 0 by k_near): one workgroup per slice as in k_near.  The touching
-// pairs of up to kSingChunk entries are listed in LDS, then each row of 16
-// lanes takes one pair, nine of its 144 outer points per lane.  Bound by
-// FP64 arithmetic.  N = 81,920 (1.07 million pairs): 10.8 ms with a wavefront
-// per pair, whose third round of points fills 16 of 64 lanes and which repeats
-// the set-up of the inner triangle in 64 lanes, 5.0 ms with a row.
-constexpr int kSingChunk = 4096;
+// Singular Galerkin entries of the near field (pairs that share a vertex, left
+// at 0 by k_near).  A workgroup takes kSingSlices slices (lane = row: a slice of
+// leaf panels has at most 64), 64 columns of each at a time: its wavefronts
+// write a mask of touching rows per column, the masks are expanded to a list of
+// pairs, and each row of 16 lanes takes one pair, nine of its 144 outer points
+// per lane.  Bound by FP64 arithmetic.  N = 81,920 (1.07 million pairs, nine per
+// slice): 10.8 ms with a wavefront per pair, whose third round of points fills
+// 16 of 64 lanes and which repeats the set-up of the inner triangle in 64 lanes;
+// 5.0 ms with a row per pair and one slice per workgroup, whose last round was
+// mostly empty; 4.2 ms with eight (two wavefronts per SIMD: 4.6, four, with 54
+// registers spilled: 4.4).
+constexpr int kSingSlices = 8, kSingList = 1024;
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_near_singular(Geom<T> g, GaussRule R,
+__global__ __launch_bounds__(256, 3) void k_near_singular(Geom<T> g, GaussRule R,
                                                        const int32_t* __restrict__ sidx,
                                                        const int32_t* __restrict__ ib,
                                                        const int32_t* __restrict__ ilf, int64_t np,
@@ -484,66 +488,100 @@ __global__ __launch_bounds__(256) void k_near_singular(Geom<T> g, GaussRule R,
                                                        const Cluster* __restrict__ cl, LeafTab L,
                                                        const int64_t* __restrict__ offI,
                                                        T* __restrict__ D) {
-  __shared__ int32_t vr[3][kMaxLeaf], vc[3][kMaxLeaf];
-  __shared__ uint16_t pair[kSingChunk];
-  __shared__ int npair;
+  __shared__ unsigned long long mask[kSingSlices * 64];
+  __shared__ int64_t off[kSingSlices];
+  __shared__ int lo[kSingSlices], ld[kSingSlices], sx[kSingSlices], sn[kSingSlices];
+  __shared__ uint16_t list[kSingList];                  // slice, column and row of a pair
+  __shared__ int wtot[4];
   __shared__ TriJ tri[16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int64_t p = blockIdx.x; p < np; p += gridDim.x) {
-    const int32_t u = sidx[p];
-    const int b = ib[u], lf = ilf[u];
-    const Cluster sig = cl[dns[b].y];
-    const int n = sig.y - sig.x;
-    const int ld = leaf_ld(L, lf), m = L.m[lf], lo = L.lo[lf];
-    T* dst = D + offI[p];
-    const bool staged = n <= kMaxLeaf;
-    if (staged) {
-      for (int j = threadIdx.x; j < n; j += blockDim.x)
-        for (int k = 0; k < 3; ++k) vc[k][j] = g.vid[(int64_t)k * g.n + sig.x + j];
-      for (int i = threadIdx.x; i < m; i += blockDim.x)
-        for (int k = 0; k < 3; ++k) vr[k][i] = g.vid[(int64_t)k * g.n + lo + i];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int64_t p0 = (int64_t)blockIdx.x * kSingSlices; p0 < np; p0 += (int64_t)gridDim.x * kSingSlices) {
+    if (threadIdx.x < kSingSlices) {
+      const int64_t p = p0 + threadIdx.x;
+      int n = 0;
+      if (p < np) {
+        const int32_t u = sidx[p];
+        const int lf = ilf[u];
+        const Cluster sig = cl[dns[ib[u]].y];
+        n = sig.y - sig.x;
+        lo[threadIdx.x] = L.lo[lf];
+        ld[threadIdx.x] = leaf_ld(L, lf) | L.m[lf] << 8;
+        sx[threadIdx.x] = sig.x;
+        off[threadIdx.x] = offI[p];
+      }
+      sn[threadIdx.x] = n;
     }
-    for (int c0 = 0; c0 < ld * n; c0 += kSingChunk) {
-      if (threadIdx.x == 0) npair = 0;
-      __syncthreads();
-      const int c1 = min(c0 + kSingChunk, ld * n);
-      for (int e0 = c0 + wave * 64; e0 < c1; e0 += blockDim.x) {
-        const int e = e0 + lane;
-        const int i = e % ld, j = e / ld;
-        bool t = false;
-        if (e < c1 && i < m) {
-          if (staged) {
-            t = lo + i == sig.x + j;
-            for (int a = 0; a < 3; ++a)
-              for (int c = 0; c < 3; ++c) t = t || vr[a][i] == vc[c][j];
-          } else {
-            t = touching(g, lo + i, sig.x + j);
+    __syncthreads();
+    int nmax = 0;
+#pragma unroll
+    for (int k = 0; k < kSingSlices; ++k) nmax = max(nmax, sn[k]);
+    for (int j0 = 0; j0 < nmax; j0 += 64) {             // uniform over the workgroup
+      for (int k = wave; k < kSingSlices; k += 4) {
+        unsigned long long mine = 0;
+        const int nc = __builtin_amdgcn_readfirstlane(min(sn[k] - j0, 64));
+        if (nc > 0) {
+          const int m = ld[k] >> 8, i = lo[k] + min(lane, m - 1), j = sx[k] + j0 + min(lane, nc - 1);
+          int r[3], c[3];
+          for (int a = 0; a < 3; ++a) {
+            r[a] = g.vid[(int64_t)a * g.n + i];
+            c[a] = g.vid[(int64_t)a * g.n + j];
+          }
+          for (int q = 0; q < nc; ++q) {
+            bool t = i == sx[k] + j0 + q;
+            for (int b = 0; b < 3; ++b) {
+              const int v = __builtin_amdgcn_readlane(c[b], q);
+              for (int a = 0; a < 3; ++a) t = t || r[a] == v;
+            }
+            const unsigned long long bits = __ballot(t && lane < m);
+            mine = lane == q ? bits : mine;
           }
         }
-        const unsigned long long mask = __ballot(t);
-        int at = 0;
-        if (lane == 0 && mask) at = atomicAdd(&npair, __popcll(mask));
-        at = __shfl(at, 0, 64) + __popcll(mask & ((1ull << lane) - 1));
-        if (t) pair[at] = (uint16_t)(e - c0);
+        mask[k * 64 + lane] = mine;
       }
       __syncthreads();
-      const int np16 = npair;
-      for (int q0 = wave * 4; q0 < np16; q0 += 16) {       // uniform over the wavefront
-        const int q = q0 + lane / 16;
-        const int e = c0 + pair[min(q, np16 - 1)];
-        TriJ& J = tri[threadIdx.x / 16];
-        {
-          TriJ Jr;                                         // the same in all lanes of a row
-          singular_setup(g, lo + e % ld, sig.x + e / ld, Jr);
-          wave_order();                                // after the last pair's reads
-          if ((lane & 15) == 0) J = Jr;
-          wave_order();
-        }
-        const double v = rowsum(singular_points(R, J, lane & 15, 16));
-        if (q < np16 && (lane & 15) == 0) dst[e] = (T)v;
+      // thread = two columns: where their pairs start among all
+      const int e = 2 * threadIdx.x;
+      const int c0 = __popcll(mask[e]), c1 = __popcll(mask[e + 1]);
+      int inc = c0 + c1;
+      for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += o;
       }
-      __syncthreads();                                  // before the list and the slice are replaced
+      if (lane == 63) wtot[wave] = inc;
+      __syncthreads();
+      int first = inc - c0 - c1, total = 0;
+      for (int w = 0; w < 4; ++w) {
+        first += w < wave ? wtot[w] : 0;
+        total += wtot[w];
+      }
+      for (int base = 0; base < total; base += kSingList) {      // uniform over the workgroup
+        const int cnt = min(kSingList, total - base);
+        int at = first - base;
+        for (int h = 0; h < 2; ++h)
+          for (unsigned long long b = mask[e + h]; b; b &= b - 1, ++at)
+            if (at >= 0 && at < cnt) list[at] = (uint16_t)((e + h) * 64 + __ffsll(b) - 1);
+        __syncthreads();
+        for (int q0 = wave * 4; q0 < cnt; q0 += 16) {            // uniform over the wavefront
+          const int q = q0 + lane / 16;
+          const int x = list[min(q, cnt - 1)];
+          const int k = x >> 12, col = j0 + (x >> 6 & 63), row = x & 63;
+          TriJ& J = tri[threadIdx.x / 16];
+          {
+            TriJ Jr;                                             // the same in all lanes of a row
+            singular_setup(g, lo[k] + row, sx[k] + col, Jr);
+            wave_order();                                        // after the last pair's reads
+            if ((lane & 15) == 0) J = Jr;
+            wave_order();
+          }
+          const double v = rowsum(singular_points(R, J, lane & 15, 16));
+          if (q < cnt && (lane & 15) == 0) D[off[k] + (int64_t)col * (ld[k] & 255) + row] = (T)v;
+        }
+        __syncthreads();                                         // before the list is replaced
+      }
+      __syncthreads();                                           // before the masks are replaced
     }
+    __syncthreads();                                             // before the slices are replaced
   }
 }
 
@@ -2381,7 +2419,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
       k_near<T, kOpGalerkin><<<gn, 256, 0, s>>>(g, PD.sidx, PD.ib, PD.ilf, PD.np, in.dns, in.cl, L,
                                                 PD.offI, D);
       HM_LAUNCH_CHECK();
-      k_near_singular<T><<<gn, 256, 0, s>>>(g, gauss_rule01(), PD.sidx, PD.ib, PD.ilf, PD.np,
+      k_near_singular<T><<<(unsigned)std::min<int64_t>(ceil_div(PD.np, kSingSlices), 1 << 20), 256, 0, s>>>(g, gauss_rule01(), PD.sidx, PD.ib, PD.ilf, PD.np,
                                             in.dns, in.cl, L, PD.offI, D);
     } else {
       k_near<T, kOpColloc><<<gn, 256, 0, s>>>(g, PD.sidx, PD.ib, PD.ilf, PD.np, in.dns, in.cl, L,
