@@ -173,7 +173,7 @@ def setup_roofline(o, form, operator="collocation"):
     entries + ACA rows and columns) x FLOPS_PER_ENTRY over their time.  The
     fraction of the ALU peak is a lower bound on how well the setup uses the
     chip: the counters show the ACA's workgroup classes bound by the bytes
-    they stream and its wavefront classes by step latency (`note`)."""
+    they stream and its wavefront classes by the instructions of a step (`note`)."""
     st = o["stats"]
     ms = o["setup_phases_ms"]["near_field"] + o["setup_phases_ms"]["aca"]
     ent = st["dense_entries"] + st["aca_entry_evals"]
@@ -184,7 +184,7 @@ def setup_roofline(o, form, operator="collocation"):
             "phases": "near_field + aca", "ms": round(ms, 3),
             "note": "ACA workgroup classes (blocks above 256) stream source records and "
                     "earlier terms at 6-7.5 TB/s by FETCH_SIZE; wavefront classes are bound "
-                    "by step latency (profiles/setup_k_aca_k_near_f32_icosphere_L8_traffic.md)"}
+                    "by the instructions of a step (profiles/setup_k_aca_k_near_f32_icosphere_L8_traffic.md)"}
 
 
 def _timed(torch, fn, reps):
