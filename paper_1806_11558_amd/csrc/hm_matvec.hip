@@ -1207,8 +1207,10 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
         // a column reads the slice's last one and adds zero), so all their
         // loads are in flight together: one column at N = 32,000, leaf 32 and
         // 64, FP32 183 -> 174 and 190 -> 185 us, FP16 129 -> 121 and 150 -> 142
-        // against a column group at a time
-        constexpr int UNR = 4;
+        // against a column group at a time.  Two for two double columns of
+        // float or half slices, whose sums take 16 registers more (N = 81,920,
+        // leaf 32: FP32 814 -> 799, FP16 530 -> 503 us)
+        constexpr int UNR = sizeof(A) == 8 && sizeof(T) < 8 && NR == 2 ? 2 : 4;
         const int ngrp = (I.w + C - 1) / C;
         for (int q0 = 0; q0 < ngrp; q0 += UNR) {
           typename Gran<T>::E s[UNR][G];
@@ -1389,7 +1391,8 @@ __global__ __launch_bounds__(256) void k_tr2_sum(MvLeaves L, int S, const A* __r
 
 // ------------------------------------------------------------------ host side
 // Transposed products of one or two columns run on the matrix cores up to this
-// many leaves (64 for one column in single precision), on the vector units above.  Small products wait for loads, and
+// many leaves (FP64 factors, or two columns in single precision; otherwise
+// fewer), on the vector units above.  Small products wait for loads, and
 // the matrix kernels have all the loads of 64 columns in flight; large ones are
 // bound by HBM, where the vector kernels use fewer, longer wavefronts.  One and
 // two columns, vector -> matrix: 64 leaves of 53 rows, FP64 64 -> 41 and 71 ->
@@ -1397,8 +1400,11 @@ __global__ __launch_bounds__(256) void k_tr2_sum(MvLeaves L, int S, const A* __r
 // 64 -> 47, FP32 33 -> 32 and 41 -> 35, of 62 rows, FP32 40 -> 43 and 55 -> 47;
 // 256 leaves of 45 rows, FP64 105 -> 112 and 120 -> 126, FP32 65 -> 67 and
 // 70 -> 69; N = 81,920, leaf 64, FP32 538 -> 614 and 598 -> 665.
-template <typename A, int NR>
-constexpr int64_t kTrMfmaLeaves = sizeof(A) == 4 && NR == 1 ? 64 : 128;
+// FP32 factors with double vectors: 64 leaves of 53 rows 37 -> 36 and 46 -> 40,
+// 128 leaves of 45 rows 40 -> 46 and 50 -> 50 us.
+template <typename TL, typename A, int NR>
+constexpr int64_t kTrMfmaLeaves =
+    sizeof(TL) == 8 || (sizeof(A) == 4 && NR == 2) ? 128 : 64;
 
 template <typename TD, typename TL, typename A, typename VT, int NR>
 static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int nv,
@@ -1408,7 +1414,7 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
   A* xt = static_cast<A*>(P.xt);
   MvProfile* pr = P.prof;
   if (pr) HM_HIP(hipEventRecord(pr->ev[0], s));
-  const bool tmx = NR >= 4 || P.L.nleaf <= kTrMfmaLeaves<A, NR>;   // transposed, on the matrix cores
+  const bool tmx = NR >= 4 || P.L.nleaf <= kTrMfmaLeaves<TL, A, NR>;   // transposed, on the matrix cores
   if (transposed ? tmx : NR >= 4)
     k_gather_x<VT, A, NR><<<(unsigned)std::min<int64_t>(P.L.nleaf, 1 << 20), 256, 0, s>>>(
         x, nrhs, k0, nv, P.perm, P.L, z, xt);
