@@ -989,7 +989,8 @@ __device__ void aca_wg(const AcaArgs<T>& A, int b, AcaShared<T, NT>& sh) {
   double s2 = 0.0;
   bool cap_hit = false;
   while (true) {
-    if (tid < r) sh.a[tid] = ld_at(U + istar, (uint32_t)(tid * m) * (uint32_t)sizeof(T));
+    // (more terms than threads are possible: ranks up to kMaxRank, NT = 128)
+    for (int l = tid; l < r; l += NT) sh.a[l] = ld_at(U + (int64_t)l * m + istar, 0u);
     __syncthreads();
     Tgt<T, OP> ti;
     if constexpr (OP == kOpColloc)
@@ -1091,12 +1092,12 @@ __device__ void aca_wg(const AcaArgs<T>& A, int b, AcaShared<T, NT>& sh) {
       const double t = wsums(pvv);                     // term l0 + k in lane 8 k
       if ((lane & 7) == 0 && l0 + lane / 8 < r) sh.dv[l0 + lane / 8][wave] = t;
     }
-    if (tid < r) sh.a[tid] = ld_at(V + jstar, (uint32_t)(tid * n) * (uint32_t)sizeof(T));
+    for (int l = tid; l < r; l += NT) sh.a[l] = ld_at(V + (int64_t)l * n + jstar, 0u);
     __syncthreads();
-    if (tid < r) {
+    for (int l = tid; l < r; l += NT) {
       double t = 0.0;
-      for (int w = 0; w < (NT / 64); ++w) t += sh.dv[tid][w];
-      sh.dt[tid] = tid < kTermBatch ? t / (double)delta : t;
+      for (int w = 0; w < (NT / 64); ++w) t += sh.dv[l][w];
+      sh.dt[l] = l < kTermBatch ? t / (double)delta : t;
     }
     __syncthreads();
     // residual column u_r; the cross terms sum_l (u_l . u_r)(v_l . v_r) are
