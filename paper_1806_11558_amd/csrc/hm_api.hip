@@ -318,6 +318,8 @@ struct hm_handle {
     // build can leave work in flight; the build stream may no longer exist)
     (void)hipDeviceSynchronize();
     for (auto& q : owned) cache_put(q.first, q.second);
+    // likewise the stream of the last graph solve
+    if (sws) sws->free_stream = nullptr;
   }
   MvLeaves leaves() const { return MvLeaves{leaf_lo, leaf_m, ldpre, nleaf}; }
   MvPlan plan() const {
