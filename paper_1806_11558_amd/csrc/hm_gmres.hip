@@ -44,7 +44,8 @@ GsShape gs_shape(int64_t n, int nr, bool coarse) {
   et = std::min<int64_t>(std::max<int64_t>(et, 128), kGsElems);
   g.tr = coarse ? kGsElems : std::max<int64_t>(1, et / nr);
   g.tiles = (int)ceil_div(n, g.tr);
-  g.fold = (int64_t)g.tiles * nr <= 160;
+  // (coarse: the second array of partial sums that folding takes is left out)
+  g.fold = !coarse && (int64_t)g.tiles * nr <= 160;
   return g;
 }
 

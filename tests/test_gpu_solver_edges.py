@@ -36,3 +36,31 @@ def test_graph_workspace_outlives_its_stream():
         hm.release_memory()
         after = torch.cuda.mem_get_info()[0]
     assert before - after < 64 << 20, (before, after)
+
+
+@pytest.mark.parametrize("n,fits", [(9978, True), (9979, False)])
+def test_largest_fixed_workspace(n, fits):
+    """16 columns at restart 100: the largest system whose workspace
+    (8 (restart + 7) n nrhs bytes, the partial sums of 2,048-row tiles and the small
+    arrays) fits the 134,217,728 bytes of the fixed array, and one unknown more."""
+    import paper_1806_11558_amd as hm
+    from synthetic import icosphere, normal_columns
+    V, T = icosphere(5)
+    T = T[:n]
+    say("fixed workspace", n)
+    H = hm.HMatrix(V, T, leaf_size=32, eps=1e-6, precision="f64")
+    f = torch.tensor(normal_columns(n, 16, seed=6), device=DEV)
+    sp = hm.SolveParams(tol=1e-8, restart=100, max_iter=300, transpose=0, use_x0=0, flags=0,
+                        refine=0, inner_tol=0.0)
+    a, b = torch.empty_like(f), torch.empty_like(f)
+    sta, ia = hm.hm_solve(H._h, f, a, sp)
+    if fits:
+        stb, ib = hm.hm_solve_noalloc(H._h, f, b, sp)
+        assert sta == stb == hm.HM_OK and ia.iters == ib.iters
+        assert torch.equal(a, b)
+        assert rel2(H.matvec(b).cpu().numpy(), f.cpu().numpy()) <= 1.5e-8
+    else:
+        with pytest.raises(hm.HMError) as e:
+            hm.hm_solve_noalloc(H._h, f, b, sp)
+        assert e.value.status == hm.HM_ERR_ARG
+    H.free()
