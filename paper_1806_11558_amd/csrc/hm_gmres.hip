@@ -46,6 +46,7 @@ GsShape gs_shape(int64_t n, int nr, bool coarse) {
   g.tiles = (int)ceil_div(n, g.tr);
   // (coarse: the second array of partial sums that folding takes is left out)
   g.fold = !coarse && (int64_t)g.tiles * nr <= 160;
+  g.coarse = coarse;
   return g;
 }
 
@@ -202,6 +203,48 @@ __global__ __launch_bounds__(kGT) void k_gs_update(const double* __restrict__ Q,
         }
       }
     }
+  }
+}
+
+// The dots and the updates of coarse tiles: partial dots of one vector and one
+// tile per workgroup (thread = column and row group), and out = in - Q h over
+// all elements.
+template <typename W>
+__global__ __launch_bounds__(kGT) void k_gs_dots(const double* __restrict__ Q, int64_t ldq,
+                                                 const int64_t* __restrict__ jd, int nk,
+                                                 const W* __restrict__ w, GsShape G,
+                                                 double* __restrict__ part) {
+  __shared__ double sum[kGT];
+  const int k = blockIdx.y;
+  if (k >= (jd ? (int)jd[0] + 1 : nk)) return;          // uniform over the workgroup
+  const double* q = Q + (int64_t)k * ldq;
+  const int per = kGT / G.nr, c = threadIdx.x % G.nr, r0 = threadIdx.x / G.nr;   // nr <= 256
+  double acc = 0.0;
+  if (r0 < per) {
+    const int64_t end = min((int64_t)(blockIdx.x + 1) * G.tr, G.n);
+#pragma unroll 4
+    for (int64_t i = (int64_t)blockIdx.x * G.tr + r0; i < end; i += per)
+      acc += q[i * G.nr + c] * (double)w[i * G.nr + c];
+  }
+  sum[threadIdx.x] = acc;
+  for (int s = 1; s < per; s <<= 1) {
+    __syncthreads();
+    if (r0 % (2 * s) == 0 && r0 + s < per) sum[threadIdx.x] += sum[threadIdx.x + s * G.nr];
+  }
+  if (r0 == 0) part[((int64_t)k * G.nr + c) * G.tiles + blockIdx.x] = sum[threadIdx.x];
+}
+template <typename W>
+__global__ __launch_bounds__(kGT) void k_gs_sub(const double* __restrict__ Q, int64_t ldq,
+                                                const int64_t* __restrict__ jd, int nk, const W* in,
+                                                const double* __restrict__ h, int nr, double* out) {
+  const int nv = jd ? (int)jd[0] + 1 : nk;
+  for (int64_t e = blockIdx.x * (int64_t)kGT + threadIdx.x; e < ldq;
+       e += (int64_t)gridDim.x * kGT) {
+    const int c = (int)(e % nr);
+    double v = (double)in[e];
+#pragma unroll 4
+    for (int k = 0; k < nv; ++k) v -= Q[(int64_t)k * ldq + e] * h[(int64_t)k * nr + c];
+    out[e] = v;
   }
 }
 
@@ -383,18 +426,38 @@ static void gs_arnoldi(const GsArgs& a, const W* win, X* xq, int j, int nkmax, h
     k_gs_final<<<fin, 256, 0, s>>>(part, jd, cnt, G.nr, G.tiles, out);
     HM_LAUNCH_CHECK();
   };
-  k_gs_first<W><<<dim3(G.tiles, kg), kGT, 0, s>>>(a.Q, tot, a.jd, nk, win, G, a.part);
-  HM_LAUNCH_CHECK();
-  total(a.part, nk, a.jd, h2);
-  // several workgroups per tile only where tiles alone leave the chip idle:
-  // each repeats the update, which reads the whole basis
-  k_gs_update<W, false><<<dim3(G.tiles, G.fold ? kg : 1), kGT, 0, s>>>(
-      a.Q, tot, a.jd, nk, win, a.w1, G, a.part, h2, h1, a.part2);
-  HM_LAUNCH_CHECK();
-  total(a.part2, nk, a.jd, h2);
-  k_gs_update<double, true><<<dim3(G.tiles, 1), kGT, 0, s>>>(a.Q, tot, a.jd, nk, a.w1, a.w1, G,
-                                                             a.part2, h2, h2, a.part);
-  HM_LAUNCH_CHECK();
+  if (G.coarse) {
+    // 16 columns at N = 9,978 are five tiles, which below would be a workgroup
+    // each (restart 100, 44 steps: 48 ms below, 8.3 here, 8.6 with fine tiles; 64
+    // columns at N = 1,280, one tile, restart 196, 31 steps: 79 and 8.8)
+    const dim3 g(G.tiles, nkmax);
+    const unsigned ge = grid_for(tot, kGT, 8192);
+    k_gs_dots<W><<<g, kGT, 0, s>>>(a.Q, tot, a.jd, nk, win, G, a.part);
+    HM_LAUNCH_CHECK();
+    total(a.part, nk, a.jd, h1);
+    k_gs_sub<W><<<ge, kGT, 0, s>>>(a.Q, tot, a.jd, nk, win, h1, G.nr, a.w1);
+    HM_LAUNCH_CHECK();
+    k_gs_dots<double><<<g, kGT, 0, s>>>(a.Q, tot, a.jd, nk, a.w1, G, a.part);
+    HM_LAUNCH_CHECK();
+    total(a.part, nk, a.jd, h2);
+    k_gs_sub<double><<<ge, kGT, 0, s>>>(a.Q, tot, a.jd, nk, a.w1, h2, G.nr, a.w1);
+    HM_LAUNCH_CHECK();
+    k_gs_dots<double><<<dim3(G.tiles, 1), kGT, 0, s>>>(a.w1, tot, nullptr, 1, a.w1, G, a.part);
+    HM_LAUNCH_CHECK();
+  } else {
+    k_gs_first<W><<<dim3(G.tiles, kg), kGT, 0, s>>>(a.Q, tot, a.jd, nk, win, G, a.part);
+    HM_LAUNCH_CHECK();
+    total(a.part, nk, a.jd, h2);
+    // several workgroups per tile only where tiles alone leave the chip idle:
+    // each repeats the update, which reads the whole basis
+    k_gs_update<W, false><<<dim3(G.tiles, G.fold ? kg : 1), kGT, 0, s>>>(
+        a.Q, tot, a.jd, nk, win, a.w1, G, a.part, h2, h1, a.part2);
+    HM_LAUNCH_CHECK();
+    total(a.part2, nk, a.jd, h2);
+    k_gs_update<double, true><<<dim3(G.tiles, 1), kGT, 0, s>>>(a.Q, tot, a.jd, nk, a.w1, a.w1, G,
+                                                               a.part2, h2, h2, a.part);
+    HM_LAUNCH_CHECK();
+  }
   total(a.part, 1, nullptr, a.nsum);
   k_gs_next<X><<<grid_for(tot, kGT, 2048), kGT, 0, s>>>(a.Q, tot, a.jd, j, a.w1, G, a.part,
                                                         a.nsum, h1, h2, xq, a.res, a.res_slot, a.seq,

@@ -311,10 +311,13 @@ void matvec_dispatch(const MvPlan& P, int storage, const void* x, void* y, int n
 // ---------------------------------------------------------------- Arnoldi step
 // Row tiles of the solver's dot products (see hm_gmres.hip); coarse: 2,048
 // rows a tile, for a fixed workspace that the finer tiles would not fit.
+// Then there are too few tiles for one workgroup each, and a step takes
+// separate kernels for its dots and updates.
 struct GsShape {
   int64_t n = 0, tr = 0;    // rows, rows per tile
   int nr = 0, tiles = 0;
   bool fold = false;        // every workgroup adds the tile sums it needs itself
+  bool coarse = false;
 };
 GsShape gs_shape(int64_t n, int nr, bool coarse);
 struct GsArgs {
