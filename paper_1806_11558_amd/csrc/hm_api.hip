@@ -670,6 +670,10 @@ void await_step(const int64_t* seq, int64_t want, hipStream_t s) {
 // seen.  That is done for small systems while the estimates, extrapolated by
 // their last reduction, do not end the cycle; a column that has converged
 // goes on without being looked at.
+//
+// A column whose step is not finite (NaN or overflow in its values or in the
+// product) ends its cycle with the steps before it; one whose residual or
+// first step is not takes no further part, and is not converged.
 template <typename Apply, typename Step>
 int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
                const Apply& apply, const Step& step, const std::vector<double>& fn,
@@ -700,7 +704,14 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
     residual(rn);
   }
   conv.assign(nr, 0);
-  for (int c = 0; c < nr; ++c) conv[c] = rel(c, rn[c]) <= tol;
+  std::vector<int> lost(nr, 0);
+  auto judge = [&]() {
+    for (int c = 0; c < nr; ++c) {
+      conv[c] = rel(c, rn[c]) <= tol;
+      if (!std::isfinite(rn[c])) lost[c] = 1;
+    }
+  };
+  judge();
   int total_it = 0;
   // per-column Arnoldi state
   std::vector<double> H((size_t)(m + 1) * m * nr), cs((size_t)m * nr), sn((size_t)m * nr),
@@ -710,15 +721,15 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
   const bool ahead = ws->page && nv <= kLookAhead;
   while (total_it < max_iter) {
     bool all = true;
-    for (int c = 0; c < nr; ++c) all = all && conv[c];
+    for (int c = 0; c < nr; ++c) all = all && (conv[c] || lost[c]);
     if (all) break;
     // Q0 = r / |r| for active columns
-    for (int c = 0; c < nr; ++c) sc[c] = (!conv[c] && rn[c] > 0) ? 1.0 / rn[c] : 0.0;
+    for (int c = 0; c < nr; ++c) sc[c] = (!conv[c] && !lost[c] && rn[c] > 0) ? 1.0 / rn[c] : 0.0;
     HM_HIP(hipMemcpyAsync(scl, sc.data(), nr * sizeof(double), hipMemcpyHostToDevice, s));
     gmres_start(ws->args(), w, scl, s);
     std::vector<int> active(nr);
     for (int c = 0; c < nr; ++c) {
-      active[c] = !conv[c];
+      active[c] = !conv[c] && !lost[c];
       kc[c] = 0;
       std::fill(gv.begin() + (size_t)c * (m + 1), gv.begin() + (size_t)(c + 1) * (m + 1), 0.0);
       gv[(size_t)c * (m + 1)] = rn[c];
@@ -772,8 +783,13 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
         double* gc = gv.data() + (size_t)c * (m + 1);
         gc[j + 1] = -snc[j] * gc[j];
         gc[j] = csc[j] * gc[j];
-        kc[c] = j + 1;
         const double est = rel(c, std::fabs(gc[j + 1]));
+        if (!std::isfinite(est) || !std::isfinite(rr)) {
+          active[c] = 0;                                // kc[c] = j: this step does not count
+          lost[c] = j == 0;
+          continue;
+        }
+        kc[c] = j + 1;
         if (est <= tol || hn == 0.0) {
           active[c] = 0;
         } else {
@@ -805,7 +821,7 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
     }
     ++restarts;
     residual(rn);
-    for (int c = 0; c < nr; ++c) conv[c] = rel(c, rn[c]) <= tol;
+    judge();
   }
   return total_it;
 }

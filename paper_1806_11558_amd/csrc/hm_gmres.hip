@@ -260,8 +260,8 @@ __global__ __launch_bounds__(256) void k_gs_final(const double* __restrict__ par
 }
 
 // q = w / |w| into basis vector j + 1 and into the next product's input (xq,
-// double or float; may be null), 0 for a column of norm 0.  |w|^2 is the sum
-// of part (fold) or nsum.  The first workgroup also writes the step's
+// double or float; may be null), 0 for a column whose norm is 0 or not finite
+// (the host ends such a column).  |w|^2 is the sum of part (fold) or nsum.  The first workgroup also writes the step's
 // coefficients h1 + h2 and |w| per column to res ([(j + 1) nr], [nr]) and
 // then, if seq is given, the number seqv + j + 1 to *seq: res and seq are
 // then host memory that the host polls (else res is device memory whose
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kGT) void k_gs_next(double* __restrict__ Q, int64_t
   const int nr = G.nr, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int c = wave; c < nr; c += kGT / 64) {
     const double v = G.fold ? gs_tile_sum(part, c, G.tiles) : nsum[c];
-    if (lane == 0) hn[c] = sqrt(fmax(v, 0.0));
+    if (lane == 0) hn[c] = v < 0.0 ? 0.0 : sqrt(v);     // NaN stays NaN
   }
   __syncthreads();
   if (blockIdx.x == 0) {
@@ -298,13 +298,14 @@ __global__ __launch_bounds__(kGT) void k_gs_next(double* __restrict__ Q, int64_t
   for (int64_t e = blockIdx.x * (int64_t)kGT + threadIdx.x; e < ldq;
        e += (int64_t)gridDim.x * kGT) {
     const double h = hn[e % nr];
-    const double v = h > 0.0 ? w[e] * (1.0 / h) : 0.0;
+    const double v = h > 0.0 && h < HUGE_VAL ? w[e] * (1.0 / h) : 0.0;
     q[e] = v;
     if (xq) xq[e] = (X)v;
   }
 }
 
-// q0 = r * scale per column, into the basis and the product's input.
+// q0 = r * scale per column, into the basis and the product's input; 0 where
+// the scale is (also if r is not finite).
 template <typename X>
 __global__ __launch_bounds__(kGT) void k_gs_start(const double* __restrict__ r,
                                                   const double* __restrict__ sc, int64_t tot,
@@ -312,7 +313,8 @@ __global__ __launch_bounds__(kGT) void k_gs_start(const double* __restrict__ r,
                                                   X* __restrict__ xq, int64_t* jd, int64_t seqv) {
   for (int64_t e = blockIdx.x * (int64_t)kGT + threadIdx.x; e < tot;
        e += (int64_t)gridDim.x * kGT) {
-    const double v = r[e] * sc[e % nr];
+    const double f = sc[e % nr];
+    const double v = f != 0.0 ? r[e] * f : 0.0;
     q[e] = v;
     if (xq) xq[e] = (X)v;
   }

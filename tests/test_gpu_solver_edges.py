@@ -64,3 +64,44 @@ def test_largest_fixed_workspace(n, fits):
             hm.hm_solve_noalloc(H._h, f, b, sp)
         assert e.value.status == hm.HM_ERR_ARG
     H.free()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("refine", [False, True])
+def test_first_guess_not_finite(graph, refine):
+    """Three columns, the first guess of one is NaN: the others are solved, that one is
+    not converged and costs no steps of its own."""
+    import paper_1806_11558_amd as hm
+    from synthetic import icosphere, normal_columns
+    V, T = icosphere(2)
+    say("NaN in the first guess", graph, refine)
+    H = hm.HMatrix(V, T, leaf_size=32, eps=1e-6, precision="f32" if refine else "f64")
+    f = torch.tensor(normal_columns(H.n, 3, seed=8), device=DEV)
+    x0 = torch.zeros_like(f)
+    _, ref, st = H.solve(f, tol=1e-8, restart=60, refine=refine, graph=graph, x0=x0)
+    assert st == hm.HM_OK
+    x0[7, 1] = float("nan")
+    s, info, st = H.solve(f, tol=1e-8, restart=60, max_iter=1000, refine=refine, graph=graph, x0=x0)
+    assert st == hm.HM_NOT_CONVERGED and info.converged == 2
+    assert info.iters <= ref.iters + 2
+    r = (f - H.matvec(s)).cpu().numpy()
+    F = f.cpu().numpy()
+    for c in (0, 2):
+        assert np.linalg.norm(r[:, c]) <= 1.5e-8 * np.linalg.norm(F[:, c])
+    H.free()
+
+
+def test_product_not_finite():
+    """A triangle given twice: the entries of the pair, 1 / 0, are infinite, so the
+    first product is not finite.  The solve ends there, not converged."""
+    import paper_1806_11558_amd as hm
+    from synthetic import icosphere, normal_columns
+    V, T = icosphere(2)
+    T = np.concatenate([T, T[:1]])
+    say("infinite entries")
+    H = hm.HMatrix(V, T, leaf_size=32, eps=1e-6, precision="f64")
+    f = torch.tensor(normal_columns(H.n, 2, seed=9), device=DEV)
+    s, info, st = H.solve(f, tol=1e-8, max_iter=500)
+    assert st == hm.HM_NOT_CONVERGED and info.converged == 0
+    assert info.iters <= 2
+    H.free()
