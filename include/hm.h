@@ -241,7 +241,8 @@ typedef struct {
   int32_t converged;      /* number of right-hand sides that converged      */
   int32_t ir_steps;       /* refinement corrections applied (0 without)     */
   double rel_residual;    /* max over rhs of the explicit |f - H s| / |f|,
-                             with double products                            */
+                             with double products; NaN if f or a residual is
+                             not finite (such a column is not converged)     */
 } hm_solve_info;
 
 /*

@@ -641,6 +641,9 @@ namespace {
 // step that turns out to be unneeded costs a product.
 constexpr int64_t kLookAhead = 400000;
 
+// |r| / |f|, 0 for a zero right-hand side, NaN where either is (never converged).
+double rel_norm(double r, double f) { return f == 0.0 ? 0.0 : r / f; }
+
 // Waits until the step counter reaches `want`.  The wait ends with the
 // stream's work or with an error of it.
 void await_step(const int64_t* seq, int64_t want, hipStream_t s) {
@@ -696,7 +699,7 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
     gmres_sub(fd, w, nv, w, s);
     norms(w, r);
   };
-  auto rel = [&](int c, double r) { return fn[c] > 0 ? r / fn[c] : 0.0; };
+  auto rel = [&](int c, double r) { return rel_norm(r, fn[c]); };
   if (x_zero) {
     copy_d2d(w, fd, nv * sizeof(double), s);
     rn = fn;
@@ -845,7 +848,7 @@ int cg_core(SolveWs* ws, int64_t n, int nr, double tol, int max_iter, const Appl
   double* rra = ws->hdev + nr;
   double* rrb = ws->hdev + 2 * nr;
   double* active = ws->scl;
-  auto rel = [&](int c, double v) { return fn[c] > 0 ? v / fn[c] : 0.0; };
+  auto rel = [&](int c, double v) { return rel_norm(v, fn[c]); };
   std::vector<double> rr(nr), act(nr), rprev;
   // r = b - H x, rra = |r|^2 per column, rn = |r|
   auto residual = [&]() {
@@ -1277,7 +1280,7 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
     std::vector<double> fn, rn;
     std::vector<int> conv(nr, 0);
     norms(fsrc, fn);
-    auto rel = [&](int c, double r) { return fn[c] > 0 ? r / fn[c] : 0.0; };
+    auto rel = [&](int c, double r) { return rel_norm(r, fn[c]); };
     int total_it = 0, restarts = 0, ir_steps = 0;
     if (cg) {
       total_it = cg_core(ws, n, nr, sp->tol, sp->max_iter, apply64, fn, rn, conv, restarts, s);
@@ -1330,7 +1333,8 @@ static hm_status solve_common(hm_handle* h, const void* f, void* sigma, int64_t 
     double worst = 0.0;
     for (int c = 0; c < nr; ++c) {
       nconv += conv[c];
-      worst = std::max(worst, rel(c, rn[c]));
+      const double r = rel(c, rn[c]);
+      if (!(r <= worst) && !std::isnan(worst)) worst = r;   // NaN stays
     }
     if (info) {
       info->iters = total_it;

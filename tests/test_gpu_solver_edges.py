@@ -105,3 +105,46 @@ def test_product_not_finite():
     assert st == hm.HM_NOT_CONVERGED and info.converged == 0
     assert info.iters <= 2
     H.free()
+
+
+@pytest.mark.parametrize("kw", [{}, {"graph": True}, {"refine": True}, {"method": "cg"}],
+                         ids=["gmres", "graph", "refine", "cg"])
+def test_right_hand_side_not_finite(kw):
+    """A right-hand side with a NaN, alone and among finite ones (one of them zero):
+    not converged, its relative residual NaN, the others solved."""
+    import paper_1806_11558_amd as hm
+    from synthetic import icosphere, normal_columns
+    V, T = icosphere(2)
+    say("NaN in f", kw)
+    H = hm.HMatrix(V, T, leaf_size=32, eps=1e-8, precision="f64",
+                   operator="galerkin" if "method" in kw else "collocation")
+    F = normal_columns(H.n, 3, seed=10)
+    F[:, 2] = 0.0
+    f = torch.tensor(F, device=DEV)
+    _, ref, st = H.solve(f, tol=1e-8, **kw)
+    assert st == hm.HM_OK
+    f[5, 1] = float("nan")
+    s, info, st = H.solve(f, tol=1e-8, **kw)
+    assert st == hm.HM_NOT_CONVERGED and info.converged == 2
+    assert np.isnan(info.rel_residual) and info.iters <= ref.iters + 2
+    r = (f - H.matvec(s)).cpu().numpy()
+    assert np.linalg.norm(r[:, 0]) <= 1.5e-8 * np.linalg.norm(F[:, 0])
+    assert torch.count_nonzero(s[:, 2]).item() == 0
+    s, info, st = H.solve(f[:, 1].contiguous(), tol=1e-8, **kw)
+    assert st == hm.HM_NOT_CONVERGED and info.converged == 0
+    assert np.isnan(info.rel_residual)
+    H.free()
+
+
+def test_adjoint_of_nan_raises():
+    """A density from a right-hand side that is not finite is not handed on."""
+    import paper_1806_11558_amd as hm
+    from synthetic import icosphere
+    V, T = icosphere(1)
+    say("hsolve of NaN")
+    H = hm.HMatrix(V, T, leaf_size=32, eps=1e-6, precision="f64")
+    f = torch.ones(H.n, dtype=torch.float64, device=DEV)
+    f[0] = float("nan")
+    with pytest.raises(hm.HMError):
+        hm.hsolve(f, H)
+    H.free()
