@@ -276,7 +276,7 @@ struct hm_handle {
   int2 *dns = nullptr, *lr = nullptr;
   Storage sto;
 
-  void *z = nullptr, *xt = nullptr, *w = nullptr, *ypart = nullptr;
+  void *z = nullptr, *w = nullptr, *ypart = nullptr;
   int64_t ypart_bytes = 0;
   std::unique_ptr<SolveWs> sws;         // graph-replay solve workspace
   std::vector<std::array<double, 2>> tune;   // autotuner: (unit columns, ms)
@@ -344,7 +344,7 @@ struct hm_handle {
     P.perm = perm;
     P.n = n;
     P.z = z;
-    P.xt = xt;
+    P.xt = ypart;
     P.w = w;
     P.su = sto.su;
     P.max_nr_t = max_nr_t;
@@ -502,13 +502,14 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
   h->nleaf = (int64_t)ct.lo.size();
   std::vector<char> up;
   auto pack = [&up](const auto& v) {
-    const size_t at = (up.size() + 255) & ~(size_t)255;
+    const size_t at = up.size();
     up.resize(at + v.size() * sizeof(v[0]));
     std::memcpy(up.data() + at, v.data(), v.size() * sizeof(v[0]));
     return at;
   };
-  const size_t o_cl = pack(ct.cl), o_leaves = pack(ct.leaves), o_lo = pack(ct.lo),
-               o_m = pack(ct.m), o_lc = pack(ct.leaf_cl), o_ld = pack(ct.ldpre);
+  // (largest elements first: none needs padding)
+  const size_t o_cl = pack(ct.cl), o_leaves = pack(ct.leaves), o_ld = pack(ct.ldpre),
+               o_lo = pack(ct.lo), o_m = pack(ct.m), o_lc = pack(ct.leaf_cl);
   char* tab = static_cast<char*>(h->alloc(up.size()));
   HM_HIP(hipMemcpyAsync(tab, up.data(), up.size(), hipMemcpyHostToDevice, s));
   h->cl = reinterpret_cast<Cluster*>(tab + o_cl);
@@ -562,14 +563,14 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
   // ---- product workspace: z = [x ; t] with 16 columns, w for the
   // transposed product sized to at most 2 GB (fewer columns per pass)
   h->z = h->alloc((size_t)(n + h->sto.toff_total + 1) * kMaxNr * sizeof(double));
-  // x per leaf with the rows padded to ld (at most three more per leaf)
-  h->xt = h->alloc((size_t)(n + 3 * h->nleaf) * kMaxNr * sizeof(double));
   {
     // partial rows for the most units any unit size of the tuner produces
     int64_t nu = h->sto.nunits;
     if (p.flags & HM_AUTOTUNE)
       nu = std::max(nu, count_units(h->sto, h->leaves(), kTuneCols[0], s));
-    h->ypart_bytes = (nu + 1) * (int64_t)h->sto.ldmax * kMaxNr * (int64_t)sizeof(double);
+    // (and, before they are written, x per leaf with its rows padded to ld)
+    h->ypart_bytes = std::max((nu + 1) * (int64_t)h->sto.ldmax, ct.ldpre.back()) * kMaxNr *
+                     (int64_t)sizeof(double);
     h->ypart = h->alloc((size_t)h->ypart_bytes);
   }
   {

@@ -137,20 +137,26 @@ struct Run {
   int32_t pad;
 };
 // Per admissible block: V factor address, rank, offset of its terms in t,
-// first/last leaf of its column (sf, sl) and row (tf, tl) cluster, and the
+// first/last leaf of its column cluster (sf, sl), row leaves (nt), and the
 // first entry of its U slices in the per-(block, row leaf) records.
 // The V factor of a block is stored in column-leaf slices, each ld x r
 // column-major; slice lf starts vw * (ldpre[lf] - ldpre[sf]) elements after
 // vptr: blocks that share a column cluster (whose leaves share one ld) lie
 // side by side in panels of vw = the sum of their ranks columns, a block
-// alone has vw = r.  The same record with r = a chunk of a panel's columns
-// describes a work unit of the forward phase 1.
+// alone has vw = r.
 struct LrMeta {
   uint64_t vptr;
-  int32_t r, toff, sf, sl, tf, tl;
   int64_t ub;
-  int32_t vld;   // ld shared by all column-leaf slices, 0 if they differ
+  int32_t r, toff, sf, sl, nt;
   int32_t vw;    // slice width: columns between the slices of one leaf and the next
+};
+// Work unit of the forward phase 1: r columns of a V panel (or a block alone),
+// the fields as above.
+struct VUnit {
+  uint64_t vptr;
+  int32_t r, toff, sf, sl;
+  int32_t vld;   // ld shared by all column-leaf slices, 0 if they differ
+  int32_t vw;
 };
 // Column-leaf item of the transposed product: kind 0 = columns of a dense
 // slice (partial dots at w[src ..]), kind 1 = V slice at `data` (w = rank,
@@ -199,9 +205,9 @@ struct MvPlan {
   const int32_t* colmap;
   const LrMeta* meta;
   int64_t nlr;
-  const LrMeta* meta1;      // work units of the forward phase 1 (panel column chunks)
+  const VUnit* meta1;       // work units of the forward phase 1 (panel column chunks)
   int64_t nu1;
-  const LrMeta* metax;      // the same panels in units of 64 columns, for the matrix-core phase 1
+  const VUnit* metax;       // the same panels in units of 64 columns, for the matrix-core phase 1
   int64_t nux;
   const int64_t* ucol;
   const int32_t* tbeg;      // column leaf -> first transposed item (nleaf + 1)
@@ -210,7 +216,8 @@ struct MvPlan {
   const int32_t* perm;
   int64_t n;
   void* z;                  // workspace: [x in Morton order ; t], 16 columns
-  void* xt;                 // workspace: x per leaf, NR columns of ld values each
+  void* xt;                 // workspace: x per leaf, NR columns of ld values each; the
+                            // memory of ypart, which phase 2 writes after phase 1 has read xt
   void* w;                  // workspace: panel-column partial dots
   const float* su;          // per-term scales of FP16 U factors (null: none)
   int max_nr_t;             // right-hand sides per transposed pass (w size)
@@ -263,9 +270,9 @@ struct Storage {
   int32_t* rank = nullptr;
   int32_t* info = nullptr;
   LrMeta* meta = nullptr;
-  LrMeta* meta1 = nullptr;   // forward phase-1 units
+  VUnit* meta1 = nullptr;    // forward phase-1 units
   int64_t nu1 = 0;
-  LrMeta* metax = nullptr;   // phase-1 units of kXUnitCols columns
+  VUnit* metax = nullptr;    // phase-1 units of kXUnitCols columns
   int64_t nux = 0;
   int64_t* ucol = nullptr;
   uint64_t* uptr = nullptr;
@@ -273,7 +280,7 @@ struct Storage {
   Run* runs = nullptr;
   int nruns = 0;
   Unit* units = nullptr;
-  int64_t nunits = 0;
+  int64_t nunits = 0, units_cap = 0;
   int unit_cols = 0;
   int esize = 0, lsize = 0;  // bytes of a dense and of a factor value
   int32_t* ubeg = nullptr;

@@ -158,7 +158,7 @@ __device__ inline void fwd1_flush(A (&p)[NR], int g, int R, int j0, int C, int r
 // are loaded with no branch between them and the x loads; columns past r
 // read column r - 1 into accumulators that are never flushed.
 template <typename T, typename A, int NR, int P>
-__device__ inline void fwd1_uniform(const LrMeta& M, const MvLeaves& L, const A* __restrict__ z,
+__device__ inline void fwd1_uniform(const VUnit& M, const MvLeaves& L, const A* __restrict__ z,
                                     int r, int ld, int R, int C, int cg, int g, bool act, int lane,
                                     A (&tl)[NR]) {
   constexpr int G = Gran<T>::G;
@@ -213,7 +213,7 @@ constexpr int fwd1_waves() {
 
 template <typename T, typename A, int NR>
 __global__ __launch_bounds__(256, (fwd1_waves<T, A, NR>())) void k_fwd1(
-    const LrMeta* __restrict__ meta, int64_t nl, MvLeaves L, A* __restrict__ z, int64_t n,
+    const VUnit* __restrict__ meta, int64_t nl, MvLeaves L, A* __restrict__ z, int64_t n,
     const float* __restrict__ su) {
   constexpr int G = Gran<T>::G;
   static_assert(NR <= 2, "more right-hand sides go to the matrix cores");
@@ -227,10 +227,10 @@ __global__ __launch_bounds__(256, (fwd1_waves<T, A, NR>())) void k_fwd1(
   const int64_t wid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t nw = (int64_t)gridDim.x * 4;
   // the next block's descriptor is loaded one iteration ahead
-  LrMeta Mn;
+  VUnit Mn;
   if (wid < nl) Mn = meta[wid];
   for (int64_t b = wid; b < nl; b += nw) {
-    const LrMeta M = Mn;
+    const VUnit M = Mn;
     if (b + nw < nl) Mn = meta[b + nw];
     const int r = M.r;
     if (r == 0) continue;
@@ -621,7 +621,7 @@ __device__ inline void fwd1x_leaf(const T* __restrict__ S, const A* __restrict__
 }
 
 template <typename T, typename A, int NR, int NTL>
-__device__ inline void fwd1x_pass(const LrMeta& M, const MvLeaves& L, const A* __restrict__ xt,
+__device__ inline void fwd1x_pass(const VUnit& M, const MvLeaves& L, const A* __restrict__ xt,
                                   int tg, int r, int lr, int lq,
                                   typename Mfma<A>::V (&acc)[4]) {
   const T* S = reinterpret_cast<const T*>((uintptr_t)M.vptr);
@@ -667,7 +667,7 @@ __device__ inline void tile_out(const typename Mfma<A>::V& acc, int lr, int lq, 
 }
 
 template <typename T, typename A, int NR>
-__global__ __launch_bounds__(256) void k_fwd1x(const LrMeta* __restrict__ meta, int64_t nl,
+__global__ __launch_bounds__(256) void k_fwd1x(const VUnit* __restrict__ meta, int64_t nl,
                                                MvLeaves L, const A* __restrict__ xt,
                                                A* __restrict__ zt, int64_t n,
                                                const float* __restrict__ su) {
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(256) void k_fwd1x(const LrMeta* __restrict__ meta, 
   const int64_t wid = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t nw = (int64_t)gridDim.x * 4;
   for (int64_t b = wid; b < nl; b += nw) {
-    const LrMeta M = meta[b];
+    const VUnit M = meta[b];
     const int r = M.r;
     if (r == 0) continue;
     for (int tg = 0; tg < r; tg += 64) {
@@ -1065,7 +1065,7 @@ template <typename A, int NR>
 __device__ inline void tr_sums_block(const LrMeta& M, const int64_t* __restrict__ ucol,
                                      const A* __restrict__ w, A* __restrict__ z, int64_t n,
                                      const float* __restrict__ su, int lane) {
-  const int nk = M.tl - M.tf + 1;
+  const int nk = M.nt;
   const int gw = M.r <= 16 ? 16 : (M.r <= 32 ? 32 : 64);   // uniform over the wavefront
   const int ng = 64 / gw, grp = lane / gw;
   for (int t0 = 0; t0 < M.r; t0 += 64) {
@@ -1129,7 +1129,7 @@ __global__ __launch_bounds__(256) void k_tr_sums(const LrMeta* __restrict__ meta
     const LrMeta M = meta[has ? b : nl - 1];
     if (__all(!has || M.r <= 16)) {                     // uniform over the wavefront
       if (has && l < M.r) {
-        const int nk = M.tl - M.tf + 1;
+        const int nk = M.nt;
         A acc[NR];
 #pragma unroll
         for (int k = 0; k < NR; ++k) acc[k] = 0;

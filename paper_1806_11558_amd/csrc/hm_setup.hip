@@ -1649,8 +1649,9 @@ __global__ void k_emit_units(const int64_t* __restrict__ gstart, int64_t ng,
                              const uint64_t* __restrict__ key, const int32_t* __restrict__ idx,
                              const int64_t* __restrict__ gw, const int64_t* __restrict__ goff,
                              const int64_t* __restrict__ uoff, const int64_t* __restrict__ tsort,
-                             int64_t toff_base, const LrMeta* __restrict__ meta, int gran, int passes,
-                             int uw0, uint64_t varena, int esize, LrMeta* __restrict__ units) {
+                             int64_t toff_base, const LrMeta* __restrict__ meta,
+                             const int64_t* __restrict__ ldpre, int gran, int passes, int uw0,
+                             uint64_t varena, int esize, VUnit* __restrict__ units) {
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < ng;
        g += (int64_t)gridDim.x * blockDim.x) {
     const int64_t a = gstart[g];
@@ -1658,21 +1659,16 @@ __global__ void k_emit_units(const int64_t* __restrict__ gstart, int64_t ng,
     if (w == 0) continue;
     const LrMeta B = meta[idx[a]];                      // the group's first block
     if (key[a] >= ((uint64_t)1 << 31)) {
-      units[uoff[g]] = B;
+      units[uoff[g]] = VUnit{B.vptr, B.r, B.toff, B.sf, B.sl, 0, B.vw};   // its leaves differ in ld
       continue;
     }
-    const int64_t ld = B.vld;
+    const int64_t ld = ldpre[B.sf + 1] - ldpre[B.sf];
     const int uw = uw0 > 0 ? uw0 : unit_cols(ld, gran, passes);
     int64_t o = uoff[g];
     for (int64_t c0 = 0; c0 < w; c0 += uw, ++o) {
-      LrMeta U = B;
-      U.vptr = varena + (uint64_t)((goff[g] + c0 * ld) * esize);
-      U.r = (int32_t)min((int64_t)uw, w - c0);
-      U.toff = (int32_t)(toff_base + tsort[a] + c0);
-      U.tf = U.tl = 0;
-      U.ub = 0;
-      U.vw = (int32_t)w;
-      units[o] = U;
+      units[o] = VUnit{varena + (uint64_t)((goff[g] + c0 * ld) * esize),
+                       (int32_t)min((int64_t)uw, w - c0), (int32_t)(toff_base + tsort[a] + c0),
+                       B.sf, B.sl, (int32_t)ld, (int32_t)w};
     }
   }
 }
@@ -1711,7 +1707,7 @@ __global__ void k_drec(const int32_t* __restrict__ sidx, const int32_t* __restri
 }
 
 __global__ void k_lr_meta(const int2* __restrict__ blk, int64_t nb, const int2* __restrict__ cl_leaves,
-                          const int64_t* __restrict__ ldpre, const int32_t* __restrict__ rank,
+                          const int32_t* __restrict__ rank,
                           const int64_t* __restrict__ toff, int64_t toff_base,
                           const uint64_t* __restrict__ vptr, const int32_t* __restrict__ vw,
                           const int64_t* __restrict__ ub, LrMeta* __restrict__ meta) {
@@ -1725,13 +1721,8 @@ __global__ void k_lr_meta(const int2* __restrict__ blk, int64_t nb, const int2* 
     M.toff = (int32_t)(toff_base + toff[b]);
     M.sf = ls.x;
     M.sl = ls.y;
-    M.tf = lt.x;
-    M.tl = lt.y;
+    M.nt = lt.y - lt.x + 1;
     M.ub = ub[b];
-    const int64_t ld0 = ldpre[ls.x + 1] - ldpre[ls.x];
-    bool uni = true;
-    for (int lf = ls.x + 1; lf <= ls.y && uni; ++lf) uni = (ldpre[lf + 1] - ldpre[lf]) == ld0;
-    M.vld = uni ? (int32_t)ld0 : 0;
     M.vw = vw[b];
     meta[b] = M;
   }
@@ -1743,7 +1734,7 @@ __global__ void k_lr_meta(const int2* __restrict__ blk, int64_t nb, const int2* 
 // block one V slice.
 // The V side comes from the phase-1 units (column chunks of the V panels:
 // wider items than single blocks, with consecutive terms).
-__global__ void k_titem_counts(const int2* __restrict__ dns, int64_t nd, const LrMeta* __restrict__ units,
+__global__ void k_titem_counts(const int2* __restrict__ dns, int64_t nd, const VUnit* __restrict__ units,
                                int64_t nl, const int2* __restrict__ cl_leaves,
                                int64_t* __restrict__ cnt) {
   for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < nd + nl;
@@ -1753,7 +1744,7 @@ __global__ void k_titem_counts(const int2* __restrict__ dns, int64_t nd, const L
       const int2 lt = cl_leaves[ts.x], ls = cl_leaves[ts.y];
       cnt[b] = (int64_t)(lt.y - lt.x + 1) * (ls.y - ls.x + 1);
     } else {
-      const LrMeta& U = units[b - nd];
+      const VUnit& U = units[b - nd];
       cnt[b] = U.sl - U.sf + 1;
     }
   }
@@ -1763,7 +1754,7 @@ __global__ void k_titem_expand(const int2* __restrict__ dns, int64_t nd, int64_t
                                const Cluster* __restrict__ cl, LeafTab L,
                                const int64_t* __restrict__ off, const int32_t* __restrict__ invD,
                                const int64_t* __restrict__ oD, const int64_t* __restrict__ gcolD,
-                               const LrMeta* __restrict__ meta, int esize, TItem* __restrict__ out,
+                               const VUnit* __restrict__ meta, int esize, TItem* __restrict__ out,
                                uint64_t* __restrict__ key, int32_t* __restrict__ idx) {
   for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < nd + nl;
        b += (int64_t)gridDim.x * blockDim.x) {
@@ -1781,7 +1772,7 @@ __global__ void k_titem_expand(const int2* __restrict__ dns, int64_t nd, int64_t
         }
       }
     } else {
-      const LrMeta M = meta[b - nd];
+      const VUnit M = meta[b - nd];
       for (int cf = M.sf; cf <= M.sl; ++cf, ++o) {
         const uint64_t d = M.vptr + (uint64_t)((int64_t)M.vw * (L.ldpre[cf] - L.ldpre[M.sf]) * esize);
         out[o] = TItem{d, (int64_t)M.toff, M.r, 1};
@@ -1836,6 +1827,7 @@ __global__ void k_unpack(const int2* __restrict__ lr, int64_t b, const Cluster* 
   const int2 ts = lr[b];
   const Cluster tau = cl[ts.x], sig = cl[ts.y];
   const LrMeta M = meta[b];
+  const int2 tl = L.cl_leaves[ts.x];
   const int m = tau.y - tau.x, n = sig.y - sig.x, r = M.r;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < (int64_t)(m + n) * r;
        e += (int64_t)gridDim.x * blockDim.x) {
@@ -1844,7 +1836,7 @@ __global__ void k_unpack(const int2* __restrict__ lr, int64_t b, const Cluster* 
     const int rows = isu ? m : n;
     const int i = (int)(ee % rows), l = (int)(ee / rows);
     const int pos = (isu ? tau.x : sig.x) + i;
-    const int lf0 = isu ? M.tf : M.sf, lf1 = isu ? M.tl : M.sl;
+    const int lf0 = isu ? tl.x : M.sf, lf1 = isu ? tl.y : M.sl;
     int lf = lf0;
     while (lf < lf1 && L.lo[lf + 1] <= pos) ++lf;
     const TL* sl;
@@ -2364,8 +2356,11 @@ void make_units(Storage& out, const MvLeaves& L, int ucols, const Alloc& alloc, 
   if (total >= INT32_MAX) throw Error{HM_ERR_STATE, "too many product units"};
   out.nunits = total;
   out.unit_cols = ucols;
-  out.units = static_cast<Unit*>(alloc((size_t)(total + 1) * sizeof(Unit)));
-  out.ubeg = static_cast<int32_t*>(alloc((size_t)(L.nleaf + 1) * sizeof(int32_t)));
+  if (total > out.units_cap || !out.units) {            // else over the last widths' records
+    out.units_cap = std::max<int64_t>(total, 1);
+    out.units = static_cast<Unit*>(alloc((size_t)out.units_cap * sizeof(Unit)));
+  }
+  if (!out.ubeg) out.ubeg = static_cast<int32_t*>(alloc((size_t)(L.nleaf + 1) * sizeof(int32_t)));
   k_unit_emit<<<grid_for(L.nleaf, 64), 64, 0, s>>>(out.runs, out.nruns, L, ucols, off, total,
                                                    out.esize, out.lsize, out.units, out.ubeg);
   HM_LAUNCH_CHECK();
@@ -2406,8 +2401,8 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   HM_LAUNCH_CHECK();
   std::vector<Run*> run_parts;
   std::vector<std::pair<int32_t*, int64_t>> colmap_parts;
-  std::vector<std::pair<LrMeta*, int64_t>> unit_parts;      // forward phase-1 units per chunk
-  std::vector<std::pair<LrMeta*, int64_t>> xunit_parts;     // the same for the matrix cores
+  std::vector<std::pair<VUnit*, int64_t>> unit_parts;       // forward phase-1 units per chunk
+  std::vector<std::pair<VUnit*, int64_t>> xunit_parts;      // the same for the matrix cores
   Run* runD = keep.get<Run>(nleaf);
   k_runs<<<grid_for(nleaf, 256), 256, 0, s>>>(PD.col0, PD.W, PD.poff, nleaf, (uint64_t)(uintptr_t)D,
                                               esize, 0, runD);
@@ -2612,21 +2607,21 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
                                                                out.rank + b0, desc + b0, voff,
                                                                vwid, varena, vptr);
       HM_LAUNCH_CHECK();
-      k_lr_meta<<<grid_for(nb, 256), 256, 0, s>>>(in.lr + b0, nb, in.cl_leaves, in.ldpre,
-                                                  out.rank + b0, toffc, toff_base, vptr, vwid,
-                                                  ub + b0, out.meta + b0);
+      k_lr_meta<<<grid_for(nb, 256), 256, 0, s>>>(in.lr + b0, nb, in.cl_leaves, out.rank + b0,
+                                                  toffc, toff_base, vptr, vwid, ub + b0,
+                                                  out.meta + b0);
       HM_LAUNCH_CHECK();
       // phase-1 units of the chunk
       {
-        LrMeta* um = keep.get<LrMeta>(nu[0] + 1);
-        LrMeta* umx = keep.get<LrMeta>(nu[1] + 1);
+        VUnit* um = keep.get<VUnit>(nu[0] + 1);
+        VUnit* umx = keep.get<VUnit>(nu[1] + 1);
         k_emit_units<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, gkey, gidx, gw, goff, guoff,
-                                                        tsort, toff_base, out.meta + b0, gran,
+                                                        tsort, toff_base, out.meta + b0, in.ldpre, gran,
                                                         passes, 0, (uint64_t)(uintptr_t)varena,
                                                         lsize, um);
         HM_LAUNCH_CHECK();
         k_emit_units<<<grid_for(ngr, 256), 256, 0, s>>>(gstart, ngr, gkey, gidx, gw, goff, guoffx,
-                                                        tsort, toff_base, out.meta + b0, gran,
+                                                        tsort, toff_base, out.meta + b0, in.ldpre, gran,
                                                         passes, kXUnitCols,
                                                         (uint64_t)(uintptr_t)varena, lsize, umx);
         HM_LAUNCH_CHECK();
@@ -2683,26 +2678,36 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   }
   out.toff_total = toff_base;
   if (toff_base >= INT32_MAX) throw Error{HM_ERR_STATE, "more than 2^31 low-rank terms"};
-  auto join_units = [&](const std::vector<std::pair<LrMeta*, int64_t>>& parts, int64_t* cnt) {
+  auto join_units = [&](const std::vector<std::pair<VUnit*, int64_t>>& parts, int64_t* cnt) {
     int64_t nu = 0, o = 0;
     for (auto& up : parts) nu += up.second;
     *cnt = nu;
-    LrMeta* dst = static_cast<LrMeta*>(alloc((size_t)(nu + 1) * sizeof(LrMeta)));
+    VUnit* dst = static_cast<VUnit*>(alloc((size_t)std::max<int64_t>(nu, 1) * sizeof(VUnit)));
     for (auto& up : parts) {
       if (up.second)
-        copy_d2d(dst + o, up.first, up.second * sizeof(LrMeta), s);
+        copy_d2d(dst + o, up.first, up.second * sizeof(VUnit), s);
       o += up.second;
     }
     return dst;
   };
   out.meta1 = join_units(unit_parts, &out.nu1);
-  out.metax = join_units(xunit_parts, &out.nux);
+  // as many units of 64 columns: those of meta1 serve both (most have 64 columns)
+  int64_t nux = 0;
+  for (auto& up : xunit_parts) nux += up.second;
+  if (nux == out.nu1) {
+    out.metax = out.meta1;
+    out.nux = nux;
+  } else {
+    out.metax = join_units(xunit_parts, &out.nux);
+  }
   out.ms_aca = ms_since(t0) - ms_pack;
 
   // ---- product plan: runs, column map, transposed items
   t0 = clk::now();
   out.nruns = (int)run_parts.size();
-  out.runs = static_cast<Run*>(alloc((size_t)out.nruns * nleaf * sizeof(Run)));
+  // (only the unit tables are made from the runs: the tuner makes some later)
+  const size_t run_cnt = (size_t)out.nruns * nleaf;
+  out.runs = in.tune_aca ? static_cast<Run*>(alloc(run_cnt * sizeof(Run))) : keep.get<Run>(run_cnt);
   for (int k = 0; k < out.nruns; ++k)
     copy_d2d(out.runs + (int64_t)k * nleaf, run_parts[k], nleaf * sizeof(Run), s);
   out.esize = esize;
@@ -2748,6 +2753,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   }
   out.ms_pack = ms_pack + ms_since(t0);
   keep.release();
+  if (!in.tune_aca) out.runs = nullptr;
 }
 template void build_storage<float, float>(const Geom<float>&, const SetupIn&, Storage&,
                                           const Alloc&, hipStream_t);
