@@ -340,6 +340,7 @@ struct hm_handle {
     P.ucol = sto.ucol;
     P.tbeg = sto.tbeg;
     P.titems = sto.titems;
+    P.vitem = sto.vitem;
     P.L = leaves();
     P.perm = perm;
     P.n = n;

@@ -212,6 +212,7 @@ struct MvPlan {
   const int64_t* ucol;
   const int32_t* tbeg;      // column leaf -> first transposed item (nleaf + 1)
   const TItem* titems;
+  double vitem;             // mean values (ld x columns) of a V item
   MvLeaves L;
   const int32_t* perm;
   int64_t n;
@@ -283,6 +284,7 @@ struct Storage {
   int64_t nunits = 0, units_cap = 0;
   int unit_cols = 0;
   int esize = 0, lsize = 0;  // bytes of a dense and of a factor value
+  double vitem = 0.0;        // mean values (ld x columns) of a transposed V item
   int32_t* ubeg = nullptr;
   int ldmax = 0;
   float* su = nullptr;       // per-term scales when the factors are FP16

@@ -1158,12 +1158,26 @@ __global__ __launch_bounds__(256) void k_tr_sums(const LrMeta* __restrict__ meta
 // i mod 4), so that a leaf's few hundred slices are not one long chain of
 // dependent loads per wavefront; with S > 1 each workgroup writes its partial
 // rows to ypart[c S + s] and k_tr2_sum adds them in order of s.
-template <typename T, typename A, typename VT, int NR>
+// The columns of a V item go up to UMAX groups of C at a time, by what is left
+// of it: with four at a time whatever the width, trees of narrow items (blocks
+// that stand alone, 9.5 columns) paid for loads of nothing: N = 200,000, FP32,
+// leaf 24, one and two columns 2,450 and 3,050 us, with one at a time 2,150 and
+// 2,400.  Wide items want the loads in flight (N = 32,000, leaf 32 and 64, FP32
+// 183 -> 174 and 190 -> 185, FP16 129 -> 121 and 150 -> 142 against one at a
+// time), unless their sums take too many registers: two for two double columns
+// of float or half slices (N = 81,920, leaf 32: FP32 814 -> 799, FP16 530 -> 503
+// us), one for four columns (62 registers, 86 with four: N = 162,000, leaf 24,
+// 1,709 and 1,844 us).
+template <typename T, typename A, int NR>
+constexpr int tr2_groups() {
+  return NR >= 4 ? 1 : (sizeof(A) == 8 && sizeof(T) < 8 && NR == 2 ? 2 : 4);
+}
+template <typename T, typename A, typename VT, int NR, int UMAX>
 __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
                                              const TItem* __restrict__ items, MvLeaves L,
                                              const A* __restrict__ w, const A* __restrict__ z,
                                              int64_t n, const int32_t* __restrict__ perm,
-                                             VT* __restrict__ y, int nrhs, int k0, int S,
+                                             VT* __restrict__ y, int nrhs, int k0, int nv, int S,
                                              A* __restrict__ ypart, int ldmax) {
   constexpr int G = Gran<T>::G;
   __shared__ A ybuf[4][kMaxLeaf][NR];
@@ -1203,34 +1217,52 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
         }
       } else {
         const T* S = reinterpret_cast<const T*>((uintptr_t)I.data);
-        // UNR column groups at a time with unconditional loads (a lane without
-        // a column reads the slice's last one and adds zero), so all their
-        // loads are in flight together: one column at N = 32,000, leaf 32 and
-        // 64, FP32 183 -> 174 and 190 -> 185 us, FP16 129 -> 121 and 150 -> 142
-        // against a column group at a time.  Two for two double columns of
-        // float or half slices, whose sums take 16 registers more (N = 81,920,
-        // leaf 32: FP32 814 -> 799, FP16 530 -> 503 us)
-        constexpr int UNR = sizeof(A) == 8 && sizeof(T) < 8 && NR == 2 ? 2 : 4;
-        const int ngrp = (I.w + C - 1) / C;
-        for (int q0 = 0; q0 < ngrp; q0 += UNR) {
-          typename Gran<T>::E s[UNR][G];
-          A zz[UNR][NR];
-          bool ok[UNR];
+        // U column groups with unconditional loads (a lane without a column
+        // reads the slice's last one and adds zero), so that all their loads
+        // are in flight together
+        auto groups = [&](auto cnt, int j0) {
+          constexpr int U = decltype(cnt)::value;
+          typename Gran<T>::E s[U][G];
+          A zz[U][NR];
+          bool ok[U];
 #pragma unroll
-          for (int u = 0; u < UNR; ++u) {
-            const int j = (q0 + u) * C + cg;
-            ok[u] = act && q0 + u < ngrp && j < I.w;
+          for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * C + cg;
+            ok[u] = act && j < I.w;
             const int jj = ok[u] ? j : I.w - 1;
             Gran<T>::load(S + (int64_t)jj * ld + g * G, s[u]);
             load_row<A, NR>(z + (n + I.src + jj) * NR, zz[u]);
           }
 #pragma unroll
-          for (int u = 0; u < UNR; ++u)
+          for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int e = 0; e < G; ++e)
 #pragma unroll
               for (int k = 0; k < NR; ++k)
                 acc[e][k] += (A)s[u][e] * (ok[u] ? zz[u][k] : (A)0);
+        };
+        for (int j0 = 0; j0 < I.w;) {                   // uniform over the wavefront
+          const int left = I.w - j0;
+          if (UMAX == 4 && left > 2 * C) {
+            groups(std::integral_constant<int, 4>{}, j0);
+            j0 += 4 * C;
+          } else if (UMAX >= 2 && left > C) {
+            groups(std::integral_constant<int, 2>{}, j0);
+            j0 += 2 * C;
+          } else {
+            const int j = j0 + cg;
+            if (act && j < I.w) {
+              typename Gran<T>::E s[G];
+              Gran<T>::load(S + (int64_t)j * ld + g * G, s);
+              A zz[NR];
+              load_row<A, NR>(z + (n + I.src + j) * NR, zz);
+#pragma unroll
+              for (int e = 0; e < G; ++e)
+#pragma unroll
+                for (int k = 0; k < NR; ++k) acc[e][k] += (A)s[e] * zz[k];
+            }
+            j0 += C;
+          }
         }
       }
     }
@@ -1266,7 +1298,7 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
       const A v = ((ybuf[0][row][k] + ybuf[1][row][k]) + ybuf[2][row][k]) + ybuf[3][row][k];
       if (S > 1)
         yp[e] = v;
-      else
+      else if (k < nv)
         y[(int64_t)perm[lo + row] * nrhs + k0 + k] = (VT)v;
     }
     __syncthreads();
@@ -1307,15 +1339,19 @@ __device__ inline void tr2x_items(const TItem* __restrict__ items, int it0, int 
       const T* P = reinterpret_cast<const T*>((uintptr_t)I.data);
       const A* zb = z + (n + I.src) * NR;
       ColBatch<T, A, NR, KQ, NT> b0, b1b;
-      for (int c = 0; c < I.w; c += 2 * CB) {
+      // two batches at a time, and one for what is left of narrow items
+      int c = 0;
+      for (; c + CB < I.w; c += 2 * CB) {               // uniform over the wavefront
         b0.template load<false>(P, zb, 0, c, I.w, ld, r1, r2, xo, lq);
         b1b.template load<false>(P, zb, 0, c + CB, I.w, ld, r1, r2, xo, lq);
-        if (c + 2 * CB > I.w) {                         // uniform over the wavefront
-          b0.mask(c, I.w, lq);
-          b1b.mask(c + CB, I.w, lq);
-        }
+        if (c + 2 * CB > I.w) b1b.mask(c + CB, I.w, lq);
         b0.mul(acc);
         b1b.mul(acc);
+      }
+      if (c < I.w) {
+        b0.template load<false>(P, zb, 0, c, I.w, ld, r1, r2, xo, lq);
+        b0.mask(c, I.w, lq);
+        b0.mul(acc);
       }
     }
   }
@@ -1406,6 +1442,22 @@ template <typename TL, typename A, int NR>
 constexpr int64_t kTrMfmaLeaves =
     sizeof(TL) == 8 || (sizeof(A) == 4 && NR == 2) ? 128 : 64;
 
+// Four single-precision columns run on the vector units from this many leaves
+// on (vcols: mean columns of a V item).  Blocks whose column leaves differ in ld
+// stand alone, and their items are as wide as their rank: a quarter of a pass
+// of the matrix kernel.  N = 200,000, 16,384 leaves of 12.2 rows (ld 12 and 16,
+// 9.5 columns) 3,859 -> 2,824 us; N = 50,000, 1,024 leaves of 48.8 rows, 485 ->
+// 438, 4,096 of 12.2, 661 -> 514, FP16 factors 359 -> 335 and 472 -> 397.  FP32
+// with wide items: 2,048 leaves of 19.8 rows 387 -> 344, of 40 rows 722 -> 682,
+// 4,096 of 39.6 rows 1,562 -> 1,509; fewer leaves 1,024 of 20 rows 171 and 169,
+// of 39.6 rows 326 and 321, 512 of 22.5 rows 82 and 102.  FP16 with wide items:
+// 2,048 leaves of 10 rows 167 and 202, of 40 rows 486 and 475, 4,096 of 39.6
+// rows 983 and 1,043.
+template <typename TL>
+constexpr int64_t tr_vec4_leaves(double vcols) {
+  return vcols < 24.0 ? 1024 : (sizeof(TL) == 4 ? 2048 : INT64_MAX);
+}
+
 template <typename TD, typename TL, typename A, typename VT, int NR>
 static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int nv,
                      bool transposed, hipStream_t s) {
@@ -1414,8 +1466,11 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
   A* xt = static_cast<A*>(P.xt);
   MvProfile* pr = P.prof;
   if (pr) HM_HIP(hipEventRecord(pr->ev[0], s));
-  const bool tmx = NR >= 4 || P.L.nleaf <= kTrMfmaLeaves<TL, A, NR>;   // transposed, on the matrix cores
-  if (transposed ? tmx : NR >= 4)
+  constexpr bool kVec4 = NR == 4 && sizeof(A) == 4;
+  // transposed, on the matrix cores
+  const bool tmx = NR >= 4 ? !(kVec4 && P.L.nleaf >= tr_vec4_leaves<TL>(P.vitem / P.ldmax))
+                           : P.L.nleaf <= kTrMfmaLeaves<TL, A, NR>;
+  if (NR >= 4 || (transposed && tmx))
     k_gather_x<VT, A, NR><<<(unsigned)std::min<int64_t>(P.L.nleaf, 1 << 20), 256, 0, s>>>(
         x, nrhs, k0, nv, P.perm, P.L, z, xt);
   else
@@ -1456,7 +1511,7 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
       const unsigned gu = (unsigned)std::min<int64_t>(ceil_div(P.nunits, kXcds) * kXcds, P.grid);
       if (tmx)
         k_tr1x<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, xt, w);
-      else if constexpr (NR < 4)
+      else if constexpr (NR < 4 || kVec4)
         k_tr1<TD, TL, A, NR><<<gu, 256, 0, s>>>(P.units, P.nunits, z, w);
       HM_LAUNCH_CHECK();
     }
@@ -1479,9 +1534,19 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
     if (tmx)
       k_tr2x<TL, A, VT, NR><<<gt, 256, 0, s>>>(P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs,
                                                k0, nv, S, static_cast<A*>(P.ypart), P.ldmax);
-    else if constexpr (NR < 4)
-      k_tr2<TL, A, VT, NR><<<gt, 256, 0, s>>>(P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs,
-                                              k0, S, static_cast<A*>(P.ypart), P.ldmax);
+    else if constexpr (NR < 4 || kVec4) {
+      auto tr2 = [&](auto u) {
+        k_tr2<TL, A, VT, NR, decltype(u)::value><<<gt, 256, 0, s>>>(
+            P.tbeg, P.titems, P.L, w, z, P.n, P.perm, y, nrhs, k0, nv, S, static_cast<A*>(P.ypart),
+            P.ldmax);
+      };
+      constexpr int UMAX = tr2_groups<TL, A, NR>();
+      // items of hardly more than one group: nothing to keep in flight
+      if (UMAX == 1 || 2.0 * P.vitem <= 3.0 * 64 * Gran<TL>::G)
+        tr2(std::integral_constant<int, 1>{});
+      else
+        tr2(std::integral_constant<int, UMAX>{});
+    }
     HM_LAUNCH_CHECK();
     if (S > 1) {
       k_tr2_sum<A, VT, NR><<<(unsigned)std::min<int64_t>(ceil_div(P.L.nleaf, sum_leaves<NR>()), P.grid), 256, 0, s>>>(

@@ -2457,7 +2457,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
   }
   out.ucol = static_cast<int64_t*>(alloc((out.u_items + 1) * sizeof(int64_t)));
   out.uptr = static_cast<uint64_t*>(alloc((out.u_items + 1) * sizeof(uint64_t)));
-  int64_t toff_base = 0, ucols = 0;
+  int64_t toff_base = 0, ucols = 0, vtotal = 0;
   double ms_pack = 0;
   if (nl > 0) {
     Temps ta{s, {}};
@@ -2670,6 +2670,7 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
       toff_base += terms;
       ucols += PU.cols;
       out.lr_elems += velems + PU.elems;
+      vtotal += velems;
       ++out.nchunks;
       b0 = b1;
     }
@@ -2733,6 +2734,9 @@ void build_storage(const Geom<T>& g, const SetupIn& in, Storage& out, const Allo
     HM_LAUNCH_CHECK();
     out.ntitems = scan_total(cnt, off, nb_all, tmp, s);
     if (out.ntitems >= INT32_MAX) throw Error{HM_ERR_STATE, "more than 2^31 transposed items"};
+    // the dense blocks have 2 np - nd of them: one cluster of a block is a leaf,
+    // and the partition is symmetric, so np counts their row and column leaves
+    out.vitem = (double)vtotal / (double)std::max<int64_t>(1, out.ntitems - (2 * PD.np - in.nd));
     TItem* raw = tt.get<TItem>(out.ntitems);
     uint64_t* key = tt.get<uint64_t>(out.ntitems);
     int32_t* idx = tt.get<int32_t>(out.ntitems);
