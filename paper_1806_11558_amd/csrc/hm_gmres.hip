@@ -44,8 +44,11 @@ GsShape gs_shape(int64_t n, int nr, bool coarse) {
   et = std::min<int64_t>(std::max<int64_t>(et, 128), kGsElems);
   g.tr = coarse ? kGsElems : std::max<int64_t>(1, et / nr);
   g.tiles = (int)ceil_div(n, g.tr);
-  // (coarse: the second array of partial sums that folding takes is left out)
-  g.fold = !coarse && (int64_t)g.tiles * nr <= 160;
+  // Every workgroup adds all sums of a step: with many columns that takes
+  // longer than the kernels saved (graph solve, N = 20, 24 columns: 1,330 us,
+  // 1,160 as separate kernels).  (coarse: the second array of partial sums
+  // that folding takes is left out)
+  g.fold = !coarse && nr <= 16 && (int64_t)g.tiles * nr <= 160;
   g.coarse = coarse;
   return g;
 }
@@ -60,18 +63,19 @@ __device__ inline double gs_tile_sum(const double* __restrict__ part, int64_t e,
 
 // Partial dots of the basis vectors [k0, k1) with the cnt elements of w held
 // in LDS (they start at element e0 of every vector): one wavefront per vector
-// and group of columns.  A power of two of columns up to 64 keeps every
-// lane's column fixed (lane mod nr) with contiguous reads; any other count
-// takes its columns one by one.  add: the tile's earlier pieces are there.
+// and group of up to 64 columns.  A power of two of columns keeps every lane's
+// column fixed (lane mod nr) with contiguous reads; any other count gives its
+// columns to consecutive lanes, as many rows at once as fit (taken one by one,
+// 40 columns at N = 80 cost 1.2 times the solve).  add: the tile's earlier
+// pieces are there.
 __device__ inline void gs_dots(const double* __restrict__ Q, int64_t ldq, int k0, int k1,
                                const double* __restrict__ ws, int64_t e0, int cnt, int nr,
                                int tiles, int tile, bool add, double* __restrict__ part) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool pow2 = nr <= 64 && (nr & (nr - 1)) == 0;
-  const int per = pow2 ? 1 : nr;
-  for (int task = wave; task < (k1 - k0) * per; task += kGT / 64) {
-    const int k = k0 + task / per;
-    const int c0 = pow2 ? 0 : task % per;
+  const int nch = (nr + 63) / 64;
+  for (int task = wave; task < (k1 - k0) * nch; task += kGT / 64) {
+    const int k = k0 + task / nch, c0 = task % nch * 64, cw = min(64, nr - c0);
     const double* q = Q + (int64_t)k * ldq + e0;
     double acc = 0.0;
     if (pow2) {
@@ -83,11 +87,15 @@ __device__ inline void gs_dots(const double* __restrict__ Q, int64_t ldq, int k0
         for (int off = 32; off >= nr; off >>= 1) acc += __shfl_xor(acc, off, 64);
       }
     } else {
-      for (int e = lane * nr + c0; e < cnt; e += 64 * nr) acc += q[e] * ws[e];
-      acc = wsum(acc);
+      const int rows = 64 / cw, g = lane / cw;
+      if (g < rows)
+        for (int e = g * nr + c0 + (lane - g * cw); e < cnt; e += rows * nr) acc += q[e] * ws[e];
+      for (int s = 1; s < rows; s <<= 1) {
+        const double o = __shfl_down(acc, s * cw, 64);
+        if (g + s < rows) acc += o;
+      }
     }
-    const int cols = pow2 ? nr : 1;
-    if (lane < cols) {
+    if (lane < cw) {
       double* o = part + ((int64_t)k * nr + c0 + lane) * tiles + tile;
       *o = add ? *o + acc : acc;
     }
