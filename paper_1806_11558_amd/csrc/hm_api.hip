@@ -277,7 +277,7 @@ struct hm_handle {
   Storage sto;
 
   void *z = nullptr, *w = nullptr, *ypart = nullptr;
-  int64_t ypart_bytes = 0;
+  int64_t ypart_bytes = 0, xt_rows = 0;
   std::unique_ptr<SolveWs> sws;         // graph-replay solve workspace
   std::vector<std::array<double, 2>> tune;   // autotuner: (unit columns, ms)
   int max_nr_t = 1;
@@ -345,7 +345,7 @@ struct hm_handle {
     P.perm = perm;
     P.n = n;
     P.z = z;
-    P.xt = ypart;
+    P.xt_rows = xt_rows;
     P.w = w;
     P.su = sto.su;
     P.max_nr_t = max_nr_t;
@@ -570,7 +570,8 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
     if (p.flags & HM_AUTOTUNE)
       nu = std::max(nu, count_units(h->sto, h->leaves(), kTuneCols[0], s));
     // (and, before they are written, x per leaf with its rows padded to ld)
-    h->ypart_bytes = std::max((nu + 1) * (int64_t)h->sto.ldmax, ct.ldpre.back()) * kMaxNr *
+    h->xt_rows = ct.ldpre.back();
+    h->ypart_bytes = std::max((nu + 1) * (int64_t)h->sto.ldmax, h->xt_rows) * kMaxNr *
                      (int64_t)sizeof(double);
     h->ypart = h->alloc((size_t)h->ypart_bytes);
   }

@@ -217,8 +217,7 @@ struct MvPlan {
   const int32_t* perm;
   int64_t n;
   void* z;                  // workspace: [x in Morton order ; t], 16 columns
-  void* xt;                 // workspace: x per leaf, NR columns of ld values each; the
-                            // memory of ypart, which phase 2 writes after phase 1 has read xt
+  int64_t xt_rows;          // sum of ld over the leaves: rows of x per leaf
   void* w;                  // workspace: panel-column partial dots
   const float* su;          // per-term scales of FP16 U factors (null: none)
   int max_nr_t;             // right-hand sides per transposed pass (w size)

@@ -1467,7 +1467,14 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
                      bool transposed, hipStream_t s) {
   A* z = static_cast<A*>(P.z);
   A* w = static_cast<A*>(P.w);
-  A* xt = static_cast<A*>(P.xt);
+  // x per leaf, NR columns of ld values each, at the end of the memory of ypart,
+  // which phase 2 writes after phase 1 has read xt.  Not at its start: lines that
+  // every XCD has just read are slow to write (32 leaves of 40 rows, FP64, two
+  // columns, transposed: the column kernel 13.7 us there, 10.6 at the end, whose
+  // lines phase 2 of a few columns doesn't reach)
+  A* xt = reinterpret_cast<A*>(
+      static_cast<char*>(P.ypart) +
+      ((P.ypart_bytes - P.xt_rows * NR * (int64_t)sizeof(A)) & ~(int64_t)255));
   MvProfile* pr = P.prof;
   if (pr) HM_HIP(hipEventRecord(pr->ev[0], s));
   constexpr bool kVec4 = NR == 4 && sizeof(A) == 4;
