@@ -377,6 +377,9 @@ __device__ inline void fwd2_run_lds(const Unit& U, int ld, int C, int cg, int g,
         jl[u] = ok[u] ? j : tw - 1;
         Gran<T>::load(St + (int64_t)jl[u] * ld, s[u]);
       }
+      // all loads before the first wait: 148 leaves of 39 rows, FP32, two double
+      // columns 49.9 -> 46.5 us
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
 #pragma unroll
@@ -390,8 +393,15 @@ __device__ inline void fwd2_run_lds(const Unit& U, int ld, int C, int cg, int g,
   }
 }
 
+// Factors narrower than the vectors: conversions in flight take registers, and
+// without a bound the wavefronts per SIMD fall from 8 and 6 (one and two columns)
+// to 6 and 4; N = 32,400, leaf 16, FP32, double vectors 334 -> 327 and 489 -> 459 us.
+template <typename TL, typename A, int NR>
+constexpr int fwd2_waves() {
+  return sizeof(TL) < sizeof(A) && NR <= 2 ? (NR == 1 ? 8 : 6) : 1;
+}
 template <typename TD, typename TL, typename A, int NR>
-__global__ __launch_bounds__(256) void k_fwd2(const Unit* __restrict__ units, int64_t nunits,
+__global__ __launch_bounds__(256, (fwd2_waves<TL, A, NR>())) void k_fwd2(const Unit* __restrict__ units, int64_t nunits,
                                               const int32_t* __restrict__ colmap,
                                               const A* __restrict__ z, A* __restrict__ ypart,
                                               int ldmax) {
