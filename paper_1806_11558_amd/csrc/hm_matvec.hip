@@ -1008,7 +1008,7 @@ __global__ __launch_bounds__(256) void k_tr1(const Unit* __restrict__ units, int
 }
 
 // The same on the matrix cores, for 4 to 16 right-hand sides and for small
-// trees (see kTrMfmaLeaves): the columns of a unit, 64 at a time per
+// trees (see tr_mfma): the columns of a unit, 64 at a time per
 // wavefront, are the terms of phase 1 (one leaf, the panel in place of the V
 // slice).  On the vector units every column cost its own reduction over the
 // rows.  Whole products at N = 32,000, leaf 64: FP64 4 columns 1,107 -> 447 us,
@@ -1450,11 +1450,19 @@ __global__ __launch_bounds__(256) void k_tr2_sum(MvLeaves L, int S, const A* __r
 // 64 -> 47, FP32 33 -> 32 and 41 -> 35, of 62 rows, FP32 40 -> 43 and 55 -> 47;
 // 256 leaves of 45 rows, FP64 105 -> 112 and 120 -> 126, FP32 65 -> 67 and
 // 70 -> 69; N = 81,920, leaf 64, FP32 538 -> 614 and 598 -> 665.
-// FP32 factors with double vectors: 64 leaves of 53 rows 37 -> 36 and 46 -> 40,
-// 128 leaves of 45 rows 40 -> 46 and 50 -> 50 us.
+// FP32 factors with double vectors: 64 leaves of 53 rows 38 -> 37 and 45 -> 40,
+// 128 leaves of 45 rows 40 -> 46 and 50 -> 50 us.  These (and FP16
+// factors, alike) go there from 2,200 elements on, or up to 16 leaves per
+// column: 500 elements, 16 leaves 21.0 -> 19.3 and 23.9 -> 21.9 us; 1,280, 32
+// leaves 22.5 -> 25.0 and 26.6 -> 26.3, 64 leaves 22.0 -> 25.4 and 24.3 -> 25.3;
+// 2,000, 64 leaves 26.0 -> 27.5 and 28.4 -> 28.0; 2,420, 64 leaves 30.5 -> 29.8
+// and 36.0 -> 32.4.
 template <typename TL, typename A, int NR>
-constexpr int64_t kTrMfmaLeaves =
-    sizeof(TL) == 8 || (sizeof(A) == 4 && NR == 2) ? 128 : 64;
+static bool tr_mfma(int64_t nleaf, int64_t n) {
+  if (NR >= 4) return true;
+  if (sizeof(TL) < sizeof(A)) return nleaf <= 16 * NR || (nleaf <= 64 && n >= 2200);
+  return nleaf <= (sizeof(TL) == 8 || (sizeof(A) == 4 && NR == 2) ? 128 : 64);
+}
 
 // Four single-precision columns run on the vector units from this many leaves
 // on (vcols: mean columns of a V item).  Blocks whose column leaves differ in ld
@@ -1489,8 +1497,8 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
   if (pr) HM_HIP(hipEventRecord(pr->ev[0], s));
   constexpr bool kVec4 = NR == 4 && sizeof(A) == 4;
   // transposed, on the matrix cores
-  const bool tmx = NR >= 4 ? !(kVec4 && P.L.nleaf >= tr_vec4_leaves<TL>(P.vitem / P.ldmax))
-                           : P.L.nleaf <= kTrMfmaLeaves<TL, A, NR>;
+  const bool tmx = tr_mfma<TL, A, NR>(P.L.nleaf, P.n) &&
+                   !(kVec4 && P.L.nleaf >= tr_vec4_leaves<TL>(P.vitem / P.ldmax));
   if (NR >= 4 || (transposed && tmx))
     k_gather_x<VT, A, NR><<<(unsigned)std::min<int64_t>(P.L.nleaf, 1 << 20), 256, 0, s>>>(
         x, nrhs, k0, nv, P.perm, P.L, z, xt);

@@ -49,3 +49,30 @@ def test_transposed_by_item_width(n, leaf, leaves, sizes, prec, eps):
                 for k in range(nrhs):
                     assert k == 1 or rel2(y[:, k], ref[:, k]) <= bound, (nrhs, k, vdt)
     H.free()
+
+
+@pytest.mark.parametrize("n,leaf,leaves", [
+    (500, 32, 16), (520, 32, 24), (1280, 64, 32), (1280, 24, 64), (2199, 64, 64),
+    (2200, 64, 64), (2560, 24, 128)])
+@pytest.mark.parametrize("prec,eps", [("f32", 1e-6), ("f16", 1e-4)])
+def test_one_double_column_narrow_factors(n, leaf, leaves, prec, eps):
+    """One and two double columns over narrower factors, on both sides of the sizes
+    at which they move between the vector and the matrix units: within 10 eps
+    of 96 exact columns of the oracle."""
+    import paper_1806_11558_amd as hm
+    from oracle import bem
+    from synthetic import icosphere, normal_columns
+    V, T = icosphere(4)
+    T = T[:n]
+    say("one column", n, leaf, prec)
+    H = hm.HMatrix(V, T, leaf_size=leaf, eps=eps, precision=prec)
+    assert len(H.leaves()) == leaves
+    pick = np.random.default_rng(1).choice(n, 96, replace=False)
+    B = bem.Operator(V, T).cols(pick)
+    x = normal_columns(n, 2, seed=5)
+    ref = B.T @ x
+    for nrhs in (1, 2):
+        y = H.matvec_T(torch.tensor(x[:, :nrhs].copy(), device=DEV)).cpu().numpy()[pick]
+        for k in range(nrhs):
+            assert rel2(y[:, k], ref[:, k]) <= 10 * eps, (nrhs, k)
+    H.free()
