@@ -97,15 +97,20 @@ void* dalloc(size_t bytes, hipStream_t s) {
   return dalloc_pool(bytes, s);
 }
 
+// A device that is full may be so because of blocks kept for later builds: they
+// go back, and the request is made once more.
 void* dalloc_pool(size_t bytes, hipStream_t s) {
   void* p = nullptr;
   if (bytes == 0) bytes = 16;
-  hipError_t e = hipMallocFromPoolAsync(&p, bytes, lib_pool(), s);
-  if (e != hipSuccess || p == nullptr) {
+  for (int again = 0; again < 2; ++again) {
+    const hipError_t e = hipMallocFromPoolAsync(&p, bytes, lib_pool(), s);
+    if (e == hipSuccess && p != nullptr) return p;
     (void)hipGetLastError();
-    throw Error{HM_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes failed"};
+    if (e != hipErrorOutOfMemory || again) break;
+    cache_release();
+    trim_pool();
   }
-  return p;
+  throw Error{HM_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes failed"};
 }
 
 void dfree(void* p, hipStream_t s) {
