@@ -732,6 +732,7 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
     // Q0 = r / |r| for active columns
     for (int c = 0; c < nr; ++c) sc[c] = (!conv[c] && !lost[c] && rn[c] > 0) ? 1.0 / rn[c] : 0.0;
     HM_HIP(hipMemcpyAsync(scl, sc.data(), nr * sizeof(double), hipMemcpyHostToDevice, s));
+    ws->seqv += m + 2;                                  // past every step of an earlier cycle, ended or not
     gmres_start(ws->args(), w, scl, s);
     std::vector<int> active(nr);
     for (int c = 0; c < nr; ++c) {
@@ -807,7 +808,6 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
       est1 = estm;
       if (!any) break;
     }
-    ws->seqv += m + 2;
     // x += Q y  (upper triangular solves on the host)
     int kmaxc = 0;
     for (int c = 0; c < nr; ++c) kmaxc = std::max(kmaxc, kc[c]);
