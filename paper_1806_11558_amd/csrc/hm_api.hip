@@ -168,7 +168,6 @@ void cg_update(double* x, double* r, const double* p, const double* q, const dou
                const double* pq, const double* active, int64_t n, int nr, hipStream_t s);
 void cg_dir(double* p, const double* r, const double* rr_new, const double* rr_old,
             const double* active, int64_t n, int nr, hipStream_t s);
-void gmres_copy_col_f32(const double* Q, int64_t ldq, const int* jd, float* out, hipStream_t s);
 
 // ------------------------------------------------------------------ errors
 static thread_local std::string g_err;
@@ -449,7 +448,6 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
   const hm_params& p = h->p;
   const auto t_start = clk::now();
   auto t0 = clk::now();
-  int64_t* tmp = dalloc_t<int64_t>(4, s);
 
   // ---- upload + geometry (application order)
   double* V = dalloc_t<double>(3 * nv, s);
@@ -589,7 +587,6 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
   HM_HIP(hipStreamSynchronize(s));
   h->ms[6] += ms_since(t0);
   if (p.flags & HM_AUTOTUNE) autotune_units(h, s);
-  dfree(tmp, s);
   release_cached_memory(s);
 
   // ---- statistics: block sums on the device, one small copy back

@@ -248,15 +248,9 @@ __global__ __launch_bounds__(256, (fwd1_waves<T, A, NR>())) void k_fwd1(
       const int P = (r + C - 1) / C;
       switch (P) {                                      // uniform over the wavefront
         case 1: fwd1_uniform<T, A, NR, 1>(M, L, z, r, ld, R, C, cg, g, act, lane, tl); break;
-        case 2:
-          if constexpr (PMAX >= 2) fwd1_uniform<T, A, NR, 2>(M, L, z, r, ld, R, C, cg, g, act, lane, tl);
-          break;
-        case 3:
-          if constexpr (PMAX >= 3) fwd1_uniform<T, A, NR, 3>(M, L, z, r, ld, R, C, cg, g, act, lane, tl);
-          break;
-        case 4:
-          if constexpr (PMAX >= 4) fwd1_uniform<T, A, NR, 4>(M, L, z, r, ld, R, C, cg, g, act, lane, tl);
-          break;
+        case 2: fwd1_uniform<T, A, NR, 2>(M, L, z, r, ld, R, C, cg, g, act, lane, tl); break;
+        case 3: fwd1_uniform<T, A, NR, 3>(M, L, z, r, ld, R, C, cg, g, act, lane, tl); break;
+        case 4: fwd1_uniform<T, A, NR, 4>(M, L, z, r, ld, R, C, cg, g, act, lane, tl); break;
         case 5:
           if constexpr (PMAX >= 5) fwd1_uniform<T, A, NR, 5>(M, L, z, r, ld, R, C, cg, g, act, lane, tl);
           break;
