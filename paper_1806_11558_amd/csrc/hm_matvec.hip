@@ -578,10 +578,11 @@ __global__ __launch_bounds__(256) void k_gather_x(const VT* __restrict__ x, int 
 // terms past r - 1 repeat term r - 1 into rows of the result that are not
 // stored.  The loads are temporal: a term's rows are 16 to 128 bytes per tile,
 // pieces of a cache line whose rest the next tile needs (non-temporal, FP64
-// fetched 3.3 GB for 1.8 GB of factors).  Bound by HBM: 16 columns at N =
-// 81,920, FP64 581 -> 448 us (1.8 GB: 4.0 TB/s), FP32 281 -> 227 us; FP16 at N =
-// 162,000 551 -> 272 us; four columns, FP32, 1,458 -> 212 us (on the vector
-// units before).
+// fetched 3.3 GB for 1.8 GB of factors).  16 columns at N = 81,920, FP64 581 ->
+// 440 us, FP32 281 -> 229; FP16 at N = 162,000 551 -> 272 us; four columns, FP32,
+// 1,458 -> 212 us (on the vector units before).  Bound by HBM in FP64: by the
+// counters 2.7 GB (z and lines read again with the 1.8 of factors) at 6.3 TB/s;
+// FP32 5.5, FP16 4.5 TB/s, the matrix cores busy for a fifth to a third.
 template <typename T, typename A, int NTL, int ST, int IU>
 __device__ inline void fwd1x_rows(const T* __restrict__ S, const A* __restrict__ xb, int ld,
                                   int i0, const int (&tc)[NTL], int xo, int lq,
@@ -722,9 +723,10 @@ __global__ __launch_bounds__(256) void k_fwd1x(const VUnit* __restrict__ meta, i
 // column's last rows again, into rows of the result that are not stored.
 // Bound by HBM and by the z rows that every column reads from L2 (64 or 128
 // bytes against 160 or 320 of an FP32 or FP64 panel column of 40 rows):
-// without the z reads it takes 85% of its time.  16 columns at N = 81,920,
-// FP64 1,102 -> 763 us (3.3 GB: 4.3 TB/s), FP32 434 us; FP16 factors at N =
-// 162,000 911 -> 630 us (2.2 GB).  One to four batches in flight, 1,024- or
+// without the z reads it takes 85% of its time.  By the counters HBM moves 5.0
+// (FP64), 4.5 (FP32) and 4.2 TB/s (FP16 factors), a third to a half of the
+// requests hit L2, and the matrix cores are busy for a quarter to a third.  16 columns at N = 81,920, FP64
+// 1,102 -> 755 us, FP32 424 us; FP16 factors at N = 162,000 911 -> 630 us.  One to four batches in flight, 1,024- or
 // 4,096-column units and 1,024 to 8,192 workgroups give the same within 5%.
 template <typename E, int NT>
 __device__ inline int fwd2x_row(int t, int i) {
@@ -1007,8 +1009,10 @@ __global__ __launch_bounds__(256) void k_tr1(const Unit* __restrict__ units, int
 // slice).  On the vector units every column cost its own reduction over the
 // rows.  Whole products at N = 32,000, leaf 64: FP64 4 columns 1,107 -> 447 us,
 // 8 2,222 -> 509, 16 5,196 -> 686; FP32 4 columns 288 -> 247, 16 1,055 -> 395
-// (leaf 32, 4 columns: 235 and 238).  Bound by HBM and by w itself, which is
-// as many bytes as 2/5 of an FP32 panel of 40 rows at 16 columns.
+// (leaf 32, 4 columns: 235 and 238; see tr_vec4_leaves).  Bound by HBM and by w
+// itself, which is as many bytes as 2/5 of an FP32 panel of 40 rows at 16
+// columns: N = 81,920, 5.7 (FP64), 4.9 (FP32) and 4.6 TB/s (FP16 factors), a
+// quarter to a third of it written.
 template <typename T, typename A, int NR>
 __device__ inline void tr1x_unit(const Unit& U, const A* __restrict__ xt, A* __restrict__ w,
                                  int wave, int lane) {
@@ -1316,7 +1320,10 @@ __global__ __launch_bounds__(256) void k_tr2(const int32_t* __restrict__ beg,
 // The same on the matrix cores, where phase 1 runs there: V items are
 // column batches as in the forward phase 2, with consecutive z rows; the w
 // entries of dense items, NR values per row of the leaf, are read as one
-// contiguous run, value e by lane e mod 64.
+// contiguous run, value e by lane e mod 64.  Bound by latency: wavefronts wait
+// 80% of their time, and HBM moves 3.8 (FP64), 3.2 (FP32) and 2.5 TB/s (FP16)
+// with 16 columns at N = 81,920 (729, 434 and 287 us): items are a descriptor,
+// then one or two batches of loads.
 template <typename T, typename A, int NR, int NT>
 __device__ inline void tr2x_items(const TItem* __restrict__ items, int it0, int b1, int step,
                                   int ld, const A* __restrict__ w, const A* __restrict__ z,
@@ -1434,28 +1441,28 @@ __global__ __launch_bounds__(256) void k_tr2_sum(MvLeaves L, int S, const A* __r
 }
 
 // ------------------------------------------------------------------ host side
-// Transposed products of one or two columns run on the matrix cores up to this
-// many leaves (FP64 factors, or two columns in single precision; otherwise
-// fewer), on the vector units above.  Small products wait for loads, and
-// the matrix kernels have all the loads of 64 columns in flight; large ones are
-// bound by HBM, where the vector kernels use fewer, longer wavefronts.  One and
-// two columns, vector -> matrix: 64 leaves of 53 rows, FP64 64 -> 41 and 71 ->
-// 43 us, FP32 41 -> 29 and 50 -> 33; 128 leaves of 45 rows, FP64 57 -> 43 and
-// 64 -> 47, FP32 33 -> 32 and 41 -> 35, of 62 rows, FP32 40 -> 43 and 55 -> 47;
-// 256 leaves of 45 rows, FP64 105 -> 112 and 120 -> 126, FP32 65 -> 67 and
-// 70 -> 69; N = 81,920, leaf 64, FP32 538 -> 614 and 598 -> 665.
+// Transposed products of one or two columns run on the matrix cores up to 128
+// leaves (FP64 factors, or two columns in single precision) or 64, on the vector
+// units above.  Small products wait for loads, and the matrix kernels have all
+// the loads of 64 columns in flight; large ones are bound by HBM, where the
+// vector kernels use fewer, longer wavefronts.  One and two columns, vector ->
+// matrix: 64 leaves of 53 rows, FP64 63 -> 41 and 70 -> 44 us, FP32 37 -> 30 and
+// 41 -> 33; 128 leaves of 45 rows, FP64 74 -> 53 and 79 -> 59, FP32 37 -> 39 and
+// 43 -> 43, FP16 37 -> 37 and 42 -> 40, of 62 rows, FP32 45 -> 52 and 56 -> 57;
+// 256 leaves of 45 rows, FP64 116 -> 123 and 132 -> 138, FP32 65 -> 69 and 73 ->
+// 71; N = 81,920, leaf 64, FP32 532 -> 628 and 590 -> 666.
 // FP32 factors with double vectors: 64 leaves of 53 rows 38 -> 37 and 45 -> 40,
-// 128 leaves of 45 rows 40 -> 46 and 50 -> 50 us.  These (and FP16
-// factors, alike) go there from 2,200 elements on, or up to 16 leaves per
-// column: 500 elements, 16 leaves 21.0 -> 19.3 and 23.9 -> 21.9 us; 1,280, 32
-// leaves 22.5 -> 25.0 and 26.6 -> 26.3, 64 leaves 22.0 -> 25.4 and 24.3 -> 25.3;
-// 2,000, 64 leaves 26.0 -> 27.5 and 28.4 -> 28.0; 2,420, 64 leaves 30.5 -> 29.8
-// and 36.0 -> 32.4.
+// 128 leaves of 45 rows 42 -> 47 and 48 -> 50 us.  These (and FP16 factors,
+// alike) go there from 2,200 elements on, or up to 16 leaves per column: 500
+// elements, 8 leaves 21.0 -> 19.3 and 23.9 -> 21.9 us, 16 leaves the same; 1,280,
+// 32 leaves 22.5 -> 25.0 and 26.6 -> 26.3, 64 leaves 22.0 -> 25.4 and 24.3 ->
+// 25.3; 2,000, 64 leaves 26.3 -> 27.6 and 28.4 -> 28.1; 2,420, 64 leaves 31.5 ->
+// 30.0 and 36.5 -> 32.5.
 template <typename TL, typename A, int NR>
 static bool tr_mfma(int64_t nleaf, int64_t n) {
   if (NR >= 4) return true;
-  if (sizeof(TL) < sizeof(A)) return nleaf <= 16 * NR || (nleaf <= 64 && n >= 2200);
-  return nleaf <= (sizeof(TL) == 8 || (sizeof(A) == 4 && NR == 2) ? 128 : 64);
+  if (sizeof(TL) < 8 && sizeof(A) == 8) return nleaf <= 16 * NR || (nleaf <= 64 && n >= 2200);
+  return nleaf <= (sizeof(TL) == 8 || NR == 2 ? 128 : 64);
 }
 
 // Four single-precision columns run on the vector units from this many leaves
