@@ -371,9 +371,10 @@ __device__ inline void fwd2_run_lds(const Unit& U, int ld, int C, int cg, int g,
         jl[u] = ok[u] ? j : tw - 1;
         Gran<T>::load(St + (int64_t)jl[u] * ld, s[u]);
       }
-      // all loads before the first wait: 148 leaves of 39 rows, FP32, two double
-      // columns 49.9 -> 46.5 us
-      __builtin_amdgcn_sched_barrier(0);
+      // all loads before the first wait, only LDS reads may pass them: 148 leaves of
+      // 39 rows, FP32, two double columns 51.3 -> 48.2 us; N = 81,920, leaf 64,
+      // 624 -> 605, four columns 638 -> 610
+      __builtin_amdgcn_sched_barrier(0x100);
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
 #pragma unroll
@@ -395,10 +396,9 @@ constexpr int fwd2_waves() {
   return sizeof(TL) < sizeof(A) && NR <= 2 ? (NR == 1 ? 8 : 6) : 1;
 }
 template <typename TD, typename TL, typename A, int NR>
-__global__ __launch_bounds__(256, (fwd2_waves<TL, A, NR>())) void k_fwd2(const Unit* __restrict__ units, int64_t nunits,
-                                              const int32_t* __restrict__ colmap,
-                                              const A* __restrict__ z, A* __restrict__ ypart,
-                                              int ldmax) {
+__global__ __launch_bounds__(256, (fwd2_waves<TL, A, NR>())) void k_fwd2(
+    const Unit* __restrict__ units, int64_t nunits, const int32_t* __restrict__ colmap,
+    const A* __restrict__ z, A* __restrict__ ypart, int ldmax) {
   constexpr int G = Gran<TD>::G;
   __shared__ A ybuf[4][kMaxLeaf][NR];
   __shared__ A zt[z_tile<A, NR>() * NR];
@@ -725,9 +725,10 @@ __global__ __launch_bounds__(256) void k_fwd1x(const VUnit* __restrict__ meta, i
 // bytes against 160 or 320 of an FP32 or FP64 panel column of 40 rows):
 // without the z reads it takes 85% of its time.  By the counters HBM moves 5.0
 // (FP64), 4.5 (FP32) and 4.2 TB/s (FP16 factors), a third to a half of the
-// requests hit L2, and the matrix cores are busy for a quarter to a third.  16 columns at N = 81,920, FP64
-// 1,102 -> 755 us, FP32 424 us; FP16 factors at N = 162,000 911 -> 630 us.  One to four batches in flight, 1,024- or
-// 4,096-column units and 1,024 to 8,192 workgroups give the same within 5%.
+// requests hit L2, and the matrix cores are busy for a quarter to a third.  16
+// columns at N = 81,920, FP64 1,102 -> 755 us, FP32 424 us; FP16 factors at N =
+// 162,000 911 -> 630 us.  One to four batches in flight, 1,024- or 4,096-column
+// units and 1,024 to 8,192 workgroups give the same within 5%.
 template <typename E, int NT>
 __device__ inline int fwd2x_row(int t, int i) {
   if (NT == 1) return i;
