@@ -388,13 +388,13 @@ __device__ inline void fwd2_run_lds(const Unit& U, int ld, int C, int cg, int g,
   }
 }
 
-// Factors narrower than the vectors: conversions in flight take registers, and
-// without a bound the wavefronts per SIMD fall from 8 and 6 (one and two columns)
-// to 6 and 4; N = 32,400, leaf 16, FP32, double vectors 334 -> 327 and 489 -> 459 us.
+// Two columns of factors narrower than the vectors: conversions in flight take
+// registers, and without a bound there are four wavefronts per SIMD instead of
+// six; N = 40,500, leaf 16, FP32, double vectors 481 -> 459 us, 5,780, leaf 64,
+// 49.9 -> 46.9.  (One column with all eight: 334 -> 327 us, but 3,380 elements,
+// 64 leaves, 30.2 -> 31.8 and FP16 30.6 -> 32.5.)
 template <typename TL, typename A, int NR>
-constexpr int fwd2_waves() {
-  return sizeof(TL) < sizeof(A) && NR <= 2 ? (NR == 1 ? 8 : 6) : 1;
-}
+constexpr int fwd2_waves() { return sizeof(TL) < sizeof(A) && NR == 2 ? 6 : 1; }
 template <typename TD, typename TL, typename A, int NR>
 __global__ __launch_bounds__(256, (fwd2_waves<TL, A, NR>())) void k_fwd2(
     const Unit* __restrict__ units, int64_t nunits, const int32_t* __restrict__ colmap,
