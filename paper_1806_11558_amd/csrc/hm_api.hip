@@ -276,7 +276,7 @@ struct hm_handle {
   Storage sto;
 
   void *z = nullptr, *w = nullptr, *ypart = nullptr;
-  int64_t ypart_bytes = 0, xt_rows = 0;
+  int64_t z_bytes = 0, ypart_bytes = 0, xt_rows = 0;
   std::unique_ptr<SolveWs> sws;         // graph-replay solve workspace
   std::vector<std::array<double, 2>> tune;   // autotuner: (unit columns, ms)
   int max_nr_t = 1;
@@ -344,6 +344,7 @@ struct hm_handle {
     P.perm = perm;
     P.n = n;
     P.z = z;
+    P.z_bytes = z_bytes;
     P.xt_rows = xt_rows;
     P.w = w;
     P.su = sto.su;
@@ -561,7 +562,8 @@ void build_impl(hm_handle* h, const double* V_host, int64_t nv, const int32_t* T
   t0 = clk::now();
   // ---- product workspace: z = [x ; t] with 16 columns, w for the
   // transposed product sized to at most 2 GB (fewer columns per pass)
-  h->z = h->alloc((size_t)(n + h->sto.toff_total + 1) * kMaxNr * sizeof(double));
+  h->z_bytes = (n + h->sto.toff_total + 1) * kMaxNr * (int64_t)sizeof(double);
+  h->z = h->alloc((size_t)h->z_bytes);
   {
     // partial rows for the most units any unit size of the tuner produces
     int64_t nu = h->sto.nunits;

@@ -217,6 +217,7 @@ struct MvPlan {
   const int32_t* perm;
   int64_t n;
   void* z;                  // workspace: [x in Morton order ; t], 16 columns
+  int64_t z_bytes;
   int64_t xt_rows;          // sum of ld over the leaves: rows of x per leaf
   void* w;                  // workspace: panel-column partial dots
   const float* su;          // per-term scales of FP16 U factors (null: none)

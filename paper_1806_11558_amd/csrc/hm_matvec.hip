@@ -547,7 +547,7 @@ __device__ inline const T* at32(const T* base, uint32_t i) {
 // leaf c holds NR columns of ld_c values at xt + ldpre[c] NR, rows in [m, ld)
 // zero, so that phase 1 reads four rows of one right-hand side with one load
 // and needs no row masks.  Columns nv .. NR - 1 (a pass wider than what is
-// left) are zero.
+// left) are zero.  z may be null.
 template <typename VT, typename A, int NR>
 __global__ __launch_bounds__(256) void k_gather_x(const VT* __restrict__ x, int nrhs, int k0,
                                                   int nv, const int32_t* __restrict__ perm,
@@ -560,7 +560,7 @@ __global__ __launch_bounds__(256) void k_gather_x(const VT* __restrict__ x, int 
     for (int e = threadIdx.x; e < ld * NR; e += blockDim.x) {
       const int i = e / NR, k = e % NR;
       const A v = (i < m && k < nv) ? (A)x[(int64_t)perm[lo + min(i, m - 1)] * nrhs + k0 + min(k, nv - 1)] : (A)0;
-      if (i < m) z[(int64_t)(lo + i) * NR + k] = v;
+      if (z && i < m) z[(int64_t)(lo + i) * NR + k] = v;
       xc[k * ld + i] = v;
     }
   }
@@ -1487,23 +1487,29 @@ static void mv_chunk(const MvPlan& P, const VT* x, VT* y, int nrhs, int k0, int 
                      bool transposed, hipStream_t s) {
   A* z = static_cast<A*>(P.z);
   A* w = static_cast<A*>(P.w);
-  // x per leaf, NR columns of ld values each, at the end of the memory of ypart,
-  // which phase 2 writes after phase 1 has read xt.  Not at its start: lines that
-  // every XCD has just read are slow to write (32 leaves of 40 rows, FP64, two
-  // columns, transposed: the column kernel 13.7 us there, 10.6 at the end, whose
-  // lines phase 2 of a few columns doesn't reach)
-  A* xt = reinterpret_cast<A*>(
-      static_cast<char*>(P.ypart) +
-      ((P.ypart_bytes - P.xt_rows * NR * (int64_t)sizeof(A)) & ~(int64_t)255));
   MvProfile* pr = P.prof;
   if (pr) HM_HIP(hipEventRecord(pr->ev[0], s));
   constexpr bool kVec4 = NR == 4 && sizeof(A) == 4;
   // transposed, on the matrix cores
   const bool tmx = tr_mfma<TL, A, NR>(P.L.nleaf, P.n) &&
                    !(kVec4 && P.L.nleaf >= tr_vec4_leaves<TL>(P.vitem / P.ldmax));
+  // x per leaf, NR columns of ld values each.  Transposed products on the matrix
+  // cores keep it where the others keep x and t: they read no other x, and t is
+  // written when it has been read.  Forward ones keep it at the end of the memory
+  // of ypart, which phase 2 writes after phase 1 has read x.  Not at its start,
+  // and no transposed one there: lines that every XCD has just read are slow to
+  // write (32 leaves of 40 rows, FP64, two columns, transposed: the column kernel
+  // 13.7 us with x at the start, 10.6 at the end, whose lines it doesn't reach;
+  // 8 leaves of 62 rows, FP32, 16 columns, which it does, the product 24.6 us,
+  // 22.7 with x in z)
+  const int64_t xt_bytes = P.xt_rows * NR * (int64_t)sizeof(A);
+  const bool xt_in_z = transposed && tmx && xt_bytes <= P.z_bytes;
+  A* xt = xt_in_z ? z
+                  : reinterpret_cast<A*>(static_cast<char*>(P.ypart) +
+                                         ((P.ypart_bytes - xt_bytes) & ~(int64_t)255));
   if (NR >= 4 || (transposed && tmx))
     k_gather_x<VT, A, NR><<<(unsigned)std::min<int64_t>(P.L.nleaf, 1 << 20), 256, 0, s>>>(
-        x, nrhs, k0, nv, P.perm, P.L, z, xt);
+        x, nrhs, k0, nv, P.perm, P.L, xt_in_z ? nullptr : z, xt);
   else
     k_gather<VT, A><<<grid_for(P.n * NR, 256, 4096), 256, 0, s>>>(x, nrhs, k0, NR, P.perm, P.n, z);
   HM_LAUNCH_CHECK();

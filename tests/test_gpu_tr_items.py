@@ -76,3 +76,26 @@ def test_one_double_column_narrow_factors(n, leaf, leaves, prec, eps):
         for k in range(nrhs):
             assert rel2(y[:, k], ref[:, k]) <= 10 * eps, (nrhs, k)
     H.free()
+
+
+@pytest.mark.parametrize("n,leaf", [(20, 64), (21, 64), (22, 64), (63, 64), (77, 24), (80, 4), (127, 64)])
+def test_small_trees_all_columns(n, leaf):
+    """Trees with no or hardly any admissible block, where x per leaf with its rows
+    padded is longer than x and the terms together: forward and transposed, 1 to 17
+    columns, against the dense matrix of the oracle within 10 eps."""
+    import paper_1806_11558_amd as hm
+    from oracle import bem
+    from synthetic import icosphere, normal_columns
+    V, T = icosphere(2)
+    T = T[:n]
+    say("small trees", n, leaf)
+    H = hm.HMatrix(V, T, leaf_size=leaf, eps=1e-8)
+    B = bem.Operator(V, T).cols(np.arange(n))
+    x = normal_columns(n, 17, seed=6)
+    for M, tr in ((B, False), (B.T, True)):
+        ref = M @ x
+        for nrhs in (1, 2, 4, 8, 16, 17):
+            y = H.matvec(torch.tensor(x[:, :nrhs].copy(), device=DEV), transpose=tr).cpu().numpy()
+            for k in range(nrhs):
+                assert rel2(y[:, k], ref[:, k]) <= 1e-7, (tr, nrhs, k)
+    H.free()
