@@ -269,8 +269,9 @@ __global__ __launch_bounds__(256) void k_gs_final(const double* __restrict__ par
 
 // q = w / |w| into basis vector j + 1 and into the next product's input (xq,
 // double or float; may be null), 0 for a column whose norm is 0 or not finite
-// (the host ends such a column).  |w|^2 is the sum of part (fold) or nsum.  The first workgroup also writes the step's
-// coefficients h1 + h2 and |w| per column to res ([(j + 1) nr], [nr]) and
+// (the host ends such a column).  |w|^2 is the sum of part (fold) or nsum.  The
+// first workgroup also writes the step's coefficients h1 + h2 and |w| per column
+// to res ([(j + 1) nr], [nr]) and
 // then, if seq is given, the number seqv + j + 1 to *seq: res and seq are
 // then host memory that the host polls (else res is device memory whose
 // coefficients may be h1 itself).
