@@ -148,3 +148,32 @@ def test_adjoint_of_nan_raises():
     with pytest.raises(hm.HMError):
         hm.hsolve(f, H)
     H.free()
+
+
+@pytest.mark.parametrize("level,counts", [(0, (3, 16, 17, 24, 63, 65, 100, 200)),
+                                          (1, (5, 15, 17, 33, 40, 96, 129)), (2, (6, 24, 48, 70))])
+@pytest.mark.parametrize("graph", [False, True])
+def test_any_number_of_columns(level, counts, graph):
+    """Columns in groups of up to 64 with as many rows at once as fit, below and above
+    the 16 columns up to which the sums are folded: the residual of every column by the
+    oracle's dense matrix, within the tolerance and 100 ACA eps; every column takes
+    the values it has in a call of its own (to 1e-8, both solves end at 1e-10)."""
+    import paper_1806_11558_amd as hm
+    from oracle import bem
+    from synthetic import icosphere, normal_columns
+    V, T = icosphere(level)
+    n = len(T)
+    say("columns", level, graph)
+    H = hm.HMatrix(V, T, leaf_size=32, eps=1e-10)
+    A = bem.Operator(V, T).cols(np.arange(n))
+    F = normal_columns(n, max(counts), seed=8)
+    for nrhs in counts:
+        f = torch.tensor(F[:, :nrhs].copy(), device=DEV)
+        s, info, status = H.solve(f, tol=1e-10, graph=graph)
+        assert status == hm.HM_OK and info.converged == nrhs
+        x = s.cpu().numpy()
+        for c in range(nrhs):
+            assert np.linalg.norm(A @ x[:, c] - F[:, c]) <= 1.1e-8 * np.linalg.norm(F[:, c]), (nrhs, c)
+        one, _, _ = H.solve(f[:, nrhs - 1:].contiguous(), tol=1e-10, graph=graph)
+        assert rel2(one.cpu().numpy()[:, 0], x[:, nrhs - 1]) <= 1e-8
+    H.free()
