@@ -710,13 +710,13 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
   }
   conv.assign(nr, 0);
   std::vector<int> lost(nr, 0);
-  auto judge = [&]() {
+  auto classify = [&]() {
     for (int c = 0; c < nr; ++c) {
       conv[c] = rel(c, rn[c]) <= tol;
       if (!std::isfinite(rn[c])) lost[c] = 1;
     }
   };
-  judge();
+  classify();
   int total_it = 0;
   // per-column Arnoldi state
   std::vector<double> H((size_t)(m + 1) * m * nr), cs((size_t)m * nr), sn((size_t)m * nr),
@@ -826,7 +826,7 @@ int gmres_core(SolveWs* ws, int64_t n, int nr, int m, double tol, int max_iter,
     }
     ++restarts;
     residual(rn);
-    judge();
+    classify();
   }
   return total_it;
 }
